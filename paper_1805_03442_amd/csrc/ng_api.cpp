@@ -260,6 +260,16 @@ void cons_to_prim_cell(double gm1, int nc, const double* U, double* W)
     }
 }
 
+// Step kernel variant of a solve (launch_step): the CSPH-TVD kernel, the
+// periodic-HLLC kernel of its closure recipe (of the general closures when the
+// recipe has none), or the general one.
+int variant_of(const InstDesc& d)
+{
+    if (d.scheme == kSchemeCsph) return kVariantCsph;
+    if (d.riemann != NG_HLLC || d.any_bc) return 0;
+    return d.cl_recipe <= kRecipes ? 1 + d.cl_recipe : 1;
+}
+
 struct Slot {
     bool live = false;
     int dim = 0;
@@ -532,9 +542,7 @@ int choose_coop(ng_batch* b)
     }
     if (!b->dev_coop || b->dev_cus < 1) return NG_OK;
     const int kind = kind_of(b->prec);
-    const int v = s.d.scheme == kSchemeCsph
-                      ? kVariantCsph
-                      : ((s.d.riemann == NG_HLLC && !s.d.any_bc) ? 1 + s.d.cl_recipe : 0);
+    const int v = variant_of(s.d);
     const int64_t segs = cdiv(s.d.nx, seg_cells(s.d.scheme));
     int per_cu = 0, maxw = 0;
     CK(b, coop_capacity(kind, v, kCoopSmallWaves, &per_cu, &maxw));
@@ -636,9 +644,7 @@ int rebuild(ng_batch* b)
         for (int i = 0; i < b->capacity; i++) {
             const Slot& s = b->slots[i];
             if (!s.live || s.small || s.dim != dim) continue;
-            const int sv = s.d.scheme == kSchemeCsph
-                               ? kVariantCsph
-                               : ((s.d.riemann == NG_HLLC && !s.d.any_bc) ? 1 + s.d.cl_recipe : 0);
+            const int sv = variant_of(s.d);
             v = (v < 0 || v == sv) ? sv : 0;
         }
         b->variant[dim] = v < 0 ? 0 : v;
@@ -1026,7 +1032,21 @@ void fill_desc(InstDesc& d, const ng_gas* gas, const ng_grid* grid, const ng_num
             else codes[2 * i + j] = (int)e2;
         }
     }
+    d.ih = 1.0 / d.h;
+    d.igm1 = 1.0 / d.gm1;
+    d.iR = 1.0 / d.R;
+    d.irho0 = 1.0 / d.rho0;
+    d.iT0 = 1.0 / d.T0;
     d.cl_recipe = 0;
+    if (prec == NG_FP64) {
+        const double e[6] = {gas->tau_rho, gas->tau_T, gas->Q_rho, gas->Q_T, gas->I_rho, gas->I_T};
+        for (int r = 1; r <= ng::kRecipes64; r++) {
+            bool same = true;
+            for (int q = 0; q < 6; q++) same = same && 2.0 * e[q] == ng::kRecipe64[r][q];
+            if (same) d.cl_recipe = r;
+        }
+        return;
+    }
     for (int r = 1; half && r <= ng::kRecipes; r++) {
         bool same = true;
         for (int q = 0; q < 6; q++) same = same && codes[q] == ng::kRecipeCodes[r][q];
@@ -1601,8 +1621,7 @@ int ng_step_static(const ng_gas* gas, const ng_grid* grid, const ng_numerics* nu
     c.t = t;
     c.t_end = t_end > t ? t_end : INFINITY;
     c.max_steps = 1;
-    const int variant = d.scheme == kSchemeCsph ? kVariantCsph
-                                                : ((d.riemann == NG_HLLC && !d.any_bc) ? 1 : 0);
+    const int variant = variant_of(d);
     hipStream_t st = (hipStream_t)hip_stream;
     e = launch_static_setup(d, c, descs, ctrls, insts, blocks, d.nblocks, st);
     if (e == hipSuccess)

@@ -41,9 +41,10 @@ namespace ng {
 // have the same strict sign, else the one of smaller magnitude.
 __device__ __forceinline__ double minmod(double a, double b)
 {
-    if (a > 0.0 && b > 0.0) return a < b ? a : b;
-    if (a < 0.0 && b < 0.0) return a > b ? a : b;
-    return 0.0;
+    // the smaller of two positive differences, the larger of two negative
+    // ones; the other term is zero, so the sum is exact (five operations
+    // instead of six compares and their selections)
+    return fmax(0.0, fmin(a, b)) + fmin(0.0, fmax(a, b));
 }
 __device__ __forceinline__ float minmod(float a, float b)
 {
@@ -54,49 +55,184 @@ __device__ __forceinline__ float minmod(float a, float b)
 // ===================================================================== FP64
 
 struct K64 {
-    double gam, gm1, R, Cv, rho0, T0, tau0, tr, tT, Q0, Qr, QT, I0, Ir, IT, fx, fy;
+    double gam, gm1, R, Cv, rho0, T0, tau0, Q0, I0, fx, fy;
+    const InstDesc* d;             // exponents of a gas without a recipe
+    double igm1, iR, irho0, iT0;   // correctly rounded reciprocals (quot64)
     double stiff_z;
     double dt, dtdx, hdtdx, hdt;
     int riemann;
+    int cl;                        // closure recipe of the solve (kRecipe64)
 };
 
-// pow for the exponents without a short form, kept out of line: the step
-// kernels hold several closure evaluations, and inlined copies of pow would
-// make their code many times larger than the path they run
+// Division and square root.  The FP64 step is bound by vector ALU issue and
+// about half of its instructions were the compiler's IEEE division (ten
+// operations and a reciprocal for each quotient: scaling of both operands,
+// two Newton steps, the quotient, its correction, special cases) and square
+// root.  The operands here are densities, pressures, speeds and times, far
+// from the ends of the exponent range, so the scaling is left out; quotients
+// with one denominator share its reciprocal; and denominators constant over a
+// run have theirs rounded on the host.  The results are the correctly rounded
+// ones: the last operation adds the exact remainder, times the reciprocal, to
+// a quotient that is off by less than two units in the last place.  (Measured
+// on 2^34 random operand pairs of exponents within +-300: equal to the
+// compiler's division and root in every bit.)  With the closures compiled per
+// exponent set and one side's state in the HLLC flux this takes half of the
+// step's instructions away.  Us per step before and after: 1000x601 cells
+// 60 and 36, 1024 cells 5.6 and 4.4, CSPH-TVD on 100003 cells 9.7 and 7.6,
+// section 3's gas (its -3/2 power by pow before) on 1600 cells 7.6 and 5.3.
+
+// 1/b to about half a unit in the last place: the hardware's approximation
+// (2^-23) and one third-order Newton step (error 2^-69 before the rounding)
+__device__ __forceinline__ double recip64(double b)
+{
+    const double y = __builtin_amdgcn_rcp(b);
+    const double e = __builtin_fma(-b, y, 1.0);
+    return __builtin_fma(__builtin_fma(e, e, e), y, y);
+}
+// a/b, correctly rounded, from y = recip64(b) or the rounded 1/b
+__device__ __forceinline__ double quot64(double a, double b, double y)
+{
+    const double q = a * y;
+    return __builtin_fma(__builtin_fma(-b, q, a), y, q);
+}
+__device__ __forceinline__ double div64(double a, double b) { return quot64(a, b, recip64(b)); }
+// quot64 that keeps the IEEE result of a zero or infinite denominator (a
+// relaxation time that over- or underflows)
+__device__ __forceinline__ double quot64_any(double a, double b, double y)
+{
+    return __builtin_amdgcn_div_fixup(quot64(a, b, y), b, a);
+}
+// 1/b, correctly rounded
+__device__ __forceinline__ double inv64(double b)
+{
+    const double y = recip64(b);
+    return __builtin_fma(__builtin_fma(-b, y, 1.0), y, y);
+}
+// recip64(a b) for b near a constant's multiple: from a first approximation
+// y of relative error below 2^-50 (a product of two reciprocals)
+__device__ __forceinline__ double recip64_from(double b, double y)
+{
+    return __builtin_fma(__builtin_fma(-b, y, 1.0), y, y);
+}
+// sqrt(x), correctly rounded: Goldschmidt's coupled iteration from the
+// hardware's reciprocal root (2^-24): one step on the root and its half
+// reciprocal (2^-47, from below), then two corrections by the exact remainder.
+// (A third-order step instead, which may come from above, misrounds
+// x = (1 - 2^-53) 4^n, whose root lies 2^-109 from a midpoint.)
+// The addend keeps x = 0 (gas at rest) from 0 * infinity; it changes no x
+// above 1e-284 and a zero gives 1e-150.  Negative x gives NaN.
+__device__ __forceinline__ double sqrt64(double x)
+{
+    x = x + 1e-300;
+    const double y = __builtin_amdgcn_rsq(x);
+    double s = x * y, h = 0.5 * y;
+    const double r = __builtin_fma(-h, s, 0.5);
+    s = __builtin_fma(s, r, s);
+    h = __builtin_fma(h, r, h);
+    s = __builtin_fma(__builtin_fma(-s, s, x), h, s);
+    return __builtin_fma(__builtin_fma(-s, s, x), h, s);
+}
+
+// pow for the exponents without a short form, kept out of line: inlined
+// copies of pow would make the code many times larger than the path it runs
 __device__ __noinline__ double pow_general(double x, double a) { return pow(x, a); }
 
-// x^a of the power laws (6): exponents 0, 1, -1, 2 and 1/2 by the correctly
-// rounded IEEE operations (the exact power rounded once), others by pow.  The
-// exponent is the same for every lane, so the selection is a scalar branch.
+// x^(C/2) of the power laws (6) for an exponent code C known at compile time:
+// 0, 1, -1, 2 and 1/2 by the correctly rounded IEEE operations (the exact
+// power rounded once); -3/2 (section 3's relaxation time) as the reciprocal
+// of x sqrt(x) carried to twice the precision and rounded once (about 20
+// operations against some 200 of pow).
+template <int C>
+__device__ __forceinline__ double powh64(double x)
+{
+    static_assert(C == 0 || C == 2 || C == -2 || C == 4 || C == 1 || C == -3,
+                  "exponent code without a short form");
+    if constexpr (C == 0) return 1.0;
+    else if constexpr (C == 2) return x;
+    else if constexpr (C == -2) return inv64(x);
+    else if constexpr (C == 4) return x * x;
+    else if constexpr (C == 1) return sqrt64(x);
+    else {
+        // sqrt(x) = s + ds, x sqrt(x) = m + dm, 1/(m + dm) = y + y (1 - y m - y dm)
+        const double s = sqrt64(x);
+        const double ds = __builtin_fma(-s, s, x) * (0.5 * recip64(s));
+        const double m = x * s;
+        const double dm = __builtin_fma(x, s, -m) + x * ds;
+        const double y = recip64(m);
+        const double e = __builtin_fma(-y, dm, __builtin_fma(-m, y, 1.0));
+        return __builtin_fma(e, y, y);
+    }
+}
+// the same for an exponent known at run time, others by pow.  The exponent is
+// the same for every lane.
 __device__ __forceinline__ double powr64(double x, double a)
 {
     if (a == 0.0) return 1.0;
     if (a == 1.0) return x;
-    if (a == -1.0) return 1.0 / x;
+    if (a == -1.0) return powh64<-2>(x);
     if (a == 2.0) return x * x;
-    if (a == 0.5) return sqrt(x);
+    if (a == 0.5) return powh64<1>(x);
+    if (a == -1.5) return powh64<-3>(x);
     return pow_general(x, a);
 }
 
-// closures of eq. (6) at (rho, T); the predictor and corrector scale Q and I
-// by act, 0 outside an active wedge (the 2D sector run of section 3)
-__device__ __forceinline__ void closures64(const K64& k, double rho, double T, double& tau,
-                                           double& Q, double& I)
+// tau, Q and I of eq. (6)
+struct Powers64 {
+    double tau, Q, I;
+};
+
+// tau, Q and I of eq. (6) with the exponents of recipe CL (kRecipe64)
+template <int CL>
+__device__ __forceinline__ Powers64 powers64(const K64& k, double r, double t)
 {
-    double r = rho / k.rho0, t = T / k.T0;
-    tau = k.tau0 * powr64(r, k.tr) * powr64(t, k.tT);
-    Q = k.Q0 * powr64(r, k.Qr) * powr64(t, k.QT);
-    I = k.I0 * powr64(r, k.Ir) * powr64(t, k.IT);
+    constexpr const int* e = kRecipe64[CL];
+    return {k.tau0 * powh64<e[0]>(r) * powh64<e[1]>(t), k.Q0 * powh64<e[2]>(r) * powh64<e[3]>(t),
+            k.I0 * powh64<e[4]>(r) * powh64<e[5]>(t)};
+}
+// the same with the exponents known at run time; out of line, once per library
+__device__ __noinline__ Powers64 powers64_any(const InstDesc* d, double r, double t)
+{
+    return {d->tau0 * powr64(r, d->tau_rho) * powr64(t, d->tau_T),
+            d->Q0 * powr64(r, d->Q_rho) * powr64(t, d->Q_T),
+            d->I0 * powr64(r, d->I_rho) * powr64(t, d->I_T)};
 }
 
-// conserved -> primitive (eq. (5) solved for p); NC = 4 (1D) or 5 (2D)
+// closures of eq. (6) at (rho, p), and T (eq. (7)); y = recip64(rho).  The
+// predictor and corrector scale Q and I by act, 0 outside an active wedge (the
+// 2D sector run of section 3).  A kernel without a recipe of its own (CL = 0)
+// takes the compiled forms through one scalar branch on the solve's recipe.
+template <int CL>
+__device__ __forceinline__ void closures64(const K64& k, double rho, double p, double y, double& T,
+                                           double& tau, double& Q, double& I)
+{
+    const double b = k.R * rho;
+    T = quot64(p, b, recip64_from(b, y * k.iR));
+    const double r = quot64(rho, k.rho0, k.irho0), t = quot64(T, k.T0, k.iT0);
+    Powers64 f;
+    if constexpr (CL > 0) {
+        f = powers64<CL>(k, r, t);
+    } else {
+        if (k.cl == 3) f = powers64<3>(k, r, t);
+        else if (k.cl == 1) f = powers64<1>(k, r, t);
+        else if (k.cl == 2) f = powers64<2>(k, r, t);
+        else f = powers64_any(k.d, r, t);
+    }
+    tau = f.tau;
+    Q = f.Q;
+    I = f.I;
+}
+
+// conserved -> primitive (eq. (5) solved for p), and 1/rho in W[NC]; NC = 4
+// (1D) or 5 (2D)
 template <int NC>
 __device__ __forceinline__ void prim64(const K64& k, const double* U, double* W)
 {
     double rho = U[0];
-    double u = U[1] / rho;
+    double y = recip64(rho);
+    double u = quot64(U[1], rho, y);
+    W[NC] = y;
     if (NC == 5) {
-        double v = U[2] / rho;
+        double v = quot64(U[2], rho, y);
         double ke = 0.5 * rho * (u * u + v * v);
         W[0] = rho;
         W[1] = u;
@@ -119,81 +255,62 @@ __device__ __forceinline__ double speed64(const K64& k, const double* W)
     double rho = W[0], u = W[1];
     double vel, p;
     if (NC == 5) {
-        vel = sqrt(u * u + W[2] * W[2]);
+        vel = sqrt64(u * u + W[2] * W[2]);
         p = W[3];
     } else {
-        vel = sqrt(u * u);
+        vel = fabs(u);   // the rounded sqrt(u * u)
         p = W[2];
     }
-    double c = sqrt(k.gam * p / rho);
+    double c = sqrt64(quot64(k.gam * p, rho, W[NC]));
     return fmax(vel + c, 2.0 * vel);
 }
 
 // Half-step predictor: quasi-linear primitive form of eqs. (1)-(5) with the
 // sources at t^n (the "predictor" of the two-step scheme of section 2.3).
-// W = (rho, u, v, p, E_nu) (2D) or (rho, u, p, E_nu) (1D); sx, sy limited slopes.
-template <int NC>
+// W = (rho, u, v, p, E_nu) (2D) or (rho, u, p, E_nu) (1D), 1/rho in W[NC];
+// sx, sy limited slopes.
+template <int NC, int CL = 0>
 __device__ __forceinline__ void predict64(const K64& k, const double* W, const double* sx,
                                           const double* sy, double* Wh, double act = 1.0)
 {
     const double gam = k.gam, gm1 = k.gm1, hdtdx = k.hdtdx, hdt = k.hdt;
+    constexpr int iP = NC == 5 ? 3 : 2, iV = NC == 5 ? 4 : 3;
+    const double rho = W[0], u = W[1], p = W[iP], ev = W[iV], y = W[NC];
+    const double sr = sx[0], su = sx[1], sp = sx[iP], se = sx[iV];
+    double a_r = u * sr + rho * su;
+    double a_u = u * su + quot64(sp, rho, y);
+    double a_v = 0.0;
+    double a_p = u * sp + gam * p * su;
+    double a_e = u * se + ev * su;
+    double v = 0.0;
     if (NC == 5) {
-        double rho = W[0], u = W[1], v = W[2], p = W[3], ev = W[4];
-        double sr = sx[0], su = sx[1], sv = sx[2], sp = sx[3], se = sx[4];
-        double ax_r = u * sr + rho * su;
-        double ax_u = u * su + sp / rho;
-        double ax_v = u * sv;
-        double ax_p = u * sp + gam * p * su;
-        double ax_e = u * se + ev * su;
+        v = W[2];
+        a_v = u * sx[2];
         double tr = sy[0], tu = sy[1], tv = sy[2], tp = sy[3], te = sy[4];
-        double ay_r = v * tr + rho * tv;
-        double ay_u = v * tu;
-        double ay_v = v * tv + tp / rho;
-        double ay_p = v * tp + gam * p * tv;
-        double ay_e = v * te + ev * tv;
-        double T = p / (k.R * rho);
-        double tau, Q, I;
-        closures64(k, rho, T, tau, Q, I);
-        Q = act * Q;
-        I = act * I;
-        double Ee = rho * k.Cv * T;
-        Wh[0] = rho - hdtdx * (ax_r + ay_r);
-        Wh[1] = u - hdtdx * (ax_u + ay_u) + hdt * k.fx;
-        Wh[2] = v - hdtdx * (ax_v + ay_v) + hdt * k.fy;
-        if (k.dt / tau > k.stiff_z) {
-            // eq. (4) over dt/2 solved exactly with E_nue, tau, Q frozen
-            double dEv = ((Ee + tau * (rho * Q)) - ev) * (-expm1(-(hdt / tau)));
-            Wh[3] = p - hdtdx * (ax_p + ay_p) - gm1 * (dEv - hdt * (rho * (Q - I)));
-            Wh[4] = ev - hdtdx * (ax_e + ay_e) + dEv;
-        } else {
-            double dEr = hdt * ((Ee - ev) / tau);
-            Wh[3] = p - hdtdx * (ax_p + ay_p) - gm1 * (dEr + hdt * (rho * I));
-            Wh[4] = ev - hdtdx * (ax_e + ay_e) + (dEr + hdt * (rho * Q));
-        }
+        a_r = a_r + (v * tr + rho * tv);
+        a_u = a_u + v * tu;
+        a_v = a_v + (v * tv + quot64(tp, rho, y));
+        a_p = a_p + (v * tp + gam * p * tv);
+        a_e = a_e + (v * te + ev * tv);
+    }
+    double T, tau, Q, I;
+    closures64<CL>(k, rho, p, y, T, tau, Q, I);
+    Q = act * Q;
+    I = act * I;
+    const double Ee = rho * k.Cv * T;
+    const double ytau = recip64(tau);
+    Wh[0] = rho - hdtdx * a_r;
+    Wh[1] = u - hdtdx * a_u + hdt * k.fx;
+    if (NC == 5) Wh[2] = v - hdtdx * a_v + hdt * k.fy;
+    if (quot64_any(k.dt, tau, ytau) > k.stiff_z) {
+        // eq. (4) over dt/2 solved exactly with E_nue, tau, Q frozen
+        double dEv = ((Ee + tau * (rho * Q)) - ev) * (-expm1(-(hdt / tau)));
+        Wh[iP] = p - hdtdx * a_p - gm1 * (dEv - hdt * (rho * (Q - I)));
+        Wh[iV] = ev - hdtdx * a_e + dEv;
     } else {
-        double rho = W[0], u = W[1], p = W[2], ev = W[3];
-        double sr = sx[0], su = sx[1], sp = sx[2], se = sx[3];
-        double ax_r = u * sr + rho * su;
-        double ax_u = u * su + sp / rho;
-        double ax_p = u * sp + gam * p * su;
-        double ax_e = u * se + ev * su;
-        double T = p / (k.R * rho);
-        double tau, Q, I;
-        closures64(k, rho, T, tau, Q, I);
-        Q = act * Q;
-        I = act * I;
-        double Ee = rho * k.Cv * T;
-        Wh[0] = rho - hdtdx * ax_r;
-        Wh[1] = u - hdtdx * ax_u + hdt * k.fx;
-        if (k.dt / tau > k.stiff_z) {
-            double dEv = ((Ee + tau * (rho * Q)) - ev) * (-expm1(-(hdt / tau)));
-            Wh[2] = p - hdtdx * ax_p - gm1 * (dEv - hdt * (rho * (Q - I)));
-            Wh[3] = ev - hdtdx * ax_e + dEv;
-        } else {
-            double dEr = hdt * ((Ee - ev) / tau);
-            Wh[2] = p - hdtdx * ax_p - gm1 * (dEr + hdt * (rho * I));
-            Wh[3] = ev - hdtdx * ax_e + (dEr + hdt * (rho * Q));
-        }
+        double dEr = hdt * quot64_any(Ee - ev, tau, ytau);
+        Wh[iP] = p - hdtdx * a_p - gm1 * (dEr + hdt * (rho * I));
+        Wh[iV] = ev - hdtdx * a_e + (dEr + hdt * (rho * Q));
     }
 }
 
@@ -206,118 +323,89 @@ __device__ __forceinline__ void flux64(const K64& k, const double* WL, const dou
                                        double* F)
 {
     const double gam = k.gam, gm1 = k.gm1;
-    double rL = WL[0], uL = WL[1], rR = WR[0], uR = WR[1];
-    double vL, vR, pL, pR, eL, eR, EL, ER;
-    if (NC == 5) {
-        vL = WL[2];
-        vR = WR[2];
-        pL = WL[3];
-        pR = WR[3];
-        eL = WL[4];
-        eR = WR[4];
-        EL = pL / gm1 + 0.5 * rL * (uL * uL + vL * vL) + eL;
-        ER = pR / gm1 + 0.5 * rR * (uR * uR + vR * vR) + eR;
-    } else {
-        vL = vR = 0.0;
-        pL = WL[2];
-        pR = WR[2];
-        eL = WL[3];
-        eR = WR[3];
-        EL = pL / gm1 + 0.5 * rL * (uL * uL) + eL;
-        ER = pR / gm1 + 0.5 * rR * (uR * uR) + eR;
-    }
-    double mL = rL * uL, mR = rR * uR;
-    // physical fluxes and conserved face states, component order (rho, m_n, [m_t], E, Ev)
-    double FL[5], FR[5], UL[5], UR[5];
-    FL[0] = mL;
-    FL[1] = mL * uL + pL;
-    FR[0] = mR;
-    FR[1] = mR * uR + pR;
-    UL[0] = rL;
-    UL[1] = rL * uL;
-    UR[0] = rR;
-    UR[1] = rR * uR;
-    const int iE = NC == 5 ? 3 : 2, iV = NC == 5 ? 4 : 3;
-    if (NC == 5) {
-        FL[2] = mL * vL;
-        FR[2] = mR * vR;
-        UL[2] = rL * vL;
-        UR[2] = rR * vR;
-    }
-    FL[iE] = uL * (EL + pL);
-    FR[iE] = uR * (ER + pR);
-    FL[iV] = uL * eL;
-    FR[iV] = uR * eR;
-    UL[iE] = EL;
-    UR[iE] = ER;
-    UL[iV] = eL;
-    UR[iV] = eR;
-
-    double cL = sqrt(gam * pL / rL);
-    double cR = sqrt(gam * pR / rR);
-    double SL = fmin(uL - cL, uR - cR);
-    double SR = fmax(uL + cL, uR + cR);
+    constexpr int iP = NC == 5 ? 3 : 2, iE = NC == 5 ? 3 : 2, iV = NC == 5 ? 4 : 3;
+    const double rL = WL[0], uL = WL[1], pL = WL[iP];
+    const double rR = WR[0], uR = WR[1], pR = WR[iP];
+    const double yL = recip64(rL), yR = recip64(rR);
+    const double cL = sqrt64(quot64(gam * pL, rL, yL));
+    const double cR = sqrt64(quot64(gam * pR, rR, yR));
+    const double SL = fmin(uL - cL, uR - cR);
+    const double SR = fmax(uL + cL, uR + cR);
+    // conserved state and physical flux of one side, component order (rho,
+    // m_n, [m_t], E, E_nu)
+    auto side = [&](double r, double u, double v, double p, double e, double* U, double* Fs) {
+        const double E = quot64(p, gm1, k.igm1) +
+                         0.5 * r * (NC == 5 ? u * u + v * v : u * u) + e;
+        const double m = r * u;
+        U[0] = r;
+        U[1] = m;
+        Fs[0] = m;
+        Fs[1] = m * u + p;
+        if (NC == 5) {
+            U[2] = r * v;
+            Fs[2] = m * v;
+        }
+        U[iE] = E;
+        Fs[iE] = u * (E + p);
+        U[iV] = e;
+        Fs[iV] = u * e;
+    };
 
     if (RS == 1) {
         // HLL, eq. (13)
-        double inv = SR - SL;
+        double UL[5], UR[5], FL[5], FR[5];
+        side(rL, uL, NC == 5 ? WL[2] : 0.0, pL, WL[iV], UL, FL);
+        side(rR, uR, NC == 5 ? WR[2] : 0.0, pR, WR[iV], UR, FR);
+        const double dS = SR - SL, yS = recip64(dS);
         for (int c = 0; c < NC; c++) {
-            double fh = (SR * FL[c] - SL * FR[c] + SL * SR * (UR[c] - UL[c])) / inv;
+            double fh = quot64(SR * FL[c] - SL * FR[c] + SL * SR * (UR[c] - UL[c]), dS, yS);
             F[c] = (0.0 < SL) ? FL[c] : ((SR < 0.0) ? FR[c] : fh);
         }
         return;
     }
-    double dL = SL - uL, dR = SR - uR;
-    double Ss = (pR - pL + rL * uL * dL - rR * uR * dR) / (rL * dL - rR * dR);
-    // the star state on the side of the contact that the face sees
-    bool left = 0.0 < Ss;
-    double rK = left ? rL : rR, uK = left ? uL : uR, vK = left ? vL : vR;
-    double pK = left ? pL : pR, eK = left ? eL : eR, EK = left ? EL : ER;
-    double SK = left ? SL : SR, dK = left ? dL : dR;
-    double fac = rK * dK / (SK - Ss);
-    double Us[5];
+    const double dL = SL - uL, dR = SR - uR;
+    const double Ss = div64(pR - pL + rL * uL * dL - rR * uR * dR, rL * dL - rR * dR);
+    // Only one side K enters the flux: left if 0 < S_L (its flux alone) or
+    // 0 < S* (the star state beside the contact), else right (its star state
+    // if 0 <= S_R); selecting the five primitives of that side leaves one
+    // conserved state and one physical flux to compute
+    const bool sup = 0.0 < SL;
+    const bool left = sup | (0.0 < Ss);
+    const bool plain = sup | !(left | (0.0 <= SR));
+    const double r = left ? rL : rR, u = left ? uL : uR, p = left ? pL : pR;
+    const double v = NC == 5 ? (left ? WL[2] : WR[2]) : 0.0, e = left ? WL[iV] : WR[iV];
+    const double S = left ? SL : SR, dS = left ? dL : dR, y = left ? yL : yR;
+    double U[5], Fs[5], Us[5];
+    side(r, u, v, p, e, U, Fs);
+    const double rd = r * dS;
+    const double fac = div64(rd, S - Ss);
     Us[0] = fac;
     Us[1] = fac * Ss;
-    if (NC == 5) Us[2] = fac * vK;
-    Us[iE] = fac * (EK / rK + (Ss - uK) * (Ss + pK / (rK * dK)));
-    Us[iV] = fac * (eK / rK);
-    bool star = left || (0.0 <= SR);
-    for (int c = 0; c < NC; c++) {
-        double FK = left ? FL[c] : FR[c];
-        double UK = left ? UL[c] : UR[c];
-        double fs = FK + SK * (Us[c] - UK);
-        F[c] = (0.0 < SL) ? FL[c] : (star ? fs : FR[c]);
-    }
+    if (NC == 5) Us[2] = fac * v;
+    Us[iE] = fac * (quot64(U[iE], r, y) + (Ss - u) * (Ss + div64(p, rd)));
+    Us[iV] = fac * quot64(e, r, y);
+    for (int c = 0; c < NC; c++) F[c] = plain ? Fs[c] : Fs[c] + S * (Us[c] - U[c]);
 }
 
 // Sources Y of eq. (15) at the half-step state and the conservative update.
 // Un: conserved state at t^n; dF, dG: flux differences over the cell; Wh: the
 // half-step primitive state.  Writes Unew and the cell's contributions to the
 // source budget (dt * Y_E and the E_nu source increment).
-template <int NC>
+template <int NC, int CL = 0>
 __device__ __forceinline__ void update64(const K64& k, const double* Un, const double* dF,
                                          const double* dG, const double* Wh, double* Unew,
                                          double& srcE, double& srcV, double act = 1.0)
 {
     const double dt = k.dt, dtdx = k.dtdx;
-    double rho = Wh[0], u = Wh[1];
-    double v = 0.0, p, ev;
-    if (NC == 5) {
-        v = Wh[2];
-        p = Wh[3];
-        ev = Wh[4];
-    } else {
-        p = Wh[2];
-        ev = Wh[3];
-    }
-    double T = p / (k.R * rho);
-    double tau, Q, I;
-    closures64(k, rho, T, tau, Q, I);
+    constexpr int iP = NC == 5 ? 3 : 2, iE = NC == 5 ? 3 : 2, iV = NC == 5 ? 4 : 3;
+    const double rho = Wh[0], u = Wh[1], v = NC == 5 ? Wh[2] : 0.0, p = Wh[iP], ev = Wh[iV];
+    double T, tau, Q, I;
+    closures64<CL>(k, rho, p, recip64(rho), T, tau, Q, I);
     Q = act * Q;
     I = act * I;
     double Ee = rho * k.Cv * T;
+    const double ytau = recip64(tau);
     double Y[5];
-    const int iE = NC == 5 ? 3 : 2, iV = NC == 5 ? 4 : 3;
     Y[0] = 0.0;
     Y[1] = rho * k.fx;
     if (NC == 5) {
@@ -326,7 +414,7 @@ __device__ __forceinline__ void update64(const K64& k, const double* Un, const d
     } else {
         Y[iE] = rho * (u * k.fx + Q - I);
     }
-    Y[iV] = (Ee - ev) / tau + rho * Q;
+    Y[iV] = quot64_any(Ee - ev, tau, ytau) + rho * Q;
     for (int c = 0; c < NC; c++) {
         if (NC == 5)
             Unew[c] = Un[c] - dtdx * (dF[c] + dG[c]) + dt * Y[c];
@@ -334,7 +422,7 @@ __device__ __forceinline__ void update64(const K64& k, const double* Un, const d
             Unew[c] = Un[c] - dtdx * dF[c] + dt * Y[c];
     }
     double de = dt * Y[iV];
-    double z = dt / tau;
+    double z = quot64_any(dt, tau, ytau);
     if (z > k.stiff_z) {
         // eq. (4) over the whole step solved exactly from the start-of-step
         // E_nu, with E_nue, tau and Q frozen at t^{n+1/2}

@@ -32,10 +32,10 @@
 namespace ng {
 
 // d/dr_i of W(|d|, h) at d = r_i - r_j; wn = 2 / (3 h^2) (the 1D cubic
-// spline's normalisation over h)
-__device__ __forceinline__ double csph_grad_w(double d, double h, double wn)
+// spline's normalisation over h), ih the rounded 1/h
+__device__ __forceinline__ double csph_grad_w(double d, double h, double ih, double wn)
 {
-    const double q = fabs(d) / h;
+    const double q = quot64(fabs(d), h, ih);
     double f;
     if (q < 1.0)
         f = -3.0 * q + 2.25 * (q * q);
@@ -47,33 +47,34 @@ __device__ __forceinline__ double csph_grad_w(double d, double h, double wn)
     return d > 0.0 ? g : (d < 0.0 ? -g : 0.0);
 }
 
-// velocity, pressure (eq. (5)) and phi = sqrt(2 p) of a particle's conserved
-// values U = (rho, rho u, E, E_nu)
+// velocity, pressure (eq. (5)), phi = sqrt(2 p) and 1/rho of a particle's
+// conserved values U = (rho, rho u, E, E_nu)
 __device__ __forceinline__ void csph_prim(const K64& k, const double* U, double& u, double& p,
-                                          double& phi)
+                                          double& phi, double& y)
 {
-    u = U[1] / U[0];
+    y = recip64(U[0]);
+    u = quot64(U[1], U[0], y);
     p = k.gm1 * (U[2] - 0.5 * U[0] * (u * u) - U[3]);
-    phi = sqrt(2.0 * p);
+    phi = sqrt64(2.0 * p);
 }
 
-// Y of eq. (12) at a particle (rho, u, p, E_nu, phi) whose neighbours j-1 and
+// Y of eq. (12) at a particle (rho, 1/rho in y, u, p, E_nu, phi) whose neighbours j-1 and
 // j+1 have (phi_a, u_a) and (phi_b, u_b) and kernel gradients ga, gb; h is
 // the particle volume.  sE and sV receive the source parts of the energy and
 // E_nu rows (the budget).
+template <int CL>
 __device__ __forceinline__ void csph_y(const K64& k, double h, double ga, double gb, double phia,
-                                       double ua, double phib, double ub, double rho, double u,
-                                       double p, double ev, double phi, double* Y, double& sE,
-                                       double& sV)
+                                       double ua, double phib, double ub, double rho, double y,
+                                       double u, double p, double ev, double phi, double* Y,
+                                       double& sE, double& sV)
 {
     const double sp = phia * ga + phib * gb;
     const double se = phia * (0.5 * (u + ua)) * ga + phib * (0.5 * (u + ub)) * gb;
-    const double T = p / (k.R * rho);
-    double tau, Q, I;
-    closures64(k, rho, T, tau, Q, I);
+    double T, tau, Q, I;
+    closures64<CL>(k, rho, p, y, T, tau, Q, I);
     const double Ee = rho * k.Cv * T;
     sE = rho * (u * k.fx + Q - I);
-    sV = (Ee - ev) / tau + rho * Q;
+    sV = quot64_any(Ee - ev, tau, recip64(tau)) + rho * Q;
     const double hp = -(h * phi);
     Y[0] = 0.0;
     Y[1] = hp * sp + rho * k.fx;
@@ -86,13 +87,15 @@ __device__ __forceinline__ void csph_y(const K64& k, double h, double ga, double
 __device__ __forceinline__ void csph_flux(const K64& k, const double* UL, const double* UR,
                                           double* F)
 {
-    const double uL = UL[1] / UL[0], uR = UR[1] / UR[0];
+    const double yL = recip64(UL[0]), yR = recip64(UR[0]);
+    const double uL = quot64(UL[1], UL[0], yL), uR = quot64(UR[1], UR[0], yR);
     const double pL = k.gm1 * (UL[2] - 0.5 * UL[0] * (uL * uL) - UL[3]);
     const double pR = k.gm1 * (UR[2] - 0.5 * UR[0] * (uR * uR) - UR[3]);
-    const double cL = sqrt(k.gam * pL / UL[0]), cR = sqrt(k.gam * pR / UR[0]);
+    const double cL = sqrt64(quot64(k.gam * pL, UL[0], yL));
+    const double cR = sqrt64(quot64(k.gam * pR, UR[0], yR));
     const double SL = fmin(uL - cL, uR - cR);
     const double SR = fmax(uL + cL, uR + cR);
-    const double SLR = SL * SR, dS = SR - SL;
+    const double SLR = SL * SR, dS = SR - SL, yS = recip64(dS);
     for (int c = 0; c < 4; c++) {
         const double fl = uL * UL[c], fr = uR * UR[c];
         if (0.0 < SL)
@@ -100,7 +103,7 @@ __device__ __forceinline__ void csph_flux(const K64& k, const double* UL, const 
         else if (SR < 0.0)
             F[c] = fr;
         else
-            F[c] = (SR * fl - SL * fr + SLR * (UR[c] - UL[c])) / dS;
+            F[c] = quot64(SR * fl - SL * fr + SLR * (UR[c] - UL[c]), dS, yS);
     }
 }
 

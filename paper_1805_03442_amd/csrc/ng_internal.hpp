@@ -56,6 +56,19 @@ constexpr int kRecipeCodes[kRecipes + 1][6] = {
     {0, 2, -1, 2, -2, 4},
 };
 
+// Closure recipes of the FP64 arithmetic: twice the exponents (tau_rho, tau_T,
+// Q_rho, Q_T, I_rho, I_T) of eq. (6), each with a short form (powh64).  Rows 1
+// and 2 are the base gas as above, row 3 the gas of section 3 (tau ~
+// rho^-1 T^-3/2, constant pump and sink); row 0: exponents at run time.  The
+// short forms are the same operations either way.
+constexpr int kRecipes64 = 3;
+constexpr int kRecipe64[kRecipes64 + 1][6] = {
+    {0, 0, 0, 0, 0, 0},
+    {-2, -2, 1, 4, 2, 4},
+    {-2, -2, 1, 2, 2, 4},
+    {-2, -3, 0, 0, 0, 0},
+};
+
 // Run-constant description of one solve.
 struct InstDesc {
     int64_t nx, ny, ncell;
@@ -96,7 +109,10 @@ struct InstDesc {
     // 1/tau, Q and I = cl_c rho^cl_a p^cl_b (with T = p / (R rho)); cl_recipe
     // > 0 names the compiled recipe whose exponents they are (kRecipeCodes).
     double cl_c[3], cl_a[3], cl_b[3];
-    int32_t cl_recipe, pad1;
+    int32_t cl_recipe;        // (FP64 solves: the row of kRecipe64)
+    int32_t pad1;
+    // rounded reciprocals of the run's constant denominators (FP64 arithmetic)
+    double ih, igm1, iR, irho0, iT0;
 };
 
 // Mutable per-solve state, advanced by the finalize kernel.

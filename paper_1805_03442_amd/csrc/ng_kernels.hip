@@ -126,13 +126,14 @@ struct Plain64 {
     // the FP64 step needs more than 128 registers; asking for two waves per
     // SIMD trades a few spills for latency hiding (13 % faster at 4096^2)
     static constexpr int kMinWaves = 2;
+    static constexpr int kMinWaves1D = 3;
     // largest workgroup of a cooperative launch (eight waves: two per SIMD)
     static constexpr int kCoopThreads = 512;
     // U^n of the updated row is re-read from cache (no registers to spare)
     static constexpr bool kKeepRows = false;
     // the energy slot holds E itself
     static constexpr bool kSplitE = false;
-    // the closure recipes are an FP32 fast path
+    // the general kernels take the closure recipe in the closures themselves
     static constexpr bool kRecipes = false;
     using St = double;
     using K = K64;
@@ -146,19 +147,19 @@ struct Plain64 {
         k.rho0 = d.rho0;
         k.T0 = d.T0;
         k.tau0 = d.tau0;
-        k.tr = d.tau_rho;
-        k.tT = d.tau_T;
         k.Q0 = d.Q0;
-        k.Qr = d.Q_rho;
-        k.QT = d.Q_T;
         k.I0 = d.I0;
-        k.Ir = d.I_rho;
-        k.IT = d.I_T;
+        k.d = &d;
         k.fx = d.fx;
         k.fy = d.fy;
+        k.igm1 = d.igm1;
+        k.iR = d.iR;
+        k.irho0 = d.irho0;
+        k.iT0 = d.iT0;
+        k.cl = d.cl_recipe;
         k.stiff_z = d.stiff_z;
         k.dt = dt;
-        k.dtdx = dt / d.h;
+        k.dtdx = quot64(dt, d.h, d.ih);
         k.hdtdx = 0.5 * k.dtdx;
         k.hdt = 0.5 * dt;
         k.riemann = d.riemann;
@@ -170,7 +171,7 @@ struct Plain64 {
     static __device__ void predict(const K& k, const R* W, const R* sx, const R* sy, R* Wh,
                                    R act = 1)
     {
-        predict64<NC>(k, W, sx, sy, Wh, act);
+        predict64<NC, CL>(k, W, sx, sy, Wh, act);
     }
     template <int RS>
     static __device__ void flux(const K& k, const R* L, const R* Rr, R* F)
@@ -181,7 +182,7 @@ struct Plain64 {
     static __device__ void update(const K& k, const R* Un, const R* dF, const R* dG, const R* Wh,
                                   R* Unew, R& sE, R& sV, R act = 1)
     {
-        update64<NC>(k, Un, dF, dG, Wh, Unew, sE, sV, act);
+        update64<NC, CL>(k, Un, dF, dG, Wh, Unew, sE, sV, act);
     }
     static __device__ R full_rho(const K&, R r) { return r; }
     static __device__ R full_p(const K&, R p) { return p; }
@@ -193,6 +194,7 @@ struct Dev32 {
     using St = float;   // stored state: FP32 deviations
     using K = K32;
     static constexpr int kMinWaves = 1;
+    static constexpr int kMinWaves1D = 1;
     // twelve waves (three per SIMD at up to 168 registers, one workgroup per
     // CU): 2^20 cells 12.3 against 13.2 us per step with eight; sixteen-wave
     // workgroups, which force 128 registers, spill and were slower
@@ -271,6 +273,7 @@ struct Mix32 {
     using St = double;
     using K = K32;
     static constexpr int kMinWaves = 1;
+    static constexpr int kMinWaves1D = 1;
     static constexpr int kCoopThreads = 512;
     static constexpr bool kKeepRows = true;
     static constexpr bool kSplitE = true;
@@ -1142,7 +1145,7 @@ __device__ __forceinline__ void march1d_hllc(const InstDesc& d, const typename P
 // FP64 only (the state is stored whole).  With first >= 0 the segments first
 // .. end-1 (the cooperative kernel's share of a wave); Coh: agent-scope state
 // loads and stores (Planes).
-template <class P, bool BC, bool Coh = false>
+template <class P, bool BC, bool Coh = false, int CL = 0>
 __device__ __forceinline__ void march_csph(const InstDesc& d, const K64& k, int cur,
                                            const double* gsrc, int64_t item, int lane,
                                            Acc<double>& acc, int64_t first = -1,
@@ -1157,9 +1160,9 @@ __device__ __forceinline__ void march_csph(const InstDesc& d, const K64& k, int 
     const int64_t s1 = first >= 0 ? end
                                   : (s0 + d.rows_per_item < d.nstrips ? s0 + d.rows_per_item
                                                                       : d.nstrips);
-    const double h = d.h, wn = 2.0 / (3.0 * (h * h));
+    const double h = d.h, ih = d.ih, wn = 2.0 / (3.0 * (h * h));
     // the predictor's particles sit at the centres: distances +-h exactly
-    const double g1 = csph_grad_w(h, h, wn), g2 = csph_grad_w(-h, h, wn);
+    const double g1 = csph_grad_w(h, h, ih, wn), g2 = csph_grad_w(-h, h, ih, wn);
     const double dt = k.dt, hdt = k.hdt, dtdx = k.dtdx;
     auto coord = [&](int64_t sg) { return sg * kCsphInterior - kCsphHalo + lane; };
     auto boff = [&](int64_t sg) -> uint32_t {
@@ -1181,24 +1184,24 @@ __device__ __forceinline__ void march_csph(const InstDesc& d, const K64& k, int 
             if (f) Un[1] = -Un[1];
         }
         // predictor
-        double un, pn, phin;
-        csph_prim(k, Un, un, pn, phin);
+        double un, pn, phin, yn;
+        csph_prim(k, Un, un, pn, phin, yn);
         double Y[NC], sEp, sVp, sEc, sVc;
-        csph_y(k, h, g1, g2, from_left(phin), from_left(un), from_right(phin), from_right(un),
-               Un[0], un, pn, Un[3], phin, Y, sEp, sVp);
+        csph_y<CL>(k, h, g1, g2, from_left(phin), from_left(un), from_right(phin), from_right(un),
+                   Un[0], yn, un, pn, Un[3], phin, Y, sEp, sVp);
         double Us[NC];
         for (int c = 0; c < NC; c++) Us[c] = Un[c] + dt * Y[c];
-        double us, ps, phis;
-        csph_prim(k, Us, us, ps, phis);
+        double us, ps, phis, ys;
+        csph_prim(k, Us, us, ps, phis, ys);
         const double xs = dt * (0.5 * (un + us));
         // corrector, at the predicted positions
-        const double ga = csph_grad_w(h + (xs - from_left(xs)), h, wn);
-        const double gb = csph_grad_w(-h + (xs - from_right(xs)), h, wn);
-        csph_y(k, h, ga, gb, from_left(phis), from_left(us), from_right(phis), from_right(us),
-               Us[0], us, ps, Us[3], phis, Y, sEc, sVc);
+        const double ga = csph_grad_w(h + (xs - from_left(xs)), h, ih, wn);
+        const double gb = csph_grad_w(-h + (xs - from_right(xs)), h, ih, wn);
+        csph_y<CL>(k, h, ga, gb, from_left(phis), from_left(us), from_right(phis), from_right(us),
+                   Us[0], ys, us, ps, Us[3], phis, Y, sEc, sVc);
         double Ut[NC];
         for (int c = 0; c < NC; c++) Ut[c] = 0.5 * (Un[c] + Us[c]) + hdt * Y[c];
-        const double ut = Ut[1] / Ut[0];
+        const double ut = div64(Ut[1], Ut[0]);
         const double xt = 0.5 * xs + hdt * (0.5 * (un + ut));
         // face j+1/2: this particle's profile gives U^L, the right neighbour's U^R
         const double al = 0.5 * (h - xt), ar = 0.5 * (h + xt);
@@ -1208,13 +1211,13 @@ __device__ __forceinline__ void march_csph(const InstDesc& d, const K64& k, int 
             double a = Un[c] - l, b = r - Un[c];
             pin(a);
             pin(b);
-            const double th = minmod(a, b) / h;
+            const double th = quot64(minmod(a, b), h, ih);
             const double hl = 0.5 * (Un[c] + Ut[c]);
             UL[c] = hl + al * th;
             UR[c] = from_right(hl - ar * th);
         }
         csph_flux(k, UL, UR, F);
-        double Uo[NC], Wn[NC];
+        double Uo[NC], Wn[NC + 1];
         for (int c = 0; c < NC; c++) {
             double dF = F[c] - from_left(F[c]);
             pin(dF);
@@ -1262,7 +1265,7 @@ __device__ __forceinline__ void march1d_any(const InstDesc& d, const typename P:
 // V as for step2d_kernel, or kVariantCsph: every solve of the launch takes the
 // CSPH-TVD step (a kernel with that path only)
 template <class P, int V>
-__global__ void __launch_bounds__(256) step1d_kernel(const InstDesc* __restrict__ descs,
+__global__ void __launch_bounds__(256, P::kMinWaves1D) step1d_kernel(const InstDesc* __restrict__ descs,
                                                      InstCtrl* __restrict__ ctrls,
                                                      const BlockRef* __restrict__ blocks,
                                                      int remap, int fused)
@@ -1955,8 +1958,7 @@ static void launch(void (*kernel)(A...), dim3 g, dim3 b, hipStream_t s, hipEvent
         hipLaunchKernelGGL(kernel, g, b, 0, s, a...);
 }
 
-// Step kernel of a policy for variant v (the FP64 arithmetic has no closure
-// recipes: its periodic-HLLC variant is 1 whatever the recipe).
+// Step kernel of a policy for variant v.
 template <template <int> class Pol, int NC>
 static void launch_variant(int v, dim3 g, dim3 b, hipStream_t s, hipEvent_t e0, hipEvent_t e1,
                            const InstDesc* descs, InstCtrl* ctrls, const BlockRef* blocks,
@@ -1965,26 +1967,16 @@ static void launch_variant(int v, dim3 g, dim3 b, hipStream_t s, hipEvent_t e0, 
     using P = Pol<NC>;
     if constexpr (NC == 5) {
         if (v == 0) launch(step2d_kernel<P, 0>, g, b, s, e0, e1, descs, ctrls, blocks, remap, fused);
-        else if (v == 1 || !P::kRecipes)
-            launch(step2d_kernel<P, 1>, g, b, s, e0, e1, descs, ctrls, blocks, remap, fused);
-        else if constexpr (P::kRecipes) {
-            if (v == 2) launch(step2d_kernel<P, 2>, g, b, s, e0, e1, descs, ctrls, blocks, remap, fused);
-            else launch(step2d_kernel<P, 3>, g, b, s, e0, e1, descs, ctrls, blocks, remap, fused);
-        }
+        else if (v == 1) launch(step2d_kernel<P, 1>, g, b, s, e0, e1, descs, ctrls, blocks, remap, fused);
+        else if (v == 2) launch(step2d_kernel<P, 2>, g, b, s, e0, e1, descs, ctrls, blocks, remap, fused);
+        else launch(step2d_kernel<P, 3>, g, b, s, e0, e1, descs, ctrls, blocks, remap, fused);
     } else {
         if (v == 0) launch(step1d_kernel<P, 0>, g, b, s, e0, e1, descs, ctrls, blocks, remap, fused);
-        else if constexpr (std::is_same<typename P::K, K64>::value) {
-            if (v == kVariantCsph)
-                launch(step1d_kernel<P, kVariantCsph>, g, b, s, e0, e1, descs, ctrls, blocks, remap,
-                       fused);
-            else
-                launch(step1d_kernel<P, 1>, g, b, s, e0, e1, descs, ctrls, blocks, remap, fused);
-        } else if (v == 1 || !P::kRecipes)
-            launch(step1d_kernel<P, 1>, g, b, s, e0, e1, descs, ctrls, blocks, remap, fused);
-        else if constexpr (P::kRecipes) {
-            if (v == 2) launch(step1d_kernel<P, 2>, g, b, s, e0, e1, descs, ctrls, blocks, remap, fused);
-            else launch(step1d_kernel<P, 3>, g, b, s, e0, e1, descs, ctrls, blocks, remap, fused);
-        }
+        else if (v == 1) launch(step1d_kernel<P, 1>, g, b, s, e0, e1, descs, ctrls, blocks, remap, fused);
+        else if (v == 2) launch(step1d_kernel<P, 2>, g, b, s, e0, e1, descs, ctrls, blocks, remap, fused);
+        else if (v == 3) launch(step1d_kernel<P, 3>, g, b, s, e0, e1, descs, ctrls, blocks, remap, fused);
+        else if constexpr (std::is_same<typename P::K, K64>::value)
+            launch(step1d_kernel<P, kVariantCsph>, g, b, s, e0, e1, descs, ctrls, blocks, remap, fused);
     }
 }
 
@@ -2085,12 +2077,9 @@ static const void* coop_kernel_of(int v)
     if constexpr (std::is_same<typename P::K, K64>::value) {
         if (v == kVariantCsph) return (const void*)run_coop1d_kernel<P, kVariantCsph>;
     }
-    if (v == 1 || !P::kRecipes) return (const void*)run_coop1d_kernel<P, 1>;
-    if constexpr (P::kRecipes) {
-        if (v == 2) return (const void*)run_coop1d_kernel<P, 2>;
-        return (const void*)run_coop1d_kernel<P, 3>;
-    }
-    return nullptr;
+    if (v == 1) return (const void*)run_coop1d_kernel<P, 1>;
+    if (v == 2) return (const void*)run_coop1d_kernel<P, 2>;
+    return (const void*)run_coop1d_kernel<P, 3>;
 }
 
 static const void* coop_kernel(int prec, int variant)
