@@ -62,17 +62,24 @@ constexpr int kSmallWaves = 8;
 // step kernel (last workgroup); beyond it the per-workgroup release fence costs
 // more than the separate finalize launch.
 constexpr int64_t kFusedMaxBlocks = 256;
-// A batch's only solve, when it is 1D with at most this many cells and no
-// forced source, runs in the cooperative kernel: many steps per launch over
-// many workgroups, with a grid barrier per step instead of two launches.
+// A batch's only solve, when it is 1D with at most this many cells, runs in the
+// cooperative kernel: many steps per launch over many workgroups, with one
+// exchange per step instead of two launches.
 constexpr int64_t kCoopCells = int64_t(1) << 22;
-// polls of a grid-barrier wait before it gives up (each a memory round trip
+// polls of an exchange's wait before it gives up (each a memory round trip
 // of about a microsecond and a short sleep: about a second)
 constexpr int32_t kCoopSpin = 1 << 20;
-// a cooperative launch gives each work item a wave of its own, four waves
-// per workgroup (one per SIMD of a CU), while the items fit in that many
-// workgroups; more items take the kernel's largest workgroups
-constexpr int kCoopSmallWaves = 4;
+// Cooperative launch shape (resident_shape): solves of up to kResSolo* segments
+// run in one workgroup, which needs no exchange (us per step of 480 cells, 8
+// segments, in one and in two workgroups: FP32 1.74 and 1.95, FP64, whose
+// second wave per SIMD costs more than the exchange, 2.9 and 2.6); larger ones
+// take a workgroup per kResSegs segments, one wave per SIMD (1024 to 65536
+// cells with 4, 6 and 8 segments: FP64 2.9, 3.6, 3.6 to 4.7, 5.3, 5.2; FP32
+// 2.2, 2.3, 2.3 to 3.3, 4.5, 4.4), at most one per CU: 262144 FP64 cells on 64,
+// 128 and 256 CUs 19.5, 11.3, 8.0.
+constexpr int64_t kResSolo64 = 4;
+constexpr int64_t kResSolo32 = 8;
+constexpr int64_t kResSegs = 4;
 // Pinned staging buffers of the initial-state upload (two, used in turn).
 constexpr size_t kStageBytes = size_t(16) << 20;
 // Host threads converting one staging chunk, and the cells each takes at least.
@@ -111,11 +118,25 @@ size_t solve_bytes(const ng_grid* g, int prec)
     return 2 * state_plane_bytes(g, prec) + align_up((size_t)partial_cap_of(g) * sizeof(Partial));
 }
 
+// Workgroups a cooperative launch of a lone solve can have (slots in its
+// header): what resident_shape takes at most.
+size_t res_wgs_of(const ng_grid* g)
+{
+    if (g->ndim != 1) return 0;
+    return (size_t)std::min<int64_t>(cdiv(strips_of(g), kResSegs), kCoopFlat);
+}
+// The same for a batch, at most 1/64 of its arena (none in an arena below 4 MB)
+size_t res_wgs_of(size_t arena_bytes)
+{
+    const size_t n = std::min<size_t>(arena_bytes / 64 / res_space(1), kCoopFlat);
+    return n < 64 ? 0 : n;
+}
+
 struct Layout {
-    size_t descs, ctrls, insts, iota, coop, blocks1, blocks2, heap;
+    size_t descs, ctrls, insts, iota, res, blocks1, blocks2, heap;
 };
 
-Layout header_layout(int capacity, size_t tcap1, size_t tcap2)
+Layout header_layout(int capacity, size_t tcap1, size_t tcap2, size_t nwg)
 {
     Layout L;
     size_t o = 0;
@@ -127,8 +148,8 @@ Layout header_layout(int capacity, size_t tcap1, size_t tcap2)
     o += align_up(sizeof(int32_t) * 5 * capacity);
     L.iota = o;
     o += align_up(sizeof(int32_t) * capacity);
-    L.coop = o;
-    o += align_up(sizeof(CoopSync));
+    L.res = o;
+    if (nwg) o += align_up(res_space(nwg));
     L.blocks1 = o;
     o += align_up(sizeof(BlockRef) * tcap1);
     L.blocks2 = o;
@@ -283,6 +304,15 @@ struct Slot {
     bool reported = false;
 };
 
+// One cooperative launch: its solve, kernel and shape (launch_resident).
+struct ResLaunch {
+    int s = 0;
+    bool lds = false;
+    int grid = 0, waves = 0;
+    size_t lds_bytes = 0;
+    ResGroup one{};
+};
+
 }  // namespace
 
 struct ng_batch {
@@ -304,8 +334,10 @@ struct ng_batch {
     int64_t small_limit = -1;  // cells; -1: by precision, 0: persistent path off
     int64_t coop_limit = -1;   // cells; -1: kCoopCells, 0: cooperative path off
     int32_t coop_spin = kCoopSpin;
-    int coop_slot = -1;        // the solve the cooperative kernel advances, or -1
-    int coop_grid = 0, coop_waves = 0, coop_variant = 0;
+    // the cooperative launches of one call (none: the other paths run)
+    std::vector<ResLaunch> res;
+    size_t res_nwg = 0;        // workgroups the arena header has slots for
+    uint64_t res_steps = 0;    // step numbers used since the slots were cleared
     int dev_coop = -1;         // cooperative launch supported (-1: not asked yet)
     int dev_cus = 0;
     int fused = 1;             // step kernels accept their own step (last workgroup)
@@ -347,7 +379,16 @@ struct ng_batch {
     int32_t* d_insts(int dim) { return (int32_t*)(arena + L.insts) + dim * capacity; }
     int32_t* d_small(int dim) { return (int32_t*)(arena + L.insts) + (2 + dim) * capacity; }
     int32_t* d_iota() { return (int32_t*)(arena + L.iota); }
-    CoopSync* d_coop() { return (CoopSync*)(arena + L.coop); }
+    ResSync d_sync()
+    {
+        char* p = arena + L.res;
+        ResSync y;
+        y.base = (uint32_t*)p;
+        y.slots = (uint64_t*)(p + 256);
+        y.edges = y.slots + 2 * kResSlot * res_nwg;
+        y.nwg = (int32_t)res_nwg;
+        return y;
+    }
     BlockRef* d_blocks(int dim) { return (BlockRef*)(arena + (dim == 1 ? L.blocks1 : L.blocks2)); }
 };
 
@@ -487,7 +528,7 @@ void shape_solve(ng_batch* b, Slot& s, bool alone = true)
 {
     InstDesc& d = s.d;
     int dim = s.dim;
-    d.waves_per_block = s.small ? 1 : (s.coop ? kCoopSmallWaves : waves_of(b, dim, {{d.nx, d.ny}}));
+    d.waves_per_block = s.small ? 1 : (s.coop ? kResMinWaves : waves_of(b, dim, {{d.nx, d.ny}}));
     if (s.small)
         d.rows_per_item = dim == 2 ? kSmallRows2D : kSmallSegs1D;
     else if (s.coop)
@@ -508,18 +549,46 @@ void shape_solve(ng_batch* b, Slot& s, bool alone = true)
     d.fused = (b->fused && alone && !s.small && d.nblocks <= kFusedMaxBlocks) ? 1 : 0;
 }
 
-// The cooperative path: a batch whose only live solve is 1D, has no forced
-// source and at most coop_limit cells, on a device that supports cooperative
-// launches.  Marks that solve (Slot::coop), sets coop_slot (else -1) and the
-// launch shape: while the segments (60 cells, 58 for CSPH-TVD) fit one per
-// wave in workgroups of kCoopSmallWaves waves (one per SIMD) with at most one
-// workgroup per CU, that; else workgroups of the kernel's largest size, as
-// many as stay resident together (and have a segment for every wave), at
-// most kCoopFlat (the slots of the grid barrier); the kernel deals the
-// segments to the waves in runs.
+// Kernel of a 1D solve on the cooperative path (launch_resident).  The FP32
+// closures of a solve with a boundary are the general ones, as in the step
+// kernels; the FP64 recipes are the same operations either way.
+int resident_kernel_of(const InstDesc& d, int prec)
+{
+    if (d.scheme == kSchemeCsph) return d.cl_recipe == 1 ? 6 : 5;
+    if (d.riemann == NG_HLL) return 4;
+    return prec != NG_FP64 && d.any_bc ? 0 : d.cl_recipe;
+}
+
+// Shape of a solve's cooperative launch: its workgroups, the waves of each (a
+// wave per segment while there are enough, at least kResMinWaves), and where
+// the cells stay.
+void resident_shape(const InstDesc& d, int prec, int cus, ResLaunch& r)
+{
+    const int64_t w = seg_cells(d.scheme), halo = (kWave - w) / 2;
+    const int64_t segs = cdiv(d.nx, w);
+    const int64_t cap = std::min<int64_t>(cus, kCoopFlat);
+    const int64_t solo = prec == NG_FP64 ? kResSolo64 : kResSolo32;
+    const int64_t G = segs <= solo ? 1 : std::min<int64_t>(cdiv(segs, kResSegs), cap);
+    const int64_t most = cdiv(segs, G);   // segments of the largest share
+    const size_t cell = 4 * real_size(prec);
+    r.s = resident_kernel_of(d, prec);
+    r.one.G = (int32_t)G;
+    r.one.first = 0;
+    r.one.pitch = (int32_t)(most * w + 2 * halo);
+    r.lds_bytes = 2 * cell * (size_t)r.one.pitch;
+    r.lds = r.lds_bytes <= kResLdsBytes;
+    if (!r.lds) r.lds_bytes = 2 * cell * (size_t)(2 * halo);
+    r.grid = (int)G;
+    r.waves = (int)std::min<int64_t>(std::max<int64_t>(most, kResMinWaves),
+                                     resident_max_waves(kind_of(prec)));
+}
+
+// The cooperative path: a batch whose only live solve is 1D and has at most
+// coop_limit cells, on a device that supports cooperative launches.  Marks
+// that solve (Slot::coop) and plans its launch.
 int choose_coop(ng_batch* b)
 {
-    b->coop_slot = -1;
+    b->res.clear();
     int live = 0, cand = -1;
     for (int i = 0; i < b->capacity; i++) {
         Slot& s = b->slots[i];
@@ -529,7 +598,7 @@ int choose_coop(ng_batch* b)
         cand = i;
     }
     const int64_t lim = b->coop_limit >= 0 ? b->coop_limit : kCoopCells;
-    if (live != 1 || lim == 0) return NG_OK;
+    if (live != 1 || lim == 0 || b->res_nwg == 0) return NG_OK;
     Slot& s = b->slots[cand];
     if (s.dim != 1 || s.d.ncell > lim) return NG_OK;
     if (b->dev_coop < 0) {
@@ -541,38 +610,37 @@ int choose_coop(ng_batch* b)
         b->dev_cus = cus;
     }
     if (!b->dev_coop || b->dev_cus < 1) return NG_OK;
-    const int kind = kind_of(b->prec);
-    const int v = variant_of(s.d);
-    const int64_t segs = cdiv(s.d.nx, seg_cells(s.d.scheme));
-    int per_cu = 0, maxw = 0;
-    CK(b, coop_capacity(kind, v, kCoopSmallWaves, &per_cu, &maxw));
-    int waves = kCoopSmallWaves;
-    if (segs > (int64_t)kCoopSmallWaves * b->dev_cus) {
-        waves = maxw;
-        CK(b, coop_capacity(kind, v, waves, &per_cu, &maxw));
-    }
-    const int64_t resident = (int64_t)per_cu * b->dev_cus;
-    const int64_t grid = std::min<int64_t>(std::min<int64_t>(cdiv(segs, waves), resident),
-                                           kCoopFlat);
-    if (grid < 1 || coop_space((uint64_t)grid) > (uint64_t)s.partial_cap * sizeof(Partial))
+    ResLaunch r;
+    resident_shape(s.d, b->prec, b->dev_cus, r);
+    int per_cu = 0;
+    CK(b, resident_capacity(kind_of(b->prec), r.s, r.lds, r.waves, r.lds_bytes, &per_cu));
+    if ((int64_t)per_cu * b->dev_cus < r.grid || (size_t)r.grid > b->res_nwg ||
+        coop_space((uint64_t)r.grid) > align_up((size_t)s.partial_cap * sizeof(Partial)))
         return NG_OK;
+    r.one.inst = cand;
     s.coop = true;
-    b->coop_slot = cand;
-    b->coop_grid = (int)grid;
-    b->coop_waves = waves;
-    b->coop_variant = v;
+    b->res.push_back(r);
     return NG_OK;
 }
 
-// Launch the cooperative kernel for nsteps steps (in launches of at most
+// Enqueue the cooperative launches for nsteps steps (each of at most
 // kCoopMaxSteps steps).
 int enqueue_coop(ng_batch* b, int64_t nsteps)
 {
     for (int64_t left = nsteps; left > 0;) {
         const int64_t n = std::min<int64_t>(left, kCoopMaxSteps);
-        CK(b, launch_coop(kind_of(b->prec), b->coop_variant, b->d_descs(), b->d_ctrls(),
-                          b->coop_slot, b->d_coop(), b->coop_grid, b->coop_waves, n,
-                          b->coop_spin, b->stream));
+        for (const ResLaunch& r : b->res) {
+            // the step numbers are 32 bits wide: start them over long before
+            // they can meet an old one
+            b->res_steps += (uint64_t)n + 1;
+            if (b->res_steps > (uint64_t(1) << 31)) {
+                CK(b, hipMemsetAsync(b->arena + b->L.res, 0, res_space(b->res_nwg), b->stream));
+                b->res_steps = (uint64_t)n + 1;
+            }
+            CK(b, launch_resident(kind_of(b->prec), r.s, r.lds, b->d_descs(), b->d_ctrls(), nullptr,
+                                  nullptr, 1, r.one, b->d_sync(), r.grid, r.waves, r.lds_bytes, n,
+                                  b->coop_spin, b->stream));
+        }
         left -= n;
     }
     return NG_OK;
@@ -722,7 +790,7 @@ int enqueue_timed(ng_batch* b, int64_t nsteps)
     size_t ne = 0;
     std::vector<std::pair<size_t, size_t>> step_pairs, fin_pairs;
     double small_ms = 0.0;
-    if (b->coop_slot >= 0) {
+    if (!b->res.empty()) {
         hipEvent_t e0 = get_event(b, 0), e1 = get_event(b, 1);
         if (!e0 || !e1) return dev_err(b, hipErrorOutOfMemory, "hipEventCreate");
         CK(b, hipEventRecord(e0, b->stream));
@@ -832,7 +900,7 @@ int enqueue_steps(ng_batch* b, int64_t nsteps)
     int rc = rebuild(b);
     if (rc) return rc;
     if (b->timing) return enqueue_timed(b, nsteps);
-    if (b->coop_slot >= 0) return enqueue_coop(b, nsteps);
+    if (!b->res.empty()) return enqueue_coop(b, nsteps);
     rc = enqueue_small(b, nsteps, b->stream);
     if (rc || !any_big(b)) return rc;
     int64_t left = nsteps;
@@ -875,7 +943,8 @@ int set_limits(ng_batch* b, const std::vector<int32_t>& slots, double t_end, int
 // Create the batch object over an arena (shared by ng_batch_create and the
 // single-solve constructor).
 int batch_new(int32_t capacity, int32_t precision, void* dev_buf, size_t dev_bytes,
-              void* hip_stream, size_t tcap1, size_t tcap2, ng_batch** out, std::string& err)
+              void* hip_stream, size_t tcap1, size_t tcap2, size_t nwg, ng_batch** out,
+              std::string& err)
 {
     if (capacity < 1 || !dev_buf || !out || !prec_ok(precision)) {
         err = "invalid batch arguments";
@@ -885,7 +954,7 @@ int batch_new(int32_t capacity, int32_t precision, void* dev_buf, size_t dev_byt
         err = "device buffer must be 256-byte aligned";
         return NG_EINVAL;
     }
-    Layout L = header_layout(capacity, tcap1, tcap2);
+    Layout L = header_layout(capacity, tcap1, tcap2, nwg);
     if (dev_bytes < L.heap) {
         err = "device buffer too small for the batch header";
         return NG_ENOMEM;
@@ -899,6 +968,7 @@ int batch_new(int32_t capacity, int32_t precision, void* dev_buf, size_t dev_byt
     b->L = L;
     b->tcap[1] = tcap1;
     b->tcap[2] = tcap2;
+    b->res_nwg = nwg;
     b->slots.resize(capacity);
     if (dev_bytes > L.heap) b->free_list[L.heap] = dev_bytes - L.heap;
     hipError_t e = hipHostMalloc((void**)&b->h_ctrls, sizeof(InstCtrl) * capacity, 0);
@@ -925,6 +995,7 @@ int batch_new(int32_t capacity, int32_t precision, void* dev_buf, size_t dev_byt
     if (e == hipSuccess)
         e = hipMemcpyAsync(b->d_iota(), iota.data(), sizeof(int32_t) * capacity,
                            hipMemcpyHostToDevice, b->stream);
+    if (e == hipSuccess && nwg) e = hipMemsetAsync(b->arena + L.res, 0, res_space(nwg), b->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(b->up_stream);
     if (e != hipSuccess) {
@@ -1369,7 +1440,8 @@ int ng_state_bytes(const ng_grid* grid, const ng_numerics* num, size_t* bytes)
         return NG_EINVAL;
     if (!prec_ok(num->precision)) return NG_EINVAL;
     size_t tc = (size_t)partial_cap_of(grid);
-    Layout L = header_layout(1, grid->ndim == 1 ? tc : 0, grid->ndim == 2 ? tc : 0);
+    Layout L = header_layout(1, grid->ndim == 1 ? tc : 0, grid->ndim == 2 ? tc : 0,
+                             res_wgs_of(grid));
     *bytes = L.heap + solve_bytes(grid, num->precision);
     return NG_OK;
 }
@@ -1390,7 +1462,7 @@ static int solver_new(const ng_gas* gas, const ng_grid* grid, const ng_numerics*
     size_t tc = (size_t)partial_cap_of(grid);
     ng_batch* b = nullptr;
     rc = batch_new(1, num->precision, dev_buf, need, hip_stream, grid->ndim == 1 ? tc : 0,
-                   grid->ndim == 2 ? tc : 0, &b, err);
+                   grid->ndim == 2 ? tc : 0, res_wgs_of(grid), &b, err);
     if (rc) return rc;
     int32_t slot = 0;
     rc = add_solve(b, gas, grid, num, data, is_prim, t0, INFINITY, INT64_MAX, &slot);
@@ -1695,7 +1767,7 @@ int ng_batch_create(int32_t capacity, int32_t precision, void* dev_buf, size_t d
     size_t tcap = dev_bytes / per + 64 * (size_t)capacity;
     std::string err;
     return batch_new(capacity, precision, dev_buf, dev_bytes, hip_stream, tcap, tcap / 4 + 64 * capacity,
-                     out, err);
+                     res_wgs_of(dev_bytes), out, err);
 }
 
 int ng_batch_solve_bytes(const ng_grid* grid, int32_t precision, size_t* bytes)

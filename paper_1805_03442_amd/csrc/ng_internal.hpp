@@ -137,21 +137,36 @@ struct InstCtrl {
                               // the third for the CSPH-TVD step's particles)
 };
 
-// Grid barrier of a cooperative launch (one solve advanced many steps per
-// launch by at most kCoopFlat workgroups that stay resident together), zeroed
-// before each launch.  Each step every workgroup writes its signal speed (low
-// and high halves) and failure flags into its own slot -- three 8-byte words,
-// each (step number << 32 | 32 bits of payload), so that a reader which sees
-// the step number in all three words holds one whole message -- and reads
-// every slot itself, so that all of them reach the same next dt and
-// acceptance.  A workgroup can be at most one step ahead of any other (it
-// needs their slots of its current step), so slots by step parity suffice.
-constexpr int kCoopFlat = 256;
-constexpr int kCoopMaxWaves = 16;   // waves per workgroup of a cooperative launch
-struct CoopSync {
-    uint32_t stall[32];                // [0]: set by a workgroup whose wait ran out
-    uint64_t fslot[2][kCoopFlat][4];   // [step parity][workgroup]
+// A cooperative launch (ng_resident.hip): solves advanced many steps per launch
+// by workgroups that stay resident together.  Every workgroup owns a slot and
+// two edges, of 8-byte words (step number << 32 | 32 bits of payload): a slot
+// word (two in FP64) holds its signal speed, or its failure flags with the
+// sign bit set, an edge the stored values of its first or last cells.  A reader
+// that sees the step number in a word has its payload.  A workgroup can be at most one step
+// ahead of any other of its solve (it needs their slots of its current step),
+// so words by step parity suffice.  The step numbers run on from launch to
+// launch (ResSync::base), so nothing is cleared in between.
+constexpr int kCoopFlat = 256;      // workgroups of one solve
+constexpr int kCoopMaxWaves = 16;   // waves per workgroup, upper bound
+constexpr int kResEdge = 24;        // words of an edge (three FP64 cells)
+constexpr int kResSlot = 8;         // words from slot to slot, at most
+constexpr int kResMinWaves = 4;     // the exchange takes three waves
+// LDS a workgroup may take for its cells (160 KiB less the kernel's own)
+constexpr uint64_t kResLdsBytes = 156 * 1024;
+struct ResGroup {
+    int32_t inst;     // solve
+    int32_t G;        // its workgroups
+    int32_t first;    // ... from this slot on
+    int32_t pitch;    // cells per LDS copy, ghosts included
 };
+struct ResSync {
+    uint32_t* base;     // last step number used
+    uint64_t* slots;    // [step parity][nwg][kResSlot]
+    uint64_t* edges;    // [step parity][nwg][side][kResEdge]
+    int32_t nwg;        // slots there are
+};
+// bytes of the slots and edges of nwg workgroups (after 256 bytes for base)
+constexpr uint64_t res_space(uint64_t nwg) { return 256 + nwg * 2 * 8 * (kResSlot + 2 * kResEdge); }
 
 // Per-workgroup data of a cooperative launch, in the solve's reduction space:
 // records of the workgroup's last two steps (by step parity), written when
@@ -168,7 +183,7 @@ struct CoopView {
     double t, dt_cfl, dt_last;
     int64_t steps, nacc;   // steps of the solve; steps this launch accepted
     int32_t cur, status;
-    uint32_t flags, pad;
+    uint32_t flags, stalled;   // ..., this workgroup's wait ran out
 };
 // bytes of reduction space a cooperative launch of G workgroups uses
 constexpr uint64_t coop_space(uint64_t G)

@@ -30,17 +30,22 @@ hipError_t launch_small(int dim, int prec, const InstDesc* descs, InstCtrl* ctrl
 hipError_t launch_set_limits(InstCtrl* ctrls, const int32_t* insts, int n, double t_end,
                              int64_t max_steps_from_now, hipStream_t s);
 
-// Cooperative launch of one 1D solve (solve `inst`) for up
-// to nsteps <= kCoopMaxSteps steps: grid workgroups of `waves` waves, all
-// resident together (the runtime refuses a grid that does not fit); cs is the
-// batch's barrier block, cleared here first.  coop_capacity gives the
-// resident workgroups per CU of that kernel and the largest waves per
-// workgroup.  variant as for launch_step.
+// Cooperative launch of 1D solves for up to nsteps <= kCoopMaxSteps steps each:
+// grid workgroups of `waves` waves, all resident together (the runtime refuses
+// a grid that does not fit).  s: 0..3 HLLC with closure recipe s, 4 HLL, 5 and
+// 6 CSPH-TVD with the general closures and recipe 1 (3, 5, 6: FP64).  lds: the
+// cells stay in LDS (lds_bytes of it), else in the state buffers.  One solve:
+// `one`, groups and refs null; more: ngroups solves in groups, refs[w] the
+// (group, workgroup of it) of workgroup w.  resident_capacity gives the
+// workgroups of that shape a CU holds at once.
 constexpr int64_t kCoopMaxSteps = int64_t(1) << 16;
-hipError_t coop_capacity(int prec, int variant, int waves, int* blocks_per_cu, int* max_waves);
-hipError_t launch_coop(int prec, int variant, const InstDesc* descs, InstCtrl* ctrls, int inst,
-                       CoopSync* cs, int grid, int waves, int64_t nsteps, int32_t spin_limit,
-                       hipStream_t s);
+int resident_max_waves(int prec);
+hipError_t resident_capacity(int prec, int s, bool lds, int waves, size_t lds_bytes,
+                             int* blocks_per_cu);
+hipError_t launch_resident(int prec, int s, bool lds, const InstDesc* descs, InstCtrl* ctrls,
+                           const ResGroup* groups, const BlockRef* refs, int ngroups,
+                           const ResGroup& one, const ResSync& sync, int grid, int waves,
+                           size_t lds_bytes, int64_t nsteps, int32_t spin_limit, hipStream_t st);
 
 // Static scratch of the entry point that allocates nothing: its device
 // address on the current device (looked up once per device), and the kernel

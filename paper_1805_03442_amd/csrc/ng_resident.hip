@@ -1,0 +1,657 @@
+// ng_resident.hip -- the cooperative path of the 1D steps: one launch advances
+// a solve, or many solves side by side, through many steps (MUSCL, eq. (15), or
+// CSPH-TVD, section 2.3).
+//
+// A solve's cells are dealt to G workgroups that stay resident together, each
+// one run of consecutive segments, and a workgroup keeps its cells in LDS (160
+// KB per CU: 4900 FP32 or 2400 FP64 cells with the two copies a step needs) for
+// the whole launch.  A step then moves no state through memory: its latency is
+// the arithmetic of the segments, one exchange and two workgroup barriers.
+// The exchange carries what the others need and nothing else: each workgroup
+// writes its largest signal speed and failure flags, and its first and last
+// two (CSPH-TVD: three) cells, as 8-byte words (step number << 32 | 32 bits of
+// payload) in device memory.  A reader that sees the step number in a word has
+// its payload, so no ordering between words, no cache write-back and no wait
+// for stores is needed.  One wave polls the speeds of all the solve's
+// workgroups and takes the next dt of eq. (16), alike in each; a second wave
+// polls the neighbours' edge cells, or fills the ghosts of a domain end.
+// A solve too large for LDS keeps its cells in the two state buffers instead
+// (InLds = false): each workgroup still reads and writes only its own cells
+// there, so plain cached loads and stores serve, and the edges travel as above.
+//
+// What it measured (us per step; before: a kernel that kept the state in memory,
+// with agent-scope loads and stores, and met at a barrier of 24-byte messages):
+//   cells            200        1024       16384      2^17       2^20
+//   FP32          2.81 1.35   2.92 2.18  3.27 2.48  5.37 3.68  11.97 9.6
+//   FP64          5.46 1.96   5.60 2.85  5.90 3.27 11.03 5.75  40.2  22.9
+//   CSPH-TVD      6.02 2.1    6.19 3.2   6.67 3.8  12.5  7.4   47.0  27
+// (the FP64 rows with the new divisions too; 2^20 FP64 cells are beyond LDS).
+// What is left at 200 cells is one segment's chain of dependent operations, at
+// 2^20 the vector ALUs (5.7 segments per wave, three waves per SIMD).
+//
+// Per-cell arithmetic, t and dt follow the step kernels and the finalize kernel
+// operation for operation, so the state, t and dt are bitwise those of one
+// launch per step; only the summation order of the FP64 totals differs.  Those
+// sums never cross the barrier: each lane keeps those of its last computed
+// step, each workgroup folds them into its records when the launch ends, and resident_after_kernel folds the records of the last
+// accepted step into the control block.
+//
+// Every wait is bounded by spin_limit polls: a workgroup whose wait runs out
+// leaves, the others leave when their own next wait runs out, and the solve
+// keeps the last step a barrier accepted.
+#include <hip/hip_runtime.h>
+#include <math.h>
+#include <stdint.h>
+
+#include <type_traits>
+
+#include "ng_device.hpp"
+#include "ng_launch.hpp"
+
+namespace ng {
+
+// largest value of the wave, in every lane (NaN lanes ignored): row shifts,
+// then the two row broadcasts, leave it in lane 63
+template <int Ctrl, int RowMask>
+__device__ __forceinline__ double dpp_max(double v)
+{
+    const int lo = __builtin_amdgcn_update_dpp(__double2loint(v), __double2loint(v), Ctrl, RowMask,
+                                               0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(__double2hiint(v), __double2hiint(v), Ctrl, RowMask,
+                                               0xf, false);
+    return fmax(v, __hiloint2double(hi, lo));
+}
+__device__ __forceinline__ double wave_max(double v)
+{
+    v = dpp_max<0x111, 0xf>(v);   // row_shr:1
+    v = dpp_max<0x112, 0xf>(v);   // row_shr:2
+    v = dpp_max<0x114, 0xf>(v);   // row_shr:4
+    v = dpp_max<0x118, 0xf>(v);   // row_shr:8
+    v = dpp_max<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
+    v = dpp_max<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63),
+                            __builtin_amdgcn_readlane(__double2loint(v), 63));
+}
+// union of three flag bits over the wave
+__device__ __forceinline__ uint32_t wave_flags(uint32_t f)
+{
+    return (__builtin_amdgcn_ballot_w64(f & 1u) ? 1u : 0u) |
+           (__builtin_amdgcn_ballot_w64(f & 2u) ? 2u : 0u) |
+           (__builtin_amdgcn_ballot_w64(f & 4u) ? 4u : 0u);
+}
+
+// Wave-wide wait for the slots of step gen of G <= kCoopFlat workgroups: lane j
+// reads slots j, j + 64, ... (NQ of them; past the last, the last again), at
+// most spin_limit polls after the first; true when they ran out.  m, f: the
+// largest signal speed and the union of the flags of this lane's slots.  R:
+// the speed's type.  What the exchange costs is set by the slots' spacing:
+// stores of different XCDs into one 128-byte line wait for each other, and
+// every poll moves all slots' sectors to every workgroup.  Us per step at 16,
+// 32, 64 and 128 bytes per slot: 16384 FP32 cells (69 workgroups) 3.03, 2.67,
+// 2.48, 2.51; 262144 FP64 cells (256 workgroups) 8.19, 8.03, 8.10, 8.36; three
+// words per slot at 32 bytes made it 8.5.  So 64 bytes up to 128 workgroups,
+// then 32.  (A second poll in flight, and no sleep between polls, changed
+// nothing or cost 0.1 us.)
+constexpr int slot_words(uint32_t G) { return G <= 128u ? 8 : 4; }
+template <class R, int NQ>
+struct SlotPoll {
+    static constexpr int kWords = (int)sizeof(R) / 4;
+    uint64_t w[NQ][kWords];
+    __device__ __forceinline__ void issue(const uint64_t* slots, uint32_t G, int lane)
+    {
+#pragma unroll
+        for (int q = 0; q < NQ; q++) {
+            const uint32_t j = (uint32_t)lane + 64u * q;
+#pragma unroll
+            for (int x = 0; x < kWords; x++)
+                w[q][x] = __hip_atomic_load(slots + (j < G ? j : G - 1u) * slot_words(NQ <= 2 ? 1u : 256u) + x,
+                                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    __device__ __forceinline__ bool have(uint32_t gen) const
+    {
+        bool h = true;
+#pragma unroll
+        for (int q = 0; q < NQ; q++)
+#pragma unroll
+            for (int x = 0; x < kWords; x++) h = h && (uint32_t)(w[q][x] >> 32) == gen;
+        return __builtin_amdgcn_ballot_w64(!h) == 0ull;
+    }
+    __device__ __forceinline__ void fold(double& m, uint32_t& f) const
+    {
+        m = 0.0;
+        f = 0u;
+#pragma unroll
+        for (int q = 0; q < NQ; q++) {
+            const uint32_t hi = (uint32_t)w[q][kWords - 1];
+            if (hi & 0x80000000u)
+                f |= hi & 7u;
+            else if (kWords == 2)
+                m = fmax(m, __hiloint2double((int)hi, (int)(uint32_t)w[q][0]));
+            else
+                m = fmax(m, (double)__int_as_float((int)hi));
+        }
+    }
+};
+template <class R, int NQ>
+__device__ __forceinline__ bool poll_slots(const uint64_t* slots, uint32_t G, uint32_t gen,
+                                           int lane, int32_t spin_limit, double& m, uint32_t& f)
+{
+    static_assert(kCoopFlat <= 4 * kWave, "at most four slots per lane");
+    SlotPoll<R, NQ> a;
+    a.issue(slots, G, lane);
+    for (int32_t n = 0;; n++) {
+        if (a.have(gen)) {
+            a.fold(m, f);
+            return false;
+        }
+        if (n >= spin_limit) {
+            m = 0.0;
+            f = 0u;
+            return true;
+        }
+        __builtin_amdgcn_s_sleep(1);
+        a.issue(slots, G, lane);
+    }
+}
+
+// One cell as LDS holds it: its components side by side, so that a lane loads
+// or stores it in one or two 16-byte operations.
+template <class St>
+struct alignas(16) ResCell {
+    St u[4];
+};
+
+// S: 0..3 the HLLC step with closure recipe S (0: general), 4 the HLL step,
+// 5 and 6 the CSPH-TVD step with the general closures and recipe 1.
+// groups/refs: the launch's solves and the (group, local workgroup) of each
+// workgroup; null: one solve, `one`.
+template <class P, int S, bool InLds>
+__global__ void __launch_bounds__(P::kResThreads) run_resident_kernel(
+    const InstDesc* __restrict__ descs, const InstCtrl* __restrict__ ctrls,
+    const ResGroup* __restrict__ groups, const BlockRef* __restrict__ refs, ResGroup one,
+    const uint32_t* __restrict__ base, uint64_t* __restrict__ slots, uint64_t* __restrict__ edges,
+    int32_t nwg, int64_t nsteps, int32_t spin_limit)
+{
+    using R = typename P::R;
+    using St = typename P::St;
+    constexpr bool csph = S >= 5;
+    constexpr int NC = 4, H = csph ? kCsphHalo : kHalo, W = kWave - 2 * H;
+    constexpr int CL = S < 4 ? S : (S == 6 ? 1 : 0), RS = S == 4 ? 1 : 0;
+    constexpr int kHalves = (int)sizeof(St) / 4;     // 32-bit payloads per value
+    constexpr int kSide = H * NC * kHalves;          // edge words per side
+    static_assert(2 * kSide <= kWave && kSide <= kResEdge, "one wave exchanges both edges");
+
+    const BlockRef ref = refs ? refs[blockIdx.x] : BlockRef{0, (int32_t)blockIdx.x};
+    const ResGroup gr = groups ? groups[ref.inst] : one;
+    const InstDesc& d = descs[gr.inst];
+    const InstCtrl& c = ctrls[gr.inst];
+    const uint32_t G = (uint32_t)gr.G, b = (uint32_t)ref.local;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int nw = blockDim.x >> 6, tid = threadIdx.x, nthr = blockDim.x;
+    const uint32_t gen0 = *base;
+    CoopRec* recs = (CoopRec*)d.partials;                // [parity][G]
+    CoopView* views = (CoopView*)(recs + 2 * (size_t)G);
+
+    extern __shared__ __align__(16) unsigned char dyn[];
+    __shared__ double s_sum[kCoopMaxWaves][10];
+    __shared__ double s_sm[kCoopMaxWaves];
+    __shared__ uint32_t s_fl[kCoopMaxWaves];
+    __shared__ double s_dt;           // the next CFL step
+    __shared__ uint32_t s_bad;        // failure flags of the step
+    __shared__ int s_stall[2];        // a wait of wave 0 / wave 1 ran out
+    __shared__ double s_gsrc[3][5];   // a forced source's ghosts
+    // cells of this workgroup: segments [g0, g1), cells [c0, c0 + len)
+    const int64_t n = d.nx;
+    const int g0 = (int)((int64_t)b * d.nstrips / G), g1 = (int)((int64_t)(b + 1) * d.nstrips / G);
+    const int64_t c0 = (int64_t)g0 * W;
+    const int len = (int)((int64_t)g1 * W < n ? (int64_t)(g1 - g0) * W : n - c0);
+    const int f0 = wave * (g1 - g0) / nw, f1 = (wave + 1) * (g1 - g0) / nw;
+
+    // Storage.  In LDS: two copies of the cells with H ghosts per side, copy q
+    // at q * pitch, cell c0 + i at H + i.  Else only the ghosts are there, H per
+    // side and copy, and the cells are in the state buffers.
+    ResCell<St>* lds = (ResCell<St>*)dyn;
+    const int pitch = InLds ? gr.pitch : 2 * H;
+    const int cur0 = c.cur;
+    const Planes<St, NC> pl0(d.buf[cur0], n), pl1(d.buf[cur0 ^ 1], n);
+    // the LDS slot of ghost i (0..H-1: left, H..2H-1: right) of copy q, and of
+    // the edge cell of the workgroup that neighbour's ghost i holds
+    auto ghost_at = [&](int q, int i) -> ResCell<St>& {
+        return lds[q * pitch + (InLds && i >= H ? len + i : i)];
+    };
+    // a cell's value by its index in [0, len), from copy q
+    auto own = [&](int q, int i, St* U) {
+        if constexpr (InLds) {
+            const ResCell<St> t = lds[q * pitch + H + i];
+            for (int x = 0; x < NC; x++) U[x] = t.u[x];
+        } else {
+            (q ? pl1 : pl0).load((uint32_t)((c0 + i) * (int64_t)sizeof(St)), U);
+        }
+    };
+
+    // the solve's control, as every workgroup tracks it
+    const double t_end = c.t_end;
+    const int64_t max_steps = c.max_steps;
+    double t = c.t, dt_cfl = c.dt_cfl, dt_last = c.dt_last;
+    int64_t steps = c.steps;
+    int nacc = 0, status = c.status;
+    uint32_t bad = 0;
+    bool active = status == 0 && t < t_end && steps < max_steps;
+    bool stalled = false;
+    const bool src = d.bc[0] == kBcSource;
+    // neighbours of this workgroup; ends without one have ghosts by the
+    // boundary rule (a lone workgroup's periodic ghosts too)
+    const bool periodic = d.bc[0] == kBcPeriodic;
+    const bool has_l = G > 1u && (b > 0u || periodic), has_r = G > 1u && (b + 1u < G || periodic);
+    const uint32_t nb_l = (uint32_t)gr.first + (b > 0u ? b - 1u : G - 1u);
+    const uint32_t nb_r = (uint32_t)gr.first + (b + 1u < G ? b + 1u : 0u);
+    const uint32_t me = (uint32_t)gr.first + b;
+
+    // copy 0 from the state buffer, ghosts by the boundary rule
+    if (active) {
+        if (src && tid < H) source_ghost_at(d, t, tid, s_gsrc[tid]);
+        __syncthreads();
+        auto fetch = [&](int64_t j, ResCell<St>& out) {
+            bool flip;
+            const int64_t x = axis_cell(j, n, d.bc[0], d.bc[1], flip);
+            St U[NC];
+            pl0.load((uint32_t)(x * (int64_t)sizeof(St)), U);
+            if (flip) U[1] = -U[1];
+            if (src && j < 0) source_cell<St, NC, P::kSplitE>(d, s_gsrc[-1 - j], U);
+            for (int x2 = 0; x2 < NC; x2++) out.u[x2] = U[x2];
+        };
+        if constexpr (InLds) {
+            for (int i = tid; i < len + 2 * H; i += nthr) fetch(c0 - H + i, lds[i]);
+        } else {
+            if (tid < 2 * H) fetch(tid < H ? c0 - H + tid : c0 + len + tid - H, ghost_at(0, tid));
+        }
+        __syncthreads();
+    }
+
+    CsphGrid cg{};
+    if constexpr (csph) cg = csph_grid(d);
+    // Per lane, the sums of the last computed step (acc) and the source
+    // increments of every accepted step (bud); they are folded into the
+    // workgroup's records once, when the launch ends, not at every step.
+    Acc<R> acc;
+    acc_init(acc);
+    double bud0 = 0.0, bud1 = 0.0;
+    int st_c = -1;         // last computed step
+    bool cur_ok = false;   // ... and whether this workgroup saw it accepted
+
+    for (int st = 0; st < (int)nsteps && active; st++) {
+        const uint32_t gen = gen0 + 1u + (uint32_t)st;
+        const int q = st & 1;   // U^n is in copy q
+        double dt = dt_cfl;
+        if (t + dt > t_end) dt = t_end - t;
+        const typename P::K k = P::make(d, dt);
+        acc_init(acc);
+        st_c = st;
+        cur_ok = false;
+        // this wave's segments; the next segment's cells are fetched before
+        // the current one is computed
+        if (f0 < f1) {
+            const Planes<St, NC>& src_pl = q ? pl1 : pl0;
+            const Planes<St, NC>& dst_pl = q ? pl0 : pl1;
+            auto get = [&](int sg, St* U) {
+                const int i = sg * W + lane;     // cell c0 - H + i
+                if constexpr (InLds) {
+                    const ResCell<St> v = lds[q * pitch + (i < len + 2 * H ? i : len + 2 * H - 1)];
+                    for (int x = 0; x < NC; x++) U[x] = v.u[x];
+                } else {
+                    const int j = i < H ? 0 : (i < H + len ? i - H : len - 1);
+                    src_pl.load((uint32_t)((c0 + j) * (int64_t)sizeof(St)), U);
+                }
+            };
+            auto seg = [&](int sg, St* Uc, St* Ux) {
+                get(sg + 1 < f1 ? sg + 1 : sg, Ux);
+                const int i = sg * W + lane;
+                if constexpr (!InLds) {
+                    // ghosts of the workgroup's ends come from LDS (the right
+                    // ones may reach into the last segment but one)
+                    if (i < H || i >= H + len) {
+                        const int gi = i < H ? i : i - len;
+                        const ResCell<St> v = lds[q * pitch + (gi < 2 * H ? gi : 2 * H - 1)];
+                        for (int x = 0; x < NC; x++) Uc[x] = v.u[x];
+                    }
+                }
+                St Uo[NC];
+                R Wn[NC + 1], sp, sE, sV;
+                if constexpr (csph)
+                    seg_csph<CL>(k, cg, Uc, Uo, Wn, sp, sE, sV);
+                else
+                    seg1d<P, RS, CL>(k, Uc, Uo, Wn, sp, sE, sV);
+                if (lane >= H && lane < kWave - H && i < H + len) {
+                    if constexpr (InLds) {
+                        ResCell<St> v;
+                        for (int x = 0; x < NC; x++) v.u[x] = Uo[x];
+                        lds[(q ^ 1) * pitch + i] = v;
+                    } else {
+                        dst_pl.store_cached((uint32_t)((c0 + i - H) * (int64_t)sizeof(St)), Uo);
+                    }
+                    acc_cell<P, NC>(acc, k, Uo, Wn, sp, sE, sV);
+                }
+            };
+            St UA[NC], UB[NC];
+            get(f0, UA);
+            int sg = f0;
+            for (; sg + 1 < f1; sg += 2) {
+                seg(sg, UA, UB);
+                seg(sg + 1, UB, UA);
+            }
+            if (sg < f1) seg(sg, UA, UB);
+        }
+        acc_finish<P>(acc, k);
+        // the exchange needs only the signal speed and the failure flags
+        {
+            const double sm = wave_max((double)acc.smax);
+            const uint32_t fl = wave_flags(acc_flags(acc));
+            if (lane == 0) {
+                s_sm[wave] = sm;
+                s_fl[wave] = fl;
+            }
+        }
+        __syncthreads();
+        if (wave == 0) {
+            double m = wave_max(lane < nw ? s_sm[lane] : 0.0);
+            uint32_t f = wave_flags(lane < nw ? s_fl[lane] : 0u);
+            bool out = false;
+            if (G > 1u) {
+                constexpr int kWords = (int)sizeof(R) / 4;
+                uint64_t* const sl = slots + (size_t)q * nwg * kResSlot + (size_t)gr.first * kResSlot;
+                if (lane < kWords) {
+                    // lane 0: the low half in FP64, the whole in FP32
+                    const uint32_t lo = kWords == 2 ? (uint32_t)__double2loint(m)
+                                                    : (uint32_t)__float_as_int((float)m);
+                    const uint32_t hi = (uint32_t)__double2hiint(m);
+                    uint32_t v = lane == 0 ? lo : hi;
+                    if (f && lane == kWords - 1) v = 0x80000000u | f;
+                    __hip_atomic_store(sl + (size_t)slot_words(G) * b + lane, ((uint64_t)gen << 32) | v,
+                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+                if (G <= 64u)
+                    out = poll_slots<R, 1>(sl, G, gen, lane, spin_limit, m, f);
+                else if (G <= 128u)
+                    out = poll_slots<R, 2>(sl, G, gen, lane, spin_limit, m, f);
+                else
+                    out = poll_slots<R, 4>(sl, G, gen, lane, spin_limit, m, f);
+                m = wave_max(m);
+                f = wave_flags(f);
+            }
+            if (lane == 0) {
+                s_stall[0] = out ? 1 : 0;
+                s_bad = f & 7u;
+                s_dt = d.cfl * d.h / m;
+            }
+        } else if (wave == 1) {
+            // Ghosts of the next step, copy q ^ 1.  Lane w of a side carries
+            // 32 bits of one value of one edge cell: it publishes this
+            // workgroup's, and takes the neighbour's (or the boundary rule's)
+            // into the ghosts.
+            const int side = lane >= kSide ? 1 : 0, w = lane - side * kSide;
+            const bool mine = lane < 2 * kSide;
+            const int g = w / (NC * kHalves), x = (w / kHalves) % NC, hf = w % kHalves;
+            auto half_of = [&](int i) -> uint32_t {
+                if constexpr (InLds) {
+                    return ((const uint32_t*)&lds[(q ^ 1) * pitch + H + i].u[x])[hf];
+                } else {
+                    St U[NC];
+                    own(q ^ 1, i, U);
+                    uint32_t r = 0;
+                    for (int y = 0; y < NC; y++)
+                        if (y == x) {
+                            uint32_t bits[kHalves];
+                            __builtin_memcpy(bits, &U[y], sizeof(St));
+                            r = kHalves == 2 && hf ? bits[kHalves - 1] : bits[0];
+                        }
+                    return r;
+                }
+            };
+            bool out = false;
+            if (G > 1u && mine) {
+                const uint32_t v = half_of(side ? len - H + g : g);
+                __hip_atomic_store(edges + (((size_t)q * nwg + me) * 2 + side) * kResEdge + w,
+                                   ((uint64_t)gen << 32) | v, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+            }
+            const bool take = mine && (side ? has_r : has_l);
+            uint32_t v = 0;
+            if (mine && !take) {
+                const int kind = d.bc[side];
+                const int i = kind == kBcPeriodic ? (side ? g : len - H + g)
+                              : kind == kBcWall   ? (side ? len - 1 - g : H - 1 - g)
+                                                  : (side ? len - 1 : 0);
+                v = half_of(i);
+                if (kind == kBcWall && x == 1 && hf == kHalves - 1) v ^= 0x80000000u;
+            }
+            const uint64_t* const from =
+                edges + (((size_t)q * nwg + (side ? nb_r : nb_l)) * 2 + (side ? 0 : 1)) * kResEdge + w;
+            if (G > 1u)
+                for (int32_t it = 0;; it++) {
+                    uint64_t word = (uint64_t)gen << 32;
+                    if (take)
+                        word = __hip_atomic_load(from, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    const bool have = (uint32_t)(word >> 32) == gen;
+                    if (__builtin_amdgcn_ballot_w64(!have) == 0ull) {
+                        if (take) v = (uint32_t)word;
+                        break;
+                    }
+                    if (it >= spin_limit) {
+                        out = true;
+                        break;
+                    }
+                    __builtin_amdgcn_s_sleep(1);
+                }
+            if (mine && !(src && side == 0 && !has_l))
+                ((uint32_t*)&ghost_at(q ^ 1, side * H + g).u[x])[hf] = v;
+            if (lane == 0) s_stall[1] = out ? 1 : 0;
+        } else if (wave == 2 && src && b == 0u && lane < H) {
+            // a forced source's ghosts for the time the step leads to
+            source_ghost_at(d, t + dt, lane, s_gsrc[lane]);
+            St U[NC];
+            source_cell<St, NC, P::kSplitE>(d, s_gsrc[lane], U);
+            for (int x = 0; x < NC; x++) ghost_at(q ^ 1, H - 1 - lane).u[x] = U[x];
+        }
+        __syncthreads();
+        if (s_stall[0] | s_stall[1]) {
+            stalled = true;
+            break;
+        }
+        bad = s_bad;
+        if (bad) {
+            status = -3;   // NG_EPHYS
+            active = false;
+        } else {
+            // accepted: as accept_step advances the control block
+            t = t + dt;
+            steps = steps + 1;
+            dt_last = dt;
+            dt_cfl = s_dt;
+            nacc++;
+            active = t < t_end && steps < max_steps;
+            bud0 += acc.src[0];
+            bud1 += acc.src[1];
+            cur_ok = true;
+        }
+    }
+    // The workgroup's records (lanes, then waves in order): the sums of the
+    // last computed step and, when this workgroup did not see that step
+    // accepted, of the last accepted one.  The after-kernel folds the records
+    // of the last step the most advanced workgroup accepted, found by its
+    // parity.
+    auto put_rec = [&](const Acc<R>& a, double b0, double b1, int step) {
+        double v[10];
+        for (int x = 0; x < 5; x++) v[x] = a.tot[x];
+        v[5] = b0;
+        v[6] = b1;
+        v[7] = (double)a.smax;
+        v[8] = (double)a.rmin;
+        v[9] = (double)a.pmin;
+        for (int m = 32; m >= 1; m >>= 1) {
+            for (int x = 0; x < 7; x++) v[x] += lane_xor(v[x], lane, m);
+            v[7] = fmax(v[7], lane_xor(v[7], lane, m));
+            v[8] = fmin(v[8], lane_xor(v[8], lane, m));
+            v[9] = fmin(v[9], lane_xor(v[9], lane, m));
+        }
+        __syncthreads();
+        if (lane == 0)
+            for (int x = 0; x < 10; x++) s_sum[wave][x] = v[x];
+        __syncthreads();
+        if (tid == 0) {
+            for (int w = 1; w < nw; w++) {
+                for (int x = 0; x < 7; x++) v[x] += s_sum[w][x];
+                v[7] = fmax(v[7], s_sum[w][7]);
+                v[8] = fmin(v[8], s_sum[w][8]);
+                v[9] = fmin(v[9], s_sum[w][9]);
+            }
+            CoopRec r;
+            for (int x = 0; x < 5; x++) r.tot[x] = v[x];
+            r.src[0] = v[5];
+            r.src[1] = v[6];
+            r.smax = v[7];
+            r.rho_min = v[8];
+            r.p_min = v[9];
+            r.flags = 0u;
+            r.step = (uint32_t)step;
+            recs[(size_t)(step & 1) * G + b] = r;
+        }
+    };
+    if (st_c >= 0) {
+        if (cur_ok) {
+            put_rec(acc, bud0, bud1, st_c);
+        } else {
+            put_rec(acc, bud0 + acc.src[0], bud1 + acc.src[1], st_c);
+            if (st_c >= 1) {
+                // the sums of the accepted state, from its cells
+                const typename P::K k = P::make(d, 0.0);
+                acc_init(acc);
+                for (int i = tid; i < len; i += nthr) {
+                    St U[NC];
+                    R Wn[NC + 1];
+                    own(nacc & 1, i, U);
+                    P::prim(k, U, Wn);
+                    acc_cell<P, NC>(acc, k, U, Wn, P::speed(k, Wn), (R)0, (R)0);
+                }
+                acc_finish<P>(acc, k);
+                put_rec(acc, bud0, bud1, st_c - 1);
+            }
+        }
+    }
+    // The state: U after a accepted steps goes to the buffer of parity a.  A
+    // workgroup whose wait ran out does not know whether the others accepted
+    // its last computed step, so it leaves that one too (in the other buffer);
+    // after zero accepted steps buffer 0 still holds the start.
+    if constexpr (InLds) {
+        auto dump = [&](int a) {
+            const Planes<St, NC>& pl = (a & 1) ? pl1 : pl0;
+            for (int i = tid; i < len; i += nthr) {
+                const ResCell<St> v = lds[(a & 1) * pitch + H + i];
+                St U[NC];
+                for (int x = 0; x < NC; x++) U[x] = v.u[x];
+                pl.store((uint32_t)((c0 + i) * (int64_t)sizeof(St)), U);
+            }
+        };
+        if (nacc > 0) dump(nacc);
+        if (stalled) dump(nacc + 1);
+    }
+    // and its view of the control
+    if (tid == 0) {
+        CoopView w;
+        w.t = t;
+        w.dt_cfl = dt_cfl;
+        w.dt_last = dt_last;
+        w.steps = steps;
+        w.nacc = nacc;
+        w.cur = cur0 ^ (nacc & 1);
+        w.status = status;
+        w.flags = bad;
+        w.stalled = stalled ? 1u : 0u;
+        views[b] = w;
+    }
+}
+
+// One workgroup per solve of a resident launch (coop_fold); the first moves
+// the step number on past every number this launch can have used.
+__global__ void __launch_bounds__(256) resident_after_kernel(const InstDesc* __restrict__ descs,
+                                                             InstCtrl* __restrict__ ctrls,
+                                                             const ResGroup* __restrict__ groups,
+                                                             ResGroup one,
+                                                             uint32_t* __restrict__ base,
+                                                             uint32_t nsteps)
+{
+    const ResGroup gr = groups ? groups[blockIdx.x] : one;
+    coop_fold(descs[gr.inst], ctrls[gr.inst], gr.G);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *base += nsteps + 1u;
+}
+
+// ================================================================ launchers
+
+template <template <int> class Pol, bool InLds>
+static const void* kernel_of(int s)
+{
+    using P = Pol<4>;
+    switch (s) {
+    case 0: return (const void*)run_resident_kernel<P, 0, InLds>;
+    case 1: return (const void*)run_resident_kernel<P, 1, InLds>;
+    case 2: return (const void*)run_resident_kernel<P, 2, InLds>;
+    case 4: return (const void*)run_resident_kernel<P, 4, InLds>;
+    default: break;
+    }
+    if constexpr (std::is_same<typename P::K, K64>::value) {
+        if (s == 3) return (const void*)run_resident_kernel<P, 3, InLds>;
+        if (s == 5) return (const void*)run_resident_kernel<P, 5, InLds>;
+        if (s == 6) return (const void*)run_resident_kernel<P, 6, InLds>;
+    }
+    return nullptr;
+}
+
+static const void* kernel_of(int prec, int s, bool lds)
+{
+    if (prec == 0) return lds ? kernel_of<Plain64, true>(s) : kernel_of<Plain64, false>(s);
+    if (prec == 1) return lds ? kernel_of<Dev32, true>(s) : kernel_of<Dev32, false>(s);
+    if (prec == 2) return lds ? kernel_of<Mix32, true>(s) : kernel_of<Mix32, false>(s);
+    return nullptr;
+}
+
+int resident_max_waves(int prec)
+{
+    return (prec == 0 ? Plain64<4>::kResThreads
+                      : (prec == 1 ? Dev32<4>::kResThreads : Mix32<4>::kResThreads)) / kWave;
+}
+
+hipError_t resident_capacity(int prec, int s, bool lds, int waves, size_t lds_bytes,
+                             int* blocks_per_cu)
+{
+    const void* k = kernel_of(prec, s, lds);
+    if (!k || waves < kResMinWaves || waves > resident_max_waves(prec)) return hipErrorInvalidValue;
+    hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)kResLdsBytes);
+    if (e != hipSuccess) return e;
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k, waves * kWave, lds_bytes);
+}
+
+hipError_t launch_resident(int prec, int s, bool lds, const InstDesc* descs, InstCtrl* ctrls,
+                           const ResGroup* groups, const BlockRef* refs, int ngroups,
+                           const ResGroup& one, const ResSync& sync, int grid, int waves,
+                           size_t lds_bytes, int64_t nsteps, int32_t spin_limit, hipStream_t st)
+{
+    const void* k = kernel_of(prec, s, lds);
+    if (!k || grid < 1 || grid > sync.nwg || ngroups < 1 || waves < kResMinWaves ||
+        waves > resident_max_waves(prec) || nsteps < 1 || nsteps > kCoopMaxSteps ||
+        spin_limit < 0 || lds_bytes > kResLdsBytes)
+        return hipErrorInvalidValue;
+    void* args[] = {(void*)&descs,      (void*)&ctrls,      (void*)&groups,
+                    (void*)&refs,       (void*)&one,        (void*)&sync.base,
+                    (void*)&sync.slots, (void*)&sync.edges, (void*)&sync.nwg,
+                    (void*)&nsteps,     (void*)&spin_limit};
+    hipError_t e = hipLaunchCooperativeKernel(k, dim3((unsigned)grid),
+                                              dim3((unsigned)(waves * kWave)), args,
+                                              (unsigned)lds_bytes, st);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(resident_after_kernel, dim3((unsigned)ngroups), dim3(256), 0, st, descs,
+                       ctrls, groups, one, sync.base, (uint32_t)nsteps);
+    return hipGetLastError();
+}
+
+}  // namespace ng
