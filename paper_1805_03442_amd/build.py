@@ -14,7 +14,7 @@ import tempfile
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "_lib", "libng.so")
-SOURCES = ["ng_kernels.hip", "ng_resident.hip", "ng_api.cpp"]
+SOURCES = ["ng_kernels.hip", "ng_resident.hip", "ng_resident2d.hip", "ng_api.cpp"]
 ARCH = os.environ.get("NG_OFFLOAD_ARCH", "gfx950")
 
 FLAGS = [

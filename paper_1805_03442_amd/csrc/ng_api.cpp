@@ -62,9 +62,14 @@ constexpr int kSmallWaves = 8;
 // step kernel (last workgroup); beyond it the per-workgroup release fence costs
 // more than the separate finalize launch.
 constexpr int64_t kFusedMaxBlocks = 256;
-// A batch's only solve, when it is 1D with at most this many cells, runs in the
-// cooperative kernel: many steps per launch over many workgroups, with one
-// exchange per step instead of two launches.
+// A batch's only solve, when it has at most this many cells, runs in the
+// cooperative kernels: many steps per launch over many workgroups, with one
+// exchange per step instead of two launches.  2D, us per step with one launch
+// per step and cooperative (FP32; FP64; mixed): 48x40 13 and 6.0, 32 and 10.1, 14
+// and 6.2; 600^2 16.3 and 9.5, 26 and 18.2, 17 and 10.5; 1024^2 27 and 19.1, 58
+// and 44.8, 36 and 22.6; 2048^2 60 and 52, 146 and 141, 98 and 87.  3000^2 is a
+// draw and 4096^2 slower (212 and 226, 532 and 555, 323 and 381): there the waves
+// have work for many times the launch's cost, and plain loads use the L2.
 constexpr int64_t kCoopCells = int64_t(1) << 22;
 // polls of an exchange's wait before it gives up (each a memory round trip
 // of about a microsecond and a short sleep: about a second)
@@ -80,6 +85,10 @@ constexpr int32_t kCoopSpin = 1 << 20;
 constexpr int64_t kResSolo64 = 4;
 constexpr int64_t kResSolo32 = 8;
 constexpr int64_t kResSegs = 4;
+// 2D: rows a wave takes at least.  Us per step with 2, 3 and 4 (FP32 / FP64):
+// 256^2 6.9 / 12.7, 6.8 / 11.2, 7.8 / 12.9; 600^2 9.7 / 18.5, 9.5 / 18.2, 10.5 /
+// 20.9 (2 rows: the launch's records then no longer fit the smallest grids).
+constexpr int64_t kRes2Rows = 3;
 // Pinned staging buffers of the initial-state upload (two, used in turn).
 constexpr size_t kStageBytes = size_t(16) << 20;
 // Host threads converting one staging chunk, and the cells each takes at least.
@@ -122,7 +131,7 @@ size_t solve_bytes(const ng_grid* g, int prec)
 // header): what resident_shape takes at most.
 size_t res_wgs_of(const ng_grid* g)
 {
-    if (g->ndim != 1) return 0;
+    if (g->ndim != 1) return (size_t)std::min<int64_t>(partial_cap_of(g), kCoopFlat);
     return (size_t)std::min<int64_t>(cdiv(strips_of(g), kResSegs), kCoopFlat);
 }
 // The same for a batch, at most 1/64 of its arena (none in an arena below 4 MB)
@@ -304,8 +313,11 @@ struct Slot {
     bool reported = false;
 };
 
-// One cooperative launch: its solve, kernel and shape (launch_resident).
+// One cooperative launch: its solve, kernel and shape (launch_resident,
+// launch_resident2d).
 struct ResLaunch {
+    int dim = 1;
+    int chunks = 0;      // 2D: runs of rows
     int s = 0;
     bool lds = false;
     int grid = 0, waves = 0;
@@ -528,10 +540,10 @@ void shape_solve(ng_batch* b, Slot& s, bool alone = true)
 {
     InstDesc& d = s.d;
     int dim = s.dim;
-    d.waves_per_block = s.small ? 1 : (s.coop ? kResMinWaves : waves_of(b, dim, {{d.nx, d.ny}}));
+    d.waves_per_block = s.small ? 1 : (s.coop && dim == 1 ? kResMinWaves : waves_of(b, dim, {{d.nx, d.ny}}));
     if (s.small)
         d.rows_per_item = dim == 2 ? kSmallRows2D : kSmallSegs1D;
-    else if (s.coop)
+    else if (s.coop && dim == 1)
         d.rows_per_item = 1;
     else if (b->rows[dim] != kAutoRows)
         d.rows_per_item = b->rows[dim];
@@ -583,9 +595,36 @@ void resident_shape(const InstDesc& d, int prec, int cus, ResLaunch& r)
                                      resident_max_waves(kind_of(prec)));
 }
 
-// The cooperative path: a batch whose only live solve is 1D and has at most
-// coop_limit cells, on a device that supports cooperative launches.  Marks
-// that solve (Slot::coop) and plans its launch.
+// Shape of a 2D solve's cooperative launch: every strip's rows in as many runs
+// of at least kRes2Rows rows as there are waves for, in workgroups of four waves
+// (one per SIMD of a CU) while there are CUs for them, then of more.  rec_bytes:
+// the solve's reduction space, which holds the workgroups' records.
+bool resident_shape2d(const InstDesc& d, int prec, int cus, size_t rec_bytes, ResLaunch& r)
+{
+    const int64_t strips = cdiv(d.nx, kInterior), cap = std::min<int64_t>(cus, kCoopFlat);
+    const int64_t maxw = resident2d_max_waves(kind_of(prec));
+    int64_t per = cdiv(d.ny, kRes2Rows);
+    int64_t waves = kResMinWaves;
+    if (strips * per > cap * waves) waves = std::min<int64_t>(maxw, cdiv(strips * per, cap));
+    if (strips * per > cap * waves) per = cap * waves / strips;
+    while (per > 1 && coop_space((uint64_t)cdiv(strips * per, waves)) > rec_bytes) per--;
+    if (per < 1) return false;
+    r.dim = 2;
+    r.chunks = (int)per;
+    r.waves = (int)waves;
+    r.grid = (int)cdiv(strips * per, waves);
+    r.one.G = r.grid;
+    r.s = d.riemann == NG_HLL ? 5
+          : d.any_bc          ? (prec == NG_FP64 && d.cl_recipe == 3 ? 4 : 3)
+                              : (d.cl_recipe <= 2 ? d.cl_recipe : 0);
+    return true;
+}
+
+// The cooperative path: a batch whose only live solve has at most coop_limit
+// cells (1D), on a device that supports cooperative launches.  Marks that
+// solve (Slot::coop) and plans its launch.  A 2D solve takes it too unless the
+// caller has asked for another path's shape (launch shape, persistent limit,
+// graph length, separate acceptance).
 int choose_coop(ng_batch* b)
 {
     b->res.clear();
@@ -600,7 +639,10 @@ int choose_coop(ng_batch* b)
     const int64_t lim = b->coop_limit >= 0 ? b->coop_limit : kCoopCells;
     if (live != 1 || lim == 0 || b->res_nwg == 0) return NG_OK;
     Slot& s = b->slots[cand];
-    if (s.dim != 1 || s.d.ncell > lim) return NG_OK;
+    if (s.d.ncell > lim) return NG_OK;
+    if (s.dim == 2 && (b->rows[2] != kDefaultRows2D || b->waves[2] != kDefaultWaves2D ||
+                       b->small_limit >= 0 || b->graph_steps != kDefaultGraphSteps || !b->fused))
+        return NG_OK;
     if (b->dev_coop < 0) {
         int dev = 0, coop = 0, cus = 0;
         CK(b, hipGetDevice(&dev));
@@ -611,9 +653,16 @@ int choose_coop(ng_batch* b)
     }
     if (!b->dev_coop || b->dev_cus < 1) return NG_OK;
     ResLaunch r;
-    resident_shape(s.d, b->prec, b->dev_cus, r);
     int per_cu = 0;
-    CK(b, resident_capacity(kind_of(b->prec), r.s, r.lds, r.waves, r.lds_bytes, &per_cu));
+    if (s.dim == 1) {
+        resident_shape(s.d, b->prec, b->dev_cus, r);
+        CK(b, resident_capacity(kind_of(b->prec), r.s, r.lds, r.waves, r.lds_bytes, &per_cu));
+    } else {
+        if (!resident_shape2d(s.d, b->prec, b->dev_cus,
+                              align_up((size_t)s.partial_cap * sizeof(Partial)), r))
+            return NG_OK;
+        CK(b, resident2d_capacity(kind_of(b->prec), r.s, r.grid > 1, r.waves, &per_cu));
+    }
     if ((int64_t)per_cu * b->dev_cus < r.grid || (size_t)r.grid > b->res_nwg ||
         coop_space((uint64_t)r.grid) > align_up((size_t)s.partial_cap * sizeof(Partial)))
         return NG_OK;
@@ -636,6 +685,12 @@ int enqueue_coop(ng_batch* b, int64_t nsteps)
             if (b->res_steps > (uint64_t(1) << 31)) {
                 CK(b, hipMemsetAsync(b->arena + b->L.res, 0, res_space(b->res_nwg), b->stream));
                 b->res_steps = (uint64_t)n + 1;
+            }
+            if (r.dim == 2) {
+                CK(b, launch_resident2d(kind_of(b->prec), r.s, b->d_descs(), b->d_ctrls(),
+                                        r.one.inst, b->d_sync(), r.grid, r.chunks, r.waves, n,
+                                        b->coop_spin, b->stream));
+                continue;
             }
             CK(b, launch_resident(kind_of(b->prec), r.s, r.lds, b->d_descs(), b->d_ctrls(), nullptr,
                                   nullptr, 1, r.one, b->d_sync(), r.grid, r.waves, r.lds_bytes, n,
@@ -790,7 +845,7 @@ int enqueue_timed(ng_batch* b, int64_t nsteps)
     size_t ne = 0;
     std::vector<std::pair<size_t, size_t>> step_pairs, fin_pairs;
     double small_ms = 0.0;
-    if (!b->res.empty()) {
+    if (!b->res.empty() && b->res[0].dim == 1) {
         hipEvent_t e0 = get_event(b, 0), e1 = get_event(b, 1);
         if (!e0 || !e1) return dev_err(b, hipErrorOutOfMemory, "hipEventCreate");
         CK(b, hipEventRecord(e0, b->stream));
@@ -1600,6 +1655,7 @@ int ng_set_graph_steps(ng_solver* s, int32_t steps)
 {
     if (!s || steps < 1 || steps > 4096) return NG_EINVAL;
     s->b->graph_steps = steps;
+    s->b->dirty = true;   // the path of a lone 2D solve may change
     drop_graph(s->b);
     return NG_OK;
 }

@@ -107,6 +107,7 @@ struct Plain64 {
     static constexpr int kMinWaves1D = 3;
     // largest workgroup of a resident launch
     static constexpr int kResThreads = 768;
+    static constexpr int kRes2Threads = 512;
     // U^n of the updated row is re-read from cache (no registers to spare)
     static constexpr bool kKeepRows = false;
     // the energy slot holds E itself
@@ -177,6 +178,8 @@ struct Dev32 {
     // CU): 2^20 cells 12.3 against 13.2 us per step with eight; sixteen-wave
     // workgroups, which force 128 registers, spill and were slower
     static constexpr int kResThreads = 768;
+    // (twelve waves, at 168 registers, spill: 1024^2 20.0 against 19.1 us per step)
+    static constexpr int kRes2Threads = 512;
     // the raw rows stay in registers until their update
     static constexpr bool kKeepRows = true;
     // the energy slot holds e = E - E_nu (deviation from e_r)
@@ -253,6 +256,7 @@ struct Mix32 {
     static constexpr int kMinWaves = 1;
     static constexpr int kMinWaves1D = 1;
     static constexpr int kResThreads = 768;
+    static constexpr int kRes2Threads = 512;
     static constexpr bool kKeepRows = true;
     static constexpr bool kSplitE = true;
     static constexpr bool kRecipes = true;
@@ -600,7 +604,7 @@ __device__ __forceinline__ void coop_fold(const InstDesc& d, InstCtrl& c, int G)
 // and the loads never take a stale line from this XCD's L2).
 typedef __attribute__((address_space(1))) char gchar;
 
-template <class R, int NC>
+template <class R, int NC, bool Coh = false>
 struct Planes {
     typedef __attribute__((address_space(1))) R gR;
     gchar* base[NC];
@@ -610,11 +614,23 @@ struct Planes {
     }
     __device__ __forceinline__ void load(uint32_t boff, R* U) const
     {
-        for (int c = 0; c < NC; c++) U[c] = *(const gR*)(base[c] + (uint64_t)boff);
+        for (int c = 0; c < NC; c++) {
+            if constexpr (Coh)
+                U[c] = __hip_atomic_load((gR*)(base[c] + (uint64_t)boff), __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT);
+            else
+                U[c] = *(const gR*)(base[c] + (uint64_t)boff);
+        }
     }
     __device__ __forceinline__ void store(uint32_t boff, const R* U) const
     {
-        for (int c = 0; c < NC; c++) __builtin_nontemporal_store(U[c], (gR*)(base[c] + (uint64_t)boff));
+        for (int c = 0; c < NC; c++) {
+            if constexpr (Coh)
+                __hip_atomic_store((gR*)(base[c] + (uint64_t)boff), U[c], __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+            else
+                __builtin_nontemporal_store(U[c], (gR*)(base[c] + (uint64_t)boff));
+        }
     }
     // a store that stays in the cache for the next step's load
     __device__ __forceinline__ void store_cached(uint32_t boff, const R* U) const

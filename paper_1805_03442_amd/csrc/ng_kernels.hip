@@ -32,6 +32,7 @@
 #include <type_traits>
 
 #include "ng_device.hpp"
+#include "ng_march2d.hpp"
 #include "ng_launch.hpp"
 
 namespace ng {
@@ -176,257 +177,17 @@ __device__ void last_block_accept(const InstDesc& d, InstCtrl& c, const StepCtl&
 
 // ================================================================ 2D step
 
-// y-face flux: the normal velocity is v, so the Riemann solver sees
-// (rho, v, u, p, E_nu) and returns (., G_v, G_u, ., .)
-template <class P, int RS>
-__device__ __forceinline__ void flux_y(const typename P::K& k, const typename P::R* N,
-                                       const typename P::R* S, typename P::R* G)
-{
-    using R = typename P::R;
-    R a[5] = {N[0], N[2], N[1], N[3], N[4]};
-    R b[5] = {S[0], S[2], S[1], S[3], S[4]};
-    R f[5];
-    P::template flux<RS>(k, a, b, f);
-    G[0] = f[0];
-    G[1] = f[2];
-    G[2] = f[1];
-    G[3] = f[3];
-    G[4] = f[4];
-}
-
-// One work item of the 2D step: strip (60 columns + halo) x chunk of rows.
-// CL: closure recipe of the FP32 arithmetic (0: general).
-template <class P, int RS, bool BC, int CL = 0>
-__device__ __forceinline__ void march2d(const InstDesc& d, const typename P::K& k, int cur,
-                                        const double* gsrc, int64_t item, int lane,
-                                        Acc<typename P::R>& acc)
-{
-    using R = typename P::R;
-    constexpr int NC = 5;
-    // the HLLC flux takes the full density in its face states
-    constexpr bool FR = RS == 0;
-    const int64_t nx = d.nx, ny = d.ny;
-    const int64_t strip = item % d.nstrips, chunk = item / d.nstrips;
-    const int64_t x0 = strip * kInterior;
-    bool flipx = false;
-    const int64_t x = BC ? axis_cell(x0 - kHalo + lane, nx, d.bc[0], d.bc[1], flipx)
-                         : wrap_axis(x0 - kHalo + lane, nx);
-    const bool inner = lane >= kHalo && lane < kWave - kHalo && x0 + (lane - kHalo) < nx;
-    // rows in 32 bits (a grid has fewer than 2^30 cells): the row arithmetic
-    // is the same for every lane and stays on the scalar unit
-    const int nyi = (int)ny;
-    const int r0 = (int)(chunk * d.rows_per_item);
-    const int r1 = r0 + d.rows_per_item < nyi ? r0 + d.rows_per_item : nyi;
-    using St = typename P::St;
-    const Planes<St, NC> src(d.buf[cur], d.ncell);
-    const Planes<St, NC> dst(d.buf[cur ^ 1], d.ncell);
-    const uint32_t rowb = (uint32_t)(nx * (int64_t)sizeof(St));
-    const uint32_t xb = (uint32_t)(x * (int64_t)sizeof(St));
-    // byte offset of (row r, this lane's column); r within two rows of [0, ny)
-    auto boff = [&](int r) -> uint32_t {
-        int rr;
-        if (BC) {
-            bool f;
-            rr = (int)axis_cell(r, ny, d.bc[2], d.bc[3], f);
-        } else {
-            rr = r < 0 ? r + nyi : (r >= nyi ? r - nyi : r);
-        }
-        return (uint32_t)rr * rowb + xb;
-    };
-    // a loaded row r as ghost values: the lanes before a forced source take
-    // its wave, wall ghosts carry the mirrored normal momentum (x ends: rho u,
-    // y ends: rho v)
-    const int64_t xr = x0 - kHalo + lane;
-    const bool srcx = BC && d.bc[0] == kBcSource && xr < 0;
-    const double* gs = gsrc + (xr == -1 ? 0 : 5);
-    // the source drives the ghosts of the rows of its segment (all rows when
-    // the segment's half-width is not positive)
-    auto src_row = [&](int64_t r) -> bool {
-        if (!(d.src_hw > 0.0)) return true;
-        const double y = ((double)r + 0.5) * d.h;
-        return fabs(y - d.src_yc) <= d.src_hw;
-    };
-    auto ghost = [&](int64_t r, St* U) {
-        if (BC) {
-            bool fy;
-            (void)axis_cell(r, ny, d.bc[2], d.bc[3], fy);
-            if (srcx && src_row(r)) source_cell<St, NC, P::kSplitE>(d, gs, U);
-            if (flipx) U[1] = -U[1];
-            if (fy) U[2] = -U[2];
-        }
-    };
-    // pump and sink only inside an active wedge (the 2D sector run of section
-    // 3): 1 or 0 for this lane's cell centre in row r, ghost cells included
-    const bool wedge = BC && d.wedge_tan > 0.0;
-    const double xc = ((double)xr + 0.5) * d.h;
-    auto active = [&](int64_t r) -> R {
-        if (!wedge) return (R)1;
-        const double y = ((double)r + 0.5) * d.h;
-        const double dx = xc - d.wedge_x0;
-        return (dx >= 0.0 && fabs(y - d.wedge_y0) <= dx * d.wedge_tan) ? (R)1 : (R)0;
-    };
-    auto slopes_x = [&](const R* W, R* sx) {
-        for (int c = 0; c < NC; c++) {
-            R l = from_left(W[c]), r = from_right(W[c]);
-            R a = W[c] - l, b = r - W[c];
-            pin(a);
-            pin(b);
-            sx[c] = minmod(a, b);
-        }
-    };
-
-    // Rolling state, in two register sets that swap roles every row:
-    //   Wd/We  primitive state of rows i+1 / i+2 (and, FP32, 1/rho)
-    //   Dp/Dn  y-differences W(i+1) - W(i) / W(i+2) - W(i+1)
-    //   h0/h1  half-step state of rows i / i+1;  x0s/x1s their x-slopes
-    //   Np/Nn  north face states of rows i / i+1
-    //   Gp/Gn  y-fluxes at faces i-1/2 / i+1/2
-    //   Uc/Ux  raw row i+2 (arrived) / row i+3 (in flight)
-    // Policies that keep the raw rows hold four of them (rows i .. i+3) in a
-    // ring U0..U3, so U^n of row i is still in registers at its update;
-    // the others re-read it and use U2/U3 only.
-    R WA[NC + 1], WB[NC + 1], DA[NC], DB[NC], HA[NC], HB[NC], XA[NC], XB[NC];
-    R NA[NC], NB[NC], GA[NC], GB[NC];
-    St U0[NC], U1[NC], U2[NC], U3[NC];
-
-    // prologue: rows r0-2 .. r0+1
-    {
-        R Wa[NC + 1], Wb[NC + 1], Wc[NC + 1], sy[NC], sx[NC], hb[NC], S[NC];
-        St t[NC];
-        St* t0 = P::kKeepRows ? U0 : t;
-        St* t1 = P::kKeepRows ? U1 : t;
-        src.load(boff(r0 - 2), t);
-        ghost(r0 - 2, t);
-        P::prim(k, t, Wa);
-        src.load(boff(r0 - 1), t);
-        ghost(r0 - 1, t);
-        P::prim(k, t, Wb);
-        src.load(boff(r0), t0);
-        ghost(r0, t0);
-        P::prim(k, t0, Wc);
-        src.load(boff(r0 + 1), t1);
-        ghost(r0 + 1, t1);
-        P::prim(k, t1, WA);
-        src.load(boff(r0 + 2), U2);
-        // row r0-1: its north face state
-        slopes_x(Wb, sx);
-        for (int c = 0; c < NC; c++) sy[c] = minmod(Wb[c] - Wa[c], Wc[c] - Wb[c]);
-        P::template predict<FR, CL>(k, Wb, sx, sy, hb, active(r0 - 1));
-        for (int c = 0; c < NC; c++) hb[c] = face(hb[c], sy[c]);
-        // row r0
-        slopes_x(Wc, XA);
-        for (int c = 0; c < NC; c++) {
-            R dp = Wc[c] - Wb[c];
-            DA[c] = WA[c] - Wc[c];
-            sy[c] = minmod(dp, DA[c]);
-        }
-        P::template predict<FR, CL>(k, Wc, XA, sy, HA, active(r0));
-        for (int c = 0; c < NC; c++) {
-            S[c] = face(HA[c], -sy[c]);
-            NA[c] = face(HA[c], sy[c]);
-        }
-        flux_y<P, RS>(k, hb, S, GA);
-    }
-
-    auto row = [&](int i, R* Wd, R* We, R* Dp, R* Dn, R* h0, R* h1, R* x0s, R* x1s,
-                   R* Np, R* Nn, R* Gp, R* Gn, St* Uk, St* Uc, St* Ux) {
-        // U^n of row i: kept in the ring (Uk), or else re-read from cache
-        // for the update (it was loaded two rows ago).  Loads complete in
-        // order, so an FP64 state asks for it before row i+3 and waiting for
-        // it does not also wait for the row in flight; an FP32 state asks late
-        // and keeps the registers free meanwhile
-        constexpr bool reread = !P::kKeepRows;
-        constexpr bool early = reread && sizeof(St) == 8;
-        St Ul[NC];
-        St* Un = reread ? Ul : Uk;
-        if (early) src.load(boff(i), Ul);
-        // row i+2 has arrived in Uc; put row i+3 in flight.  The load is
-        // issued on every row (on the chunk's last row it fetches row i+2
-        // again, from cache, into the unused buffer): a load on one path only
-        // makes the compiler's wait counts assume the other path, so each row
-        // would wait for the loads it has just issued
-        ghost(i + 2, Uc);
-        P::prim(k, Uc, We);
-        src.load(boff(i + 1 < r1 ? i + 3 : i + 2), Ux);
-        // predictor of row i+1
-        R sy[NC];
-        slopes_x(Wd, x1s);
-        for (int c = 0; c < NC; c++) {
-            Dn[c] = We[c] - Wd[c];
-            sy[c] = minmod(Dp[c], Dn[c]);
-        }
-        P::template predict<FR, CL>(k, Wd, x1s, sy, h1, active(i + 1));
-        // y-face i+1/2 between the north state of row i and the south state
-        // of row i+1
-        {
-            R S[NC];
-            for (int c = 0; c < NC; c++) {
-                S[c] = face(h1[c], -sy[c]);
-                Nn[c] = face(h1[c], sy[c]);
-            }
-            flux_y<P, RS>(k, Np, S, Gn);
-        }
-        // x-faces of row i: lane j computes face j+1/2 from its east state and
-        // lane j+1's west state; face j-1/2 comes from lane j-1
-        R dF[NC], dG[NC];
-        {
-            R E[NC], Wr[NC], Fx[NC];
-            for (int c = 0; c < NC; c++) {
-                E[c] = face(h0[c], x0s[c]);
-                Wr[c] = from_right(face(h0[c], -x0s[c]));
-            }
-            P::template flux<RS>(k, E, Wr, Fx);
-            for (int c = 0; c < NC; c++) {
-                dF[c] = Fx[c] - from_left(Fx[c]);
-                pin(dF[c]);
-                dG[c] = Gn[c] - Gp[c];
-            }
-        }
-        // update of row i
-        St Uo[NC];
-        R Wn[NC + 1], sE, sV;
-        const uint32_t o = boff(i);
-        if (reread && !early) src.load(o, Ul);
-        P::template update<FR, CL>(k, Un, dF, dG, h0, Uo, sE, sV, active(i));
-        P::prim(k, Uo, Wn);
-        R s = P::speed(k, Wn);
-        if (inner) {
-            dst.store(o, Uo);
-            acc_cell<P, NC>(acc, k, Uo, Wn, s, sE, sV);
-        }
-    };
-
-    int i = r0;
-    if constexpr (P::kKeepRows) {
-        for (; i < r1; i += 4) {
-            row(i, WA, WB, DA, DB, HA, HB, XA, XB, NA, NB, GA, GB, U0, U2, U3);
-            if (i + 1 >= r1) break;
-            row(i + 1, WB, WA, DB, DA, HB, HA, XB, XA, NB, NA, GB, GA, U1, U3, U0);
-            if (i + 2 >= r1) break;
-            row(i + 2, WA, WB, DA, DB, HA, HB, XA, XB, NA, NB, GA, GB, U2, U0, U1);
-            if (i + 3 >= r1) break;
-            row(i + 3, WB, WA, DB, DA, HB, HA, XB, XA, NB, NA, GB, GA, U3, U1, U2);
-        }
-    } else {
-        for (; i + 1 < r1; i += 2) {
-            row(i, WA, WB, DA, DB, HA, HB, XA, XB, NA, NB, GA, GB, U0, U2, U3);
-            row(i + 1, WB, WA, DB, DA, HB, HA, XB, XA, NB, NA, GB, GA, U0, U3, U2);
-        }
-        if (i < r1) row(i, WA, WB, DA, DB, HA, HB, XA, XB, NA, NB, GA, GB, U0, U2, U3);
-    }
-}
-
 // periodic solves take the plain wrap-around indexing; solves with a wall or
 // outflow end the ghost mapping (a uniform choice per solve)
 template <class P, int RS>
 __device__ __forceinline__ void march2d_bc(const InstDesc& d, const typename P::K& k, int cur,
-                                           const double* gsrc, int64_t item, int lane,
+                                           const double* gsrc, int strip, int r0, int r1, int lane,
                                            Acc<typename P::R>& acc)
 {
     if (d.any_bc)
-        march2d<P, RS, true>(d, k, cur, gsrc, item, lane, acc);
+        march2d<P, RS, true>(d, k, cur, gsrc, strip, r0, r1, lane, acc);
     else
-        march2d<P, RS, false>(d, k, cur, gsrc, item, lane, acc);
+        march2d<P, RS, false>(d, k, cur, gsrc, strip, r0, r1, lane, acc);
 }
 
 // One HLLC work item: a periodic solve whose closures match a compiled recipe
@@ -435,19 +196,32 @@ __device__ __forceinline__ void march2d_bc(const InstDesc& d, const typename P::
 // state is bitwise the same on every path.
 template <class P, int CL = kRecipes>
 __device__ __forceinline__ void march2d_hllc(const InstDesc& d, const typename P::K& k, int cur,
-                                             const double* gsrc, int64_t item, int lane,
-                                             Acc<typename P::R>& acc)
+                                             const double* gsrc, int strip, int r0, int r1,
+                                             int lane, Acc<typename P::R>& acc)
 {
     if constexpr (P::kRecipes && CL > 0) {
         if (!d.any_bc && d.cl_recipe == CL) {
-            march2d<P, 0, false, CL>(d, k, cur, gsrc, item, lane, acc);
+            march2d<P, 0, false, CL>(d, k, cur, gsrc, strip, r0, r1, lane, acc);
             return;
         }
-        march2d_hllc<P, CL - 1>(d, k, cur, gsrc, item, lane, acc);
+        march2d_hllc<P, CL - 1>(d, k, cur, gsrc, strip, r0, r1, lane, acc);
     } else {
-        march2d_bc<P, 0>(d, k, cur, gsrc, item, lane, acc);
+        march2d_bc<P, 0>(d, k, cur, gsrc, strip, r0, r1, lane, acc);
     }
 }
+
+// The strip and rows of work item `item`: strips fastest, then chunks of
+// rows_per_item rows.
+struct Item2d {
+    int strip, r0, r1;
+    __device__ Item2d(const InstDesc& d, int64_t item)
+    {
+        const int64_t chunk = item / d.nstrips;
+        strip = (int)(item - chunk * d.nstrips);
+        r0 = (int)(chunk * d.rows_per_item);
+        r1 = r0 + d.rows_per_item < (int)d.ny ? r0 + d.rows_per_item : (int)d.ny;
+    }
+};
 
 // V = 0: any solves (boundary kind, flux and closures per solve);
 // V = 1 + r: every solve of the launch is periodic with the HLLC flux and its
@@ -473,12 +247,13 @@ __global__ void __launch_bounds__(256, P::kMinWaves) step2d_kernel(const InstDes
     acc_init(acc);
     const int64_t item = (int64_t)br.local * nwaves + wave;
     if (item < d.nitems) {
+        const Item2d it(d, item);
         if constexpr (V > 0)
-            march2d<P, 0, false, V - 1>(d, k, sc.cur, sc.gsrc, item, lane, acc);
+            march2d<P, 0, false, V - 1>(d, k, sc.cur, sc.gsrc, it.strip, it.r0, it.r1, lane, acc);
         else if (d.riemann == 1)
-            march2d_bc<P, 1>(d, k, sc.cur, sc.gsrc, item, lane, acc);
+            march2d_bc<P, 1>(d, k, sc.cur, sc.gsrc, it.strip, it.r0, it.r1, lane, acc);
         else
-            march2d_hllc<P>(d, k, sc.cur, sc.gsrc, item, lane, acc);
+            march2d_hllc<P>(d, k, sc.cur, sc.gsrc, it.strip, it.r0, it.r1, lane, acc);
     }
     acc_finish<P>(acc, k);
     Partial* parts = (Partial*)d.partials;
@@ -789,10 +564,11 @@ __global__ void __launch_bounds__(512) run_small_kernel(const InstDesc* __restri
         acc_init(acc);
         for (int64_t item = wave; item < d.nitems; item += nw) {
             if constexpr (NC == 5) {
+                const Item2d it(d, item);
                 if (d.riemann == 1)
-                    march2d_bc<P, 1>(d, k, sc.cur, sc.gsrc, item, lane, acc);
+                    march2d_bc<P, 1>(d, k, sc.cur, sc.gsrc, it.strip, it.r0, it.r1, lane, acc);
                 else
-                    march2d_hllc<P>(d, k, sc.cur, sc.gsrc, item, lane, acc);
+                    march2d_hllc<P>(d, k, sc.cur, sc.gsrc, it.strip, it.r0, it.r1, lane, acc);
             } else {
                 march1d_any<P>(d, k, sc.cur, sc.gsrc, item, lane, acc);
             }

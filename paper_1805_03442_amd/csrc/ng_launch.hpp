@@ -47,6 +47,19 @@ hipError_t launch_resident(int prec, int s, bool lds, const InstDesc* descs, Ins
                            const ResGroup& one, const ResSync& sync, int grid, int waves,
                            size_t lds_bytes, int64_t nsteps, int32_t spin_limit, hipStream_t st);
 
+// Folds the records of a cooperative launch into the control blocks of its
+// solves and moves the step number on.
+hipError_t launch_resident_after(const InstDesc* descs, InstCtrl* ctrls, const ResGroup* groups,
+                                 int ngroups, const ResGroup& one, uint32_t* base, int64_t nsteps,
+                                 hipStream_t st);
+// The same for one 2D solve: every strip's rows in `chunks` runs, a wave each.  s: 0..2 periodic HLLC with closure recipe s, 3 HLLC with any
+// ends, 4 the same with recipe 3 (FP64), 5 HLL.
+int resident2d_max_waves(int prec);
+hipError_t resident2d_capacity(int prec, int s, bool coh, int waves, int* blocks_per_cu);
+hipError_t launch_resident2d(int prec, int s, const InstDesc* descs, InstCtrl* ctrls, int inst,
+                             const ResSync& sync, int grid, int chunks, int waves, int64_t nsteps,
+                             int32_t spin_limit, hipStream_t st);
+
 // Static scratch of the entry point that allocates nothing: its device
 // address on the current device (looked up once per device), and the kernel
 // that writes one solve's descriptor, control block, finalize index list and

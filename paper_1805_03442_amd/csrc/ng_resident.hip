@@ -46,114 +46,10 @@
 #include <type_traits>
 
 #include "ng_device.hpp"
+#include "ng_exchange.hpp"
 #include "ng_launch.hpp"
 
 namespace ng {
-
-// largest value of the wave, in every lane (NaN lanes ignored): row shifts,
-// then the two row broadcasts, leave it in lane 63
-template <int Ctrl, int RowMask>
-__device__ __forceinline__ double dpp_max(double v)
-{
-    const int lo = __builtin_amdgcn_update_dpp(__double2loint(v), __double2loint(v), Ctrl, RowMask,
-                                               0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp(__double2hiint(v), __double2hiint(v), Ctrl, RowMask,
-                                               0xf, false);
-    return fmax(v, __hiloint2double(hi, lo));
-}
-__device__ __forceinline__ double wave_max(double v)
-{
-    v = dpp_max<0x111, 0xf>(v);   // row_shr:1
-    v = dpp_max<0x112, 0xf>(v);   // row_shr:2
-    v = dpp_max<0x114, 0xf>(v);   // row_shr:4
-    v = dpp_max<0x118, 0xf>(v);   // row_shr:8
-    v = dpp_max<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
-    v = dpp_max<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
-    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63),
-                            __builtin_amdgcn_readlane(__double2loint(v), 63));
-}
-// union of three flag bits over the wave
-__device__ __forceinline__ uint32_t wave_flags(uint32_t f)
-{
-    return (__builtin_amdgcn_ballot_w64(f & 1u) ? 1u : 0u) |
-           (__builtin_amdgcn_ballot_w64(f & 2u) ? 2u : 0u) |
-           (__builtin_amdgcn_ballot_w64(f & 4u) ? 4u : 0u);
-}
-
-// Wave-wide wait for the slots of step gen of G <= kCoopFlat workgroups: lane j
-// reads slots j, j + 64, ... (NQ of them; past the last, the last again), at
-// most spin_limit polls after the first; true when they ran out.  m, f: the
-// largest signal speed and the union of the flags of this lane's slots.  R:
-// the speed's type.  What the exchange costs is set by the slots' spacing:
-// stores of different XCDs into one 128-byte line wait for each other, and
-// every poll moves all slots' sectors to every workgroup.  Us per step at 16,
-// 32, 64 and 128 bytes per slot: 16384 FP32 cells (69 workgroups) 3.03, 2.67,
-// 2.48, 2.51; 262144 FP64 cells (256 workgroups) 8.19, 8.03, 8.10, 8.36; three
-// words per slot at 32 bytes made it 8.5.  So 64 bytes up to 128 workgroups,
-// then 32.  (A second poll in flight, and no sleep between polls, changed
-// nothing or cost 0.1 us.)
-constexpr int slot_words(uint32_t G) { return G <= 128u ? 8 : 4; }
-template <class R, int NQ>
-struct SlotPoll {
-    static constexpr int kWords = (int)sizeof(R) / 4;
-    uint64_t w[NQ][kWords];
-    __device__ __forceinline__ void issue(const uint64_t* slots, uint32_t G, int lane)
-    {
-#pragma unroll
-        for (int q = 0; q < NQ; q++) {
-            const uint32_t j = (uint32_t)lane + 64u * q;
-#pragma unroll
-            for (int x = 0; x < kWords; x++)
-                w[q][x] = __hip_atomic_load(slots + (j < G ? j : G - 1u) * slot_words(NQ <= 2 ? 1u : 256u) + x,
-                                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-    }
-    __device__ __forceinline__ bool have(uint32_t gen) const
-    {
-        bool h = true;
-#pragma unroll
-        for (int q = 0; q < NQ; q++)
-#pragma unroll
-            for (int x = 0; x < kWords; x++) h = h && (uint32_t)(w[q][x] >> 32) == gen;
-        return __builtin_amdgcn_ballot_w64(!h) == 0ull;
-    }
-    __device__ __forceinline__ void fold(double& m, uint32_t& f) const
-    {
-        m = 0.0;
-        f = 0u;
-#pragma unroll
-        for (int q = 0; q < NQ; q++) {
-            const uint32_t hi = (uint32_t)w[q][kWords - 1];
-            if (hi & 0x80000000u)
-                f |= hi & 7u;
-            else if (kWords == 2)
-                m = fmax(m, __hiloint2double((int)hi, (int)(uint32_t)w[q][0]));
-            else
-                m = fmax(m, (double)__int_as_float((int)hi));
-        }
-    }
-};
-template <class R, int NQ>
-__device__ __forceinline__ bool poll_slots(const uint64_t* slots, uint32_t G, uint32_t gen,
-                                           int lane, int32_t spin_limit, double& m, uint32_t& f)
-{
-    static_assert(kCoopFlat <= 4 * kWave, "at most four slots per lane");
-    SlotPoll<R, NQ> a;
-    a.issue(slots, G, lane);
-    for (int32_t n = 0;; n++) {
-        if (a.have(gen)) {
-            a.fold(m, f);
-            return false;
-        }
-        if (n >= spin_limit) {
-            m = 0.0;
-            f = 0u;
-            return true;
-        }
-        __builtin_amdgcn_s_sleep(1);
-        a.issue(slots, G, lane);
-    }
-}
 
 // One cell as LDS holds it: its components side by side, so that a lane loads
 // or stores it in one or two 16-byte operations.
@@ -197,9 +93,8 @@ __global__ void __launch_bounds__(P::kResThreads) run_resident_kernel(
     __shared__ double s_sum[kCoopMaxWaves][10];
     __shared__ double s_sm[kCoopMaxWaves];
     __shared__ uint32_t s_fl[kCoopMaxWaves];
-    __shared__ double s_dt;           // the next CFL step
-    __shared__ uint32_t s_bad;        // failure flags of the step
-    __shared__ int s_stall[2];        // a wait of wave 0 / wave 1 ran out
+    __shared__ ResCtl s_c;
+    __shared__ int s_edge_out;        // the wait for the edges ran out
     __shared__ double s_gsrc[3][5];   // a forced source's ghosts
     // cells of this workgroup: segments [g0, g1), cells [c0, c0 + len)
     const int64_t n = d.nx;
@@ -230,15 +125,6 @@ __global__ void __launch_bounds__(P::kResThreads) run_resident_kernel(
         }
     };
 
-    // the solve's control, as every workgroup tracks it
-    const double t_end = c.t_end;
-    const int64_t max_steps = c.max_steps;
-    double t = c.t, dt_cfl = c.dt_cfl, dt_last = c.dt_last;
-    int64_t steps = c.steps;
-    int nacc = 0, status = c.status;
-    uint32_t bad = 0;
-    bool active = status == 0 && t < t_end && steps < max_steps;
-    bool stalled = false;
     const bool src = d.bc[0] == kBcSource;
     // neighbours of this workgroup; ends without one have ghosts by the
     // boundary rule (a lone workgroup's periodic ghosts too)
@@ -248,9 +134,14 @@ __global__ void __launch_bounds__(P::kResThreads) run_resident_kernel(
     const uint32_t nb_r = (uint32_t)gr.first + (b + 1u < G ? b + 1u : 0u);
     const uint32_t me = (uint32_t)gr.first + b;
 
+    if (tid == 0) {
+        s_c.start(c);
+        s_edge_out = 0;
+    }
+    __syncthreads();
     // copy 0 from the state buffer, ghosts by the boundary rule
-    if (active) {
-        if (src && tid < H) source_ghost_at(d, t, tid, s_gsrc[tid]);
+    if (s_c.go) {
+        if (src && tid < H) source_ghost_at(d, s_c.t, tid, s_gsrc[tid]);
         __syncthreads();
         auto fetch = [&](int64_t j, ResCell<St>& out) {
             bool flip;
@@ -277,18 +168,14 @@ __global__ void __launch_bounds__(P::kResThreads) run_resident_kernel(
     Acc<R> acc;
     acc_init(acc);
     double bud0 = 0.0, bud1 = 0.0;
-    int st_c = -1;         // last computed step
-    bool cur_ok = false;   // ... and whether this workgroup saw it accepted
+    int st = 0;
 
-    for (int st = 0; st < (int)nsteps && active; st++) {
+    for (; st < (int)nsteps && s_c.go; st++) {
         const uint32_t gen = gen0 + 1u + (uint32_t)st;
         const int q = st & 1;   // U^n is in copy q
-        double dt = dt_cfl;
-        if (t + dt > t_end) dt = t_end - t;
-        const typename P::K k = P::make(d, dt);
+        const typename P::K k = P::make(d, s_c.dt);
+        const double t_new = src ? s_c.t + s_c.dt : 0.0;   // where the step leads
         acc_init(acc);
-        st_c = st;
-        cur_ok = false;
         // this wave's segments; the next segment's cells are fetched before
         // the current one is computed
         if (f0 < f1) {
@@ -358,32 +245,10 @@ __global__ void __launch_bounds__(P::kResThreads) run_resident_kernel(
             uint32_t f = wave_flags(lane < nw ? s_fl[lane] : 0u);
             bool out = false;
             if (G > 1u) {
-                constexpr int kWords = (int)sizeof(R) / 4;
-                uint64_t* const sl = slots + (size_t)q * nwg * kResSlot + (size_t)gr.first * kResSlot;
-                if (lane < kWords) {
-                    // lane 0: the low half in FP64, the whole in FP32
-                    const uint32_t lo = kWords == 2 ? (uint32_t)__double2loint(m)
-                                                    : (uint32_t)__float_as_int((float)m);
-                    const uint32_t hi = (uint32_t)__double2hiint(m);
-                    uint32_t v = lane == 0 ? lo : hi;
-                    if (f && lane == kWords - 1) v = 0x80000000u | f;
-                    __hip_atomic_store(sl + (size_t)slot_words(G) * b + lane, ((uint64_t)gen << 32) | v,
-                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
-                if (G <= 64u)
-                    out = poll_slots<R, 1>(sl, G, gen, lane, spin_limit, m, f);
-                else if (G <= 128u)
-                    out = poll_slots<R, 2>(sl, G, gen, lane, spin_limit, m, f);
-                else
-                    out = poll_slots<R, 4>(sl, G, gen, lane, spin_limit, m, f);
-                m = wave_max(m);
-                f = wave_flags(f);
+                out = exchange_slots<R>(slots + ((size_t)q * nwg + gr.first) * kResSlot, G, b, gen,
+                                        lane, spin_limit, m, f);
             }
-            if (lane == 0) {
-                s_stall[0] = out ? 1 : 0;
-                s_bad = f & 7u;
-                s_dt = d.cfl * d.h / m;
-            }
+            if (lane == 0) s_c.decide(d, c, out, m, f);
         } else if (wave == 1) {
             // Ghosts of the next step, copy q ^ 1.  Lane w of a side carries
             // 32 bits of one value of one edge cell: it publishes this
@@ -445,77 +310,34 @@ __global__ void __launch_bounds__(P::kResThreads) run_resident_kernel(
                 }
             if (mine && !(src && side == 0 && !has_l))
                 ((uint32_t*)&ghost_at(q ^ 1, side * H + g).u[x])[hf] = v;
-            if (lane == 0) s_stall[1] = out ? 1 : 0;
+            if (out && lane == 0) s_edge_out = 1;
         } else if (wave == 2 && src && b == 0u && lane < H) {
             // a forced source's ghosts for the time the step leads to
-            source_ghost_at(d, t + dt, lane, s_gsrc[lane]);
+            source_ghost_at(d, t_new, lane, s_gsrc[lane]);
             St U[NC];
             source_cell<St, NC, P::kSplitE>(d, s_gsrc[lane], U);
             for (int x = 0; x < NC; x++) ghost_at(q ^ 1, H - 1 - lane).u[x] = U[x];
         }
         __syncthreads();
-        if (s_stall[0] | s_stall[1]) {
-            stalled = true;
-            break;
-        }
-        bad = s_bad;
-        if (bad) {
-            status = -3;   // NG_EPHYS
-            active = false;
-        } else {
-            // accepted: as accept_step advances the control block
-            t = t + dt;
-            steps = steps + 1;
-            dt_last = dt;
-            dt_cfl = s_dt;
-            nacc++;
-            active = t < t_end && steps < max_steps;
+        if (s_edge_out) break;
+        if (s_c.ok) {
             bud0 += acc.src[0];
             bud1 += acc.src[1];
-            cur_ok = true;
         }
     }
-    // The workgroup's records (lanes, then waves in order): the sums of the
-    // last computed step and, when this workgroup did not see that step
-    // accepted, of the last accepted one.  The after-kernel folds the records
-    // of the last step the most advanced workgroup accepted, found by its
-    // parity.
+    // st_c: the last computed step; cur_ok: this workgroup saw it accepted.
+    // (Edges that did not come stop the workgroup like slots that did not, but
+    // with the step accepted: its next one is what it cannot compute.)
+    const int nacc = s_c.nacc;
+    const bool cur_ok = s_c.ok != 0;
+    const int st_c = s_edge_out ? st : st - 1;
+    if (s_edge_out && cur_ok) {
+        bud0 += acc.src[0];
+        bud1 += acc.src[1];
+    }
+    const bool stalled = s_c.stalled != 0;
     auto put_rec = [&](const Acc<R>& a, double b0, double b1, int step) {
-        double v[10];
-        for (int x = 0; x < 5; x++) v[x] = a.tot[x];
-        v[5] = b0;
-        v[6] = b1;
-        v[7] = (double)a.smax;
-        v[8] = (double)a.rmin;
-        v[9] = (double)a.pmin;
-        for (int m = 32; m >= 1; m >>= 1) {
-            for (int x = 0; x < 7; x++) v[x] += lane_xor(v[x], lane, m);
-            v[7] = fmax(v[7], lane_xor(v[7], lane, m));
-            v[8] = fmin(v[8], lane_xor(v[8], lane, m));
-            v[9] = fmin(v[9], lane_xor(v[9], lane, m));
-        }
-        __syncthreads();
-        if (lane == 0)
-            for (int x = 0; x < 10; x++) s_sum[wave][x] = v[x];
-        __syncthreads();
-        if (tid == 0) {
-            for (int w = 1; w < nw; w++) {
-                for (int x = 0; x < 7; x++) v[x] += s_sum[w][x];
-                v[7] = fmax(v[7], s_sum[w][7]);
-                v[8] = fmin(v[8], s_sum[w][8]);
-                v[9] = fmin(v[9], s_sum[w][9]);
-            }
-            CoopRec r;
-            for (int x = 0; x < 5; x++) r.tot[x] = v[x];
-            r.src[0] = v[5];
-            r.src[1] = v[6];
-            r.smax = v[7];
-            r.rho_min = v[8];
-            r.p_min = v[9];
-            r.flags = 0u;
-            r.step = (uint32_t)step;
-            recs[(size_t)(step & 1) * G + b] = r;
-        }
+        put_record(a, b0, b1, step, recs + (size_t)(step & 1) * G + b, s_sum, wave, lane, nw);
     };
     if (st_c >= 0) {
         if (cur_ok) {
@@ -557,17 +379,8 @@ __global__ void __launch_bounds__(P::kResThreads) run_resident_kernel(
     }
     // and its view of the control
     if (tid == 0) {
-        CoopView w;
-        w.t = t;
-        w.dt_cfl = dt_cfl;
-        w.dt_last = dt_last;
-        w.steps = steps;
-        w.nacc = nacc;
-        w.cur = cur0 ^ (nacc & 1);
-        w.status = status;
-        w.flags = bad;
-        w.stalled = stalled ? 1u : 0u;
-        views[b] = w;
+        if (s_edge_out) s_c.stalled = 1;
+        s_c.view(cur0, views[b]);
     }
 }
 
@@ -649,8 +462,15 @@ hipError_t launch_resident(int prec, int s, bool lds, const InstDesc* descs, Ins
                                               dim3((unsigned)(waves * kWave)), args,
                                               (unsigned)lds_bytes, st);
     if (e != hipSuccess) return e;
+    return launch_resident_after(descs, ctrls, groups, ngroups, one, sync.base, nsteps, st);
+}
+
+hipError_t launch_resident_after(const InstDesc* descs, InstCtrl* ctrls, const ResGroup* groups,
+                                 int ngroups, const ResGroup& one, uint32_t* base, int64_t nsteps,
+                                 hipStream_t st)
+{
     hipLaunchKernelGGL(resident_after_kernel, dim3((unsigned)ngroups), dim3(256), 0, st, descs,
-                       ctrls, groups, one, sync.base, (uint32_t)nsteps);
+                       ctrls, groups, one, base, (uint32_t)nsteps);
     return hipGetLastError();
 }
 
