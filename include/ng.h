@@ -228,6 +228,10 @@ int ng_diagnostics(ng_solver* s, ng_diag* out);
 int ng_get_state(ng_solver* s, double* prim_out);
 int ng_get_conserved(ng_solver* s, double* cons_out);
 
+/* The same into planes of the caller's: planes[c] receives component c (4
+ * pointers in 1D, 5 in 2D), primitive (prim != 0) or conserved.  Synchronising. */
+int ng_get_planes(ng_solver* s, int32_t prim, double* const* planes);
+
 /* Launch shape of the step kernel: rows per work item (2D) or 60-cell
  * segments per work item (1D), and waves per workgroup.  Results do not
  * depend on it (every cell's arithmetic is the same); only the order of the
@@ -384,6 +388,8 @@ int ng_batch_active(ng_batch* b, int32_t* nactive);
 int ng_batch_diagnostics(ng_batch* b, int32_t slot, ng_diag* out);
 int ng_batch_get_state(ng_batch* b, int32_t slot, double* prim_out);
 int ng_batch_get_conserved(ng_batch* b, int32_t slot, double* cons_out);
+
+int ng_batch_get_planes(ng_batch* b, int32_t slot, int32_t prim, double* const* planes);
 
 /* Release a slot and its arena space. */
 int ng_batch_remove(ng_batch* b, int32_t slot);

@@ -13,6 +13,7 @@
 #include <algorithm>
 #include <map>
 #include <string>
+#include <system_error>
 #include <thread>
 #include <utility>
 #include <vector>
@@ -71,6 +72,10 @@ constexpr int64_t kFusedMaxBlocks = 256;
 // draw and 4096^2 slower (212 and 226, 532 and 555, 323 and 381): there the waves
 // have work for many times the launch's cost, and plain loads use the L2.
 constexpr int64_t kCoopCells = int64_t(1) << 22;
+// Calls of fewer steps launch them one by one: a cooperative launch and the fold
+// of its records cost about three steps (one step of 200 to 600^2 cells 47 to 57
+// us against 34 to 42 us; four steps 54 to 85 against 56 to 99).
+constexpr int64_t kCoopMinSteps = 3;
 // polls of an exchange's wait before it gives up (each a memory round trip
 // of about a microsecond and a short sleep: about a second)
 constexpr int32_t kCoopSpin = 1 << 20;
@@ -94,6 +99,10 @@ constexpr size_t kStageBytes = size_t(16) << 20;
 // Host threads converting one staging chunk, and the cells each takes at least.
 constexpr int kHostThreads = 8;
 constexpr int64_t kCellsPerThread = 65536;
+// FP64 values a host thread copies out of the staging at least
+constexpr int64_t kValuesPerThread = 65536;
+// least pinned staging: the FP64 planes of a small solve in one piece
+constexpr size_t kStageMin = size_t(64) << 10;
 
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -407,6 +416,7 @@ struct ng_batch {
 struct ng_solver {
     ng_batch* b = nullptr;
     int slot = 0;
+    bool limited = false;   // the control block has ng_run_to_time's limits
     std::string err;
 };
 
@@ -540,11 +550,9 @@ void shape_solve(ng_batch* b, Slot& s, bool alone = true)
 {
     InstDesc& d = s.d;
     int dim = s.dim;
-    d.waves_per_block = s.small ? 1 : (s.coop && dim == 1 ? kResMinWaves : waves_of(b, dim, {{d.nx, d.ny}}));
+    d.waves_per_block = s.small ? 1 : waves_of(b, dim, {{d.nx, d.ny}});
     if (s.small)
         d.rows_per_item = dim == 2 ? kSmallRows2D : kSmallSegs1D;
-    else if (s.coop && dim == 1)
-        d.rows_per_item = 1;
     else if (b->rows[dim] != kAutoRows)
         d.rows_per_item = b->rows[dim];
     else if (b->auto_rows[dim] > 0)
@@ -955,7 +963,7 @@ int enqueue_steps(ng_batch* b, int64_t nsteps)
     int rc = rebuild(b);
     if (rc) return rc;
     if (b->timing) return enqueue_timed(b, nsteps);
-    if (!b->res.empty()) return enqueue_coop(b, nsteps);
+    if (!b->res.empty() && nsteps >= kCoopMinSteps) return enqueue_coop(b, nsteps);
     rc = enqueue_small(b, nsteps, b->stream);
     if (rc || !any_big(b)) return rc;
     int64_t left = nsteps;
@@ -982,16 +990,11 @@ int read_ctrls(ng_batch* b)
     return NG_OK;
 }
 
-int set_limits(ng_batch* b, const std::vector<int32_t>& slots, double t_end, int64_t max_steps)
+// The stop condition of a solve (t_end, at most max_steps more steps; -1: any
+// number), set on the stream by the slot's entry of the resident index list.
+int set_limits(ng_batch* b, int slot, double t_end, int64_t max_steps)
 {
-    if (slots.empty()) return NG_OK;
-    // the instance list of a dim lives in device memory; use a scratch copy of
-    // the requested slots in the unused third list
-    int32_t* dl = b->d_insts(0);
-    CK(b, hipMemcpyAsync(dl, slots.data(), sizeof(int32_t) * slots.size(), hipMemcpyHostToDevice,
-                         b->stream));
-    CK(b, launch_set_limits(b->d_ctrls(), dl, (int)slots.size(), t_end, max_steps, b->stream));
-    CK(b, hipStreamSynchronize(b->stream));
+    CK(b, launch_set_limits(b->d_ctrls(), b->d_iota() + slot, 1, t_end, max_steps, b->stream));
     return NG_OK;
 }
 
@@ -1191,7 +1194,7 @@ int64_t small_limit_of(const ng_batch* b)
 // Pinned staging of at least `bytes` (at most kStageBytes), both buffers idle.
 int ensure_stage(ng_batch* b, size_t bytes)
 {
-    bytes = bytes < kStageBytes ? bytes : kStageBytes;
+    bytes = std::max(kStageMin, std::min(bytes, kStageBytes));
     if (b->stage_bytes >= bytes) return NG_OK;
     for (int k = 0; k < 2; k++) {
         CK(b, hipEventSynchronize(b->ev_stage[k]));
@@ -1385,56 +1388,90 @@ int add_solve(ng_batch* b, const ng_gas* gas, const ng_grid* grid, const ng_nume
     return NG_OK;
 }
 
-int read_conserved(ng_batch* b, int slot, double* out, bool prim)
+// Copy m values per plane from the staging (planes of m) to the caller's planes
+// at i0, split over host threads where that is worth a thread.
+void unstage(const double* st, int64_t m, int nc, double* const* planes, int64_t i0)
 {
-    if (slot < 0 || slot >= b->capacity || !b->slots[slot].live || !out) {
+    const int64_t total = m * nc;
+    const int hw = (int)std::thread::hardware_concurrency();
+    int nt = (int)std::min<int64_t>(total / kValuesPerThread, std::min(hw < 1 ? 1 : hw, kHostThreads));
+    auto part = [&](int64_t a, int64_t b) {
+        for (int c = 0; c < nc; c++) {
+            const int64_t lo = std::max<int64_t>(a, c * m), hi = std::min<int64_t>(b, (c + 1) * m);
+            if (lo < hi)
+                memcpy(planes[c] + i0 + (lo - c * m), st + lo, sizeof(double) * (size_t)(hi - lo));
+        }
+    };
+    if (nt <= 1) {
+        part(0, total);
+        return;
+    }
+    std::thread th[kHostThreads];
+    int64_t from = 0;   // what no thread took is copied here
+    for (int t = nt - 1; t >= 1; t--) {
+        try {
+            th[t] = std::thread(part, total * t / nt, total * (t + 1) / nt);
+        } catch (const std::system_error&) {
+            from = total * (t + 1) / nt;
+            break;
+        }
+    }
+    part(0, from ? from : total / nt);
+    for (auto& x : th)
+        if (x.joinable()) x.join();
+}
+
+// The current state of a solve as FP64 planes.  The device converts it chunk by
+// chunk straight into the two pinned staging buffers, and the host copies one
+// chunk out while the next is written.  (Before, the whole stored state came
+// through the driver's pageable copy into a zeroed vector, and one host thread
+// converted and copied it again: 2^20 FP32 cells 13.8 ms, 4096^2 278 ms.)
+int read_planes(ng_batch* b, int slot, double* const* planes, bool prim)
+{
+    if (slot < 0 || slot >= b->capacity || !b->slots[slot].live) {
         b->err = "invalid slot or output";
         return NG_EINVAL;
     }
-    int rc = read_ctrls(b);
-    if (rc) return rc;
-    Slot& s = b->slots[slot];
+    const Slot& s = b->slots[slot];
     const int nc = ncomp(s.dim);
-    const int64_t n = s.d.ncell;
-    const int cur = b->h_ctrls[slot].cur;
-    std::vector<double> U((size_t)nc * n);
-    if (b->prec != NG_FP32) {
-        // FP64 state (deviations from the reference for the mixed path)
-        CK(b, hipMemcpy(U.data(), (void*)s.d.buf[cur], sizeof(double) * U.size(),
-                        hipMemcpyDeviceToHost));
-        if (b->prec == NG_MIXED) {
-            const double ref5[5] = {s.d.uref[0], 0.0, 0.0, s.d.e1_r, s.d.uref[4]};
-            const double ref4[4] = {s.d.uref[0], 0.0, s.d.e1_r, s.d.uref[4]};
-            const double* ref = nc == 5 ? ref5 : ref4;
-            for (int c = 0; c < nc; c++)
-                for (int64_t i = 0; i < n; i++) U[c * n + i] += ref[c];
+    for (int c = 0; c < nc; c++)
+        if (!planes || !planes[c]) {
+            b->err = "invalid slot or output";
+            return NG_EINVAL;
         }
-    } else {
-        std::vector<float> D((size_t)nc * n);
-        CK(b, hipMemcpy(D.data(), (void*)s.d.buf[cur], sizeof(float) * D.size(),
-                        hipMemcpyDeviceToHost));
-        const double ref5[5] = {s.d.uref[0], 0.0, 0.0, s.d.e1_r, s.d.uref[4]};
-        const double ref4[4] = {s.d.uref[0], 0.0, s.d.e1_r, s.d.uref[4]};
-        const double* ref = nc == 5 ? ref5 : ref4;
-        for (int c = 0; c < nc; c++)
-            for (int64_t i = 0; i < n; i++) U[c * n + i] = ref[c] + (double)D[c * n + i];
+    const int64_t n = s.d.ncell;
+    const int64_t per = (int64_t)(b->stage_bytes / (sizeof(double) * nc));
+    if (per < 1) {
+        b->err = "no staging";
+        return NG_EDEVICE;
     }
-    if (b->prec != NG_FP64) {
-        // the energy slot held E - E_nu
-        const int iE = nc == 5 ? 3 : 2, iV = nc - 1;
-        for (int64_t i = 0; i < n; i++) U[iE * n + i] += U[iV * n + i];
-    }
-    if (!prim) {
-        memcpy(out, U.data(), sizeof(double) * U.size());
-        return NG_OK;
-    }
-    double Uc[5], Wc[5];
-    for (int64_t i = 0; i < n; i++) {
-        for (int c = 0; c < nc; c++) Uc[c] = U[c * n + i];
-        cons_to_prim_cell(s.d.gm1, nc, Uc, Wc);
-        for (int c = 0; c < nc; c++) out[c * n + i] = Wc[c];
+    // (both buffers are idle once the last uploads have left them; the event of
+    // a buffer then marks the kernel that fills it)
+    auto fill = [&](int k, int64_t i0) -> hipError_t {
+        hipError_t e = hipEventSynchronize(b->ev_stage[k]);
+        if (e == hipSuccess)
+            e = launch_readout(s.dim, kind_of(b->prec), b->d_descs(), b->d_ctrls(), slot, i0,
+                               std::min(per, n - i0), prim ? 1 : 0, (double*)b->stage[k], b->stream);
+        if (e == hipSuccess) e = hipEventRecord(b->ev_stage[k], b->stream);
+        return e;
+    };
+    CK(b, fill(0, 0));
+    int k = 0;
+    for (int64_t i0 = 0; i0 < n; i0 += per, k ^= 1) {
+        if (i0 + per < n) CK(b, fill(k ^ 1, i0 + per));
+        CK(b, hipEventSynchronize(b->ev_stage[k]));
+        unstage((const double*)b->stage[k], std::min(per, n - i0), nc, planes, i0);
     }
     return NG_OK;
+}
+
+// the same into nc contiguous planes
+int read_conserved(ng_batch* b, int slot, double* out, bool prim)
+{
+    double* planes[5] = {};
+    if (out && slot >= 0 && slot < b->capacity)
+        for (int c = 0; c < ncomp(b->slots[slot].dim); c++) planes[c] = out + c * b->slots[slot].d.ncell;
+    return read_planes(b, slot, planes, prim);
 }
 
 int diag_of(ng_batch* b, int slot, ng_diag* out)
@@ -1558,9 +1595,12 @@ int ng_step(ng_solver* s, int64_t nsteps)
 {
     if (!s || nsteps < 0) return NG_EINVAL;
     if (nsteps == 0) return NG_OK;
-    std::vector<int32_t> sl{s->slot};
-    int rc = set_limits(s->b, sl, INFINITY, -1);
-    if (!rc) rc = enqueue_steps(s->b, nsteps);
+    // a new solver has no limits; ng_run_to_time leaves its own
+    int rc = s->limited ? set_limits(s->b, s->slot, INFINITY, -1) : NG_OK;
+    if (!rc) {
+        s->limited = false;
+        rc = enqueue_steps(s->b, nsteps);
+    }
     return solver_rc(s, rc);
 }
 
@@ -1571,11 +1611,12 @@ int ng_run_to_time(ng_solver* s, double t_end, int64_t max_steps, int64_t* steps
     int rc = read_ctrls(b);
     if (rc) return solver_rc(s, rc);
     const int64_t steps0 = b->h_ctrls[s->slot].steps;
-    std::vector<int32_t> sl{s->slot};
-    rc = set_limits(b, sl, t_end, max_steps);
+    s->limited = true;
+    rc = set_limits(b, s->slot, t_end, max_steps);
     if (rc) return solver_rc(s, rc);
-    for (;;) {
-        rc = read_ctrls(b);
+    for (bool first = true;; first = false) {
+        // (the limits change nothing of what was just read)
+        if (!first) rc = read_ctrls(b);
         if (rc) return solver_rc(s, rc);
         const InstCtrl& c = b->h_ctrls[s->slot];
         if (c.status != 0) {
@@ -1617,6 +1658,12 @@ int ng_get_conserved(ng_solver* s, double* cons_out)
 {
     if (!s) return NG_EINVAL;
     return solver_rc(s, read_conserved(s->b, s->slot, cons_out, false));
+}
+
+int ng_get_planes(ng_solver* s, int32_t prim, double* const* planes)
+{
+    if (!s) return NG_EINVAL;
+    return solver_rc(s, read_planes(s->b, s->slot, planes, prim != 0));
 }
 
 int ng_set_launch(ng_solver* s, int32_t rows_per_item, int32_t waves_per_block)
@@ -1910,6 +1957,12 @@ int ng_batch_get_conserved(ng_batch* b, int32_t slot, double* cons_out)
 {
     if (!b) return NG_EINVAL;
     return read_conserved(b, slot, cons_out, false);
+}
+
+int ng_batch_get_planes(ng_batch* b, int32_t slot, int32_t prim, double* const* planes)
+{
+    if (!b) return NG_EINVAL;
+    return read_planes(b, slot, planes, prim != 0);
 }
 
 int ng_batch_remove(ng_batch* b, int32_t slot)

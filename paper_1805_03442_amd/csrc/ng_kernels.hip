@@ -523,6 +523,43 @@ __global__ void __launch_bounds__(256) prime_kernel(const InstDesc* __restrict__
     block_reduce_store(acc, parts + br.local, wave, lane, nwaves);
 }
 
+// ============================================================== read-out
+
+// Cells [i0, i0 + m) of a solve's current state as full FP64 planes of m values
+// at out (pinned host memory: the kernel's stores cross the bus themselves):
+// conserved, or primitive by eq. (5).  The reference of a deviation state is
+// added back and its energy slot made E again; every operation is one IEEE
+// operation in a fixed order.
+template <class St, int NC, bool Split>
+__global__ void __launch_bounds__(256) readout_kernel(const InstDesc* __restrict__ descs,
+                                                      const InstCtrl* __restrict__ ctrls, int inst,
+                                                      int64_t i0, int64_t m, int prim,
+                                                      double* __restrict__ out)
+{
+    const InstDesc& d = descs[inst];
+    const St* __restrict__ src = (const St*)d.buf[ctrls[inst].cur];
+    constexpr int iE = NC == 5 ? 3 : 2, iV = NC - 1;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m;
+         i += (int64_t)gridDim.x * blockDim.x) {
+        double U[NC];
+        for (int c = 0; c < NC; c++) U[c] = (double)src[c * d.ncell + i0 + i];
+        if (Split) {
+            for (int c = 0; c < NC; c++)
+                U[c] = U[c] + (c == 0 ? d.uref[0] : (c == iE ? d.e1_r : (c == iV ? d.uref[4] : 0.0)));
+            U[iE] = U[iE] + U[iV];
+        }
+        if (prim) {
+            const double rho = U[0], u = U[1] / rho;
+            const double v = NC == 5 ? U[2] / rho : 0.0;
+            const double ke = 0.5 * rho * (NC == 5 ? u * u + v * v : u * u);
+            U[1] = u;
+            if (NC == 5) U[2] = v;
+            U[iE] = d.gm1 * (U[iE] - ke - U[iV]);
+        }
+        for (int c = 0; c < NC; c++) __builtin_nontemporal_store(U[c], out + c * m + i);
+    }
+}
+
 // Set the stop condition of a set of solves (a kernel, so that it can sit in
 // the stream between captured graphs without a host copy).
 __global__ void set_limits_kernel(InstCtrl* __restrict__ ctrls, const int32_t* __restrict__ insts,
@@ -788,6 +825,27 @@ hipError_t launch_small(int dim, int prec, const InstDesc* descs, InstCtrl* ctrl
             hipLaunchKernelGGL((run_small_kernel<Dev32<4>, 4>), g, b, 0, s, descs, ctrls, insts, nsteps);
         else
             hipLaunchKernelGGL((run_small_kernel<Mix32<4>, 4>), g, b, 0, s, descs, ctrls, insts, nsteps);
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_readout(int dim, int prec, const InstDesc* descs, const InstCtrl* ctrls, int inst,
+                          int64_t i0, int64_t m, int prim, double* out, hipStream_t s)
+{
+    if (m <= 0) return hipErrorInvalidValue;
+    const int64_t g = (m + 255) / 256;
+    dim3 gr((unsigned)(g < 1024 ? g : 1024)), b(256);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, gr, b, 0, s, descs, ctrls, inst, i0, m, prim, out);
+    };
+    if (dim == 2) {
+        if (prec == 0) go(readout_kernel<double, 5, false>);
+        else if (prec == 1) go(readout_kernel<float, 5, true>);
+        else go(readout_kernel<double, 5, true>);
+    } else {
+        if (prec == 0) go(readout_kernel<double, 4, false>);
+        else if (prec == 1) go(readout_kernel<float, 4, true>);
+        else go(readout_kernel<double, 4, true>);
     }
     return hipGetLastError();
 }

@@ -30,10 +30,11 @@ GAS_FIELDS = ("gamma", "R", "Cv", "rho0", "T0", "tau0", "tau_rho", "tau_T",
 
 EXPORTED = (
     "ng_strerror", "ng_state_bytes", "ng_init_state", "ng_init_conserved", "ng_step",
-    "ng_run_to_time", "ng_diagnostics", "ng_get_state", "ng_get_conserved", "ng_set_launch",
+    "ng_run_to_time", "ng_diagnostics", "ng_get_state", "ng_get_conserved", "ng_get_planes", "ng_set_launch",
     "ng_set_graph_steps", "ng_set_small_limit", "ng_set_coop", "ng_set_fused_accept", "ng_enable_timing", "ng_kernel_time", "ng_last_error", "ng_destroy",
     "ng_batch_create", "ng_batch_solve_bytes", "ng_batch_fits", "ng_batch_add", "ng_batch_run", "ng_batch_poll",
     "ng_batch_active", "ng_batch_diagnostics", "ng_batch_get_state", "ng_batch_get_conserved",
+    "ng_batch_get_planes",
     "ng_batch_remove", "ng_batch_set_launch", "ng_batch_set_small_limit", "ng_batch_set_coop",
     "ng_batch_set_fused_accept", "ng_batch_last_error",
     "ng_batch_destroy", "ng_step_static", "ng_static_last_error",
@@ -102,6 +103,8 @@ def lib():
             "ng_diagnostics": ([vp, C.POINTER(NgDiag)], C.c_int),
             "ng_get_state": ([vp, dp], C.c_int),
             "ng_get_conserved": ([vp, dp], C.c_int),
+            "ng_get_planes": ([vp, i32, C.POINTER(dp)], C.c_int),
+            "ng_batch_get_planes": ([vp, i32, i32, C.POINTER(dp)], C.c_int),
             "ng_set_launch": ([vp, i32, i32], C.c_int),
             "ng_set_graph_steps": ([vp, i32], C.c_int),
             "ng_set_small_limit": ([vp, i64], C.c_int),
@@ -179,13 +182,15 @@ def _planes(W: np.ndarray, ny: int) -> np.ndarray:
     return np.ascontiguousarray(W)
 
 
-def _unplanes(A: np.ndarray, nx: int, ny: int) -> np.ndarray:
-    """ABI plane layout -> (5, ny, nx) with a zero v plane in 1D."""
-    if ny == 1:
-        out = np.zeros((5, 1, nx))
-        out[[0, 1, 3, 4], 0] = A.reshape(4, nx)
-        return out
-    return A.reshape(5, ny, nx)
+def _read(call, nx: int, ny: int) -> np.ndarray:
+    """(5, ny, nx) filled by ``call(planes)``, planes an array of the addresses
+    of its component planes (4 in 1D, whose v plane stays zero)."""
+    out = np.zeros((5, 1, nx)) if ny == 1 else np.empty((5, ny, nx))
+    dp = C.POINTER(C.c_double)
+    comps = (0, 1, 3, 4) if ny == 1 else range(5)
+    planes = (dp * 5)(*[out[c].ctypes.data_as(dp) for c in comps])
+    call(planes)
+    return out
 
 
 def stream_handle(stream=None) -> int:
@@ -258,16 +263,12 @@ class Solver:
         return d.as_dict()
 
     def conserved(self) -> np.ndarray:
-        nc = 4 if self.ny == 1 else 5
-        out = np.empty(nc * self.nx * self.ny)
-        check(lib().ng_get_conserved(self.h, _dp(out)), "ng_get_conserved", self._err())
-        return _unplanes(out, self.nx, self.ny)
+        return _read(lambda p: check(lib().ng_get_planes(self.h, 0, p), "ng_get_conserved",
+                                     self._err()), self.nx, self.ny)
 
     def primitive(self) -> np.ndarray:
-        nc = 4 if self.ny == 1 else 5
-        out = np.empty(nc * self.nx * self.ny)
-        check(lib().ng_get_state(self.h, _dp(out)), "ng_get_state", self._err())
-        return _unplanes(out, self.nx, self.ny)
+        return _read(lambda p: check(lib().ng_get_planes(self.h, 1, p), "ng_get_state",
+                                     self._err()), self.nx, self.ny)
 
     def set_launch(self, rows: int = 0, waves: int = 0):
         check(lib().ng_set_launch(self.h, int(rows), int(waves)), "ng_set_launch", self._err())
@@ -394,19 +395,13 @@ class Batch:
 
     def conserved(self, slot: int) -> np.ndarray:
         nx, ny = self.shapes[slot]
-        nc = 4 if ny == 1 else 5
-        out = np.empty(nc * nx * ny)
-        check(lib().ng_batch_get_conserved(self.h, int(slot), _dp(out)), "ng_batch_get_conserved",
-              self._err())
-        return _unplanes(out, nx, ny)
+        return _read(lambda p: check(lib().ng_batch_get_planes(self.h, int(slot), 0, p),
+                                     "ng_batch_get_conserved", self._err()), nx, ny)
 
     def primitive(self, slot: int) -> np.ndarray:
         nx, ny = self.shapes[slot]
-        nc = 4 if ny == 1 else 5
-        out = np.empty(nc * nx * ny)
-        check(lib().ng_batch_get_state(self.h, int(slot), _dp(out)), "ng_batch_get_state",
-              self._err())
-        return _unplanes(out, nx, ny)
+        return _read(lambda p: check(lib().ng_batch_get_planes(self.h, int(slot), 1, p),
+                                     "ng_batch_get_state", self._err()), nx, ny)
 
     def remove(self, slot: int):
         check(lib().ng_batch_remove(self.h, int(slot)), "ng_batch_remove", self._err())
