@@ -90,6 +90,10 @@ constexpr int32_t kCoopSpin = 1 << 20;
 constexpr int64_t kResSolo64 = 4;
 constexpr int64_t kResSolo32 = 8;
 constexpr int64_t kResSegs = 4;
+// A batch's 1D solves run side by side in cooperative launches of four-wave
+// workgroups (resident_fleet); its header has room for the workgroups of this
+// many full launches.
+constexpr size_t kResLaunches = 4;
 // 2D: rows a wave takes at least.  Us per step with 2, 3 and 4 (FP32 / FP64):
 // 256^2 6.9 / 12.7, 6.8 / 11.2, 7.8 / 12.9; 600^2 9.7 / 18.5, 9.5 / 18.2, 10.5 /
 // 20.9 (2 rows: the launch's records then no longer fit the smallest grids).
@@ -143,15 +147,18 @@ size_t res_wgs_of(const ng_grid* g)
     if (g->ndim != 1) return (size_t)std::min<int64_t>(partial_cap_of(g), kCoopFlat);
     return (size_t)std::min<int64_t>(cdiv(strips_of(g), kResSegs), kCoopFlat);
 }
-// The same for a batch, at most 1/64 of its arena (none in an arena below 4 MB)
+// The same for a batch, whose slots and tables take at most 1/64 of its arena
+// (none in an arena below 4 MB)
 size_t res_wgs_of(size_t arena_bytes)
 {
-    const size_t n = std::min<size_t>(arena_bytes / 64 / res_space(1), kCoopFlat);
+    const size_t n = std::min<size_t>(arena_bytes / 64 / res_space(1), kResMaxWgs);
     return n < 64 ? 0 : n;
 }
+// entries of a batch's workgroup table for its cooperative launches
+size_t res_refs_of(int capacity, size_t nwg) { return capacity > 1 ? kResLaunches * nwg : 0; }
 
 struct Layout {
-    size_t descs, ctrls, insts, iota, res, blocks1, blocks2, heap;
+    size_t descs, ctrls, insts, iota, res, groups, refs, blocks1, blocks2, heap;
 };
 
 Layout header_layout(int capacity, size_t tcap1, size_t tcap2, size_t nwg)
@@ -168,6 +175,10 @@ Layout header_layout(int capacity, size_t tcap1, size_t tcap2, size_t nwg)
     o += align_up(sizeof(int32_t) * capacity);
     L.res = o;
     if (nwg) o += align_up(res_space(nwg));
+    L.groups = o;
+    if (nwg && capacity > 1) o += align_up(sizeof(ResGroup) * capacity);
+    L.refs = o;
+    if (nwg) o += align_up(sizeof(BlockRef) * res_refs_of(capacity, nwg));
     L.blocks1 = o;
     o += align_up(sizeof(BlockRef) * tcap1);
     L.blocks2 = o;
@@ -332,6 +343,8 @@ struct ResLaunch {
     int grid = 0, waves = 0;
     size_t lds_bytes = 0;
     ResGroup one{};
+    int ngroups = 0;        // several solves: their groups and workgroups from
+    size_t group0 = 0, ref0 = 0;   // these entries of the tables on
 };
 
 }  // namespace
@@ -357,6 +370,9 @@ struct ng_batch {
     int32_t coop_spin = kCoopSpin;
     // the cooperative launches of one call (none: the other paths run)
     std::vector<ResLaunch> res;
+    std::vector<ResGroup> h_groups;   // tables of the launches of several solves
+    std::vector<BlockRef> h_refs;
+    bool coop_dim[3] = {false, false, false};   // dims whose solves they advance
     size_t res_nwg = 0;        // workgroups the arena header has slots for
     uint64_t res_steps = 0;    // step numbers used since the slots were cleared
     int dev_coop = -1;         // cooperative launch supported (-1: not asked yet)
@@ -371,6 +387,7 @@ struct ng_batch {
     // captured step sequence
     hipGraphExec_t gexec = nullptr;
     int gsteps = 0;
+    bool gskips = false;       // captured without the cooperative dims
     int graph_steps = kDefaultGraphSteps;
     // pinned read-back of the control blocks
     InstCtrl* h_ctrls = nullptr;
@@ -628,29 +645,101 @@ bool resident_shape2d(const InstDesc& d, int prec, int cus, size_t rec_bytes, Re
     return true;
 }
 
-// The cooperative path: a batch whose only live solve has at most coop_limit
-// cells (1D), on a device that supports cooperative launches.  Marks that
-// solve (Slot::coop) and plans its launch.  A 2D solve takes it too unless the
-// caller has asked for another path's shape (launch shape, persistent limit,
-// graph length, separate acceptance).
+// The cooperative launches of several 1D solves side by side (slots in `ids`, all
+// of one kernel): four-wave workgroups, three to a CU at most, each with a run
+// of segments of one solve; the runs are as short as lets all solves into one
+// launch (at least kResSegs segments), so that every CU has the same work.  The
+// cells stay in LDS when the workgroups of a CU share it, else in the state
+// buffers.  Solves beyond one launch's workgroups go to a further launch, after
+// the first has taken all its steps.  False: no room or no such shape.
+int resident_fleet(ng_batch* b, const std::vector<int>& ids, bool* ok)
+{
+    *ok = false;
+    const int kind = kind_of(b->prec);
+    const int64_t cap = std::min<int64_t>((int64_t)b->res_nwg, 3LL * b->dev_cus);
+    const size_t cell = 4 * real_size(b->prec);
+    for (size_t at = 0; at < ids.size();) {
+        const size_t n = std::min<size_t>(ids.size() - at, (size_t)cap);
+        int64_t most = 1, w = 0;
+        auto segs_of = [&](size_t i) { return (int64_t)b->slots[ids[at + i]].d.nstrips; };
+        for (size_t i = 0; i < n; i++) most = std::max(most, segs_of(i));
+        auto wgs_at = [&](int64_t run) {
+            int64_t t = 0;
+            for (size_t i = 0; i < n; i++) t += cdiv(segs_of(i), run);
+            return t;
+        };
+        // shortest run of at least kResSegs segments that fits
+        int64_t lo = std::max<int64_t>(kResSegs, cdiv(most, kCoopFlat)), hi = std::max(most, lo);
+        while (lo < hi) {
+            const int64_t mid = (lo + hi) / 2;
+            if (wgs_at(mid) <= cap) hi = mid;
+            else lo = mid + 1;
+        }
+        const int64_t wgs = wgs_at(lo);
+        if (wgs > cap) return NG_OK;
+        ResLaunch r;
+        r.s = resident_kernel_of(b->slots[ids[at]].d, b->prec);
+        r.waves = kResMinWaves;
+        r.grid = (int)wgs;
+        r.ngroups = (int)n;
+        r.group0 = b->h_groups.size();
+        r.ref0 = b->h_refs.size();
+        int first = 0;
+        for (size_t i = 0; i < n; i++) {
+            const Slot& s = b->slots[ids[at + i]];
+            w = seg_cells(s.d.scheme);
+            ResGroup g;
+            g.inst = ids[at + i];
+            g.G = (int)cdiv(segs_of(i), lo);
+            g.first = first;
+            g.pitch = (int)(cdiv(segs_of(i), g.G) * w + (kWave - w));
+            if (coop_space((uint64_t)g.G) > align_up((size_t)s.partial_cap * sizeof(Partial)))
+                return NG_OK;
+            for (int j = 0; j < g.G; j++) b->h_refs.push_back(BlockRef{(int32_t)i, j});
+            first += g.G;
+            r.lds_bytes = std::max(r.lds_bytes, 2 * cell * (size_t)g.pitch);
+            b->h_groups.push_back(g);
+        }
+        const int64_t per_cu = cdiv(wgs, b->dev_cus);
+        r.lds = r.lds_bytes * (size_t)per_cu <= kResLdsBytes;
+        if (!r.lds) r.lds_bytes = 2 * cell * (size_t)(2 * kCsphHalo);
+        int fits = 0;
+        CK(b, resident_capacity(kind, r.s, r.lds, r.waves, r.lds_bytes, &fits));
+        if (fits < per_cu || b->h_refs.size() > res_refs_of(b->capacity, b->res_nwg)) return NG_OK;
+        b->res.push_back(r);
+        at += n;
+    }
+    *ok = true;
+    return NG_OK;
+}
+
+// The cooperative path, on a device that supports cooperative launches: the 1D
+// solves when each has at most coop_limit cells, and a 2D solve that is the
+// only 2D one, unless the caller has asked for the shape of another path
+// (launch shape, persistent limit, graph length, separate acceptance).  Marks
+// the solves (Slot::coop) and plans their launches.
 int choose_coop(ng_batch* b)
 {
     b->res.clear();
-    int live = 0, cand = -1;
+    b->h_groups.clear();
+    b->h_refs.clear();
+    b->coop_dim[1] = b->coop_dim[2] = false;
+    const int64_t lim = b->coop_limit >= 0 ? b->coop_limit : kCoopCells;
+    std::vector<int> live[3];
+    bool within[3] = {true, true, true};
     for (int i = 0; i < b->capacity; i++) {
         Slot& s = b->slots[i];
         s.coop = false;
         if (!s.live) continue;
-        live++;
-        cand = i;
+        live[s.dim].push_back(i);
+        if (s.d.ncell > lim) within[s.dim] = false;
     }
-    const int64_t lim = b->coop_limit >= 0 ? b->coop_limit : kCoopCells;
-    if (live != 1 || lim == 0 || b->res_nwg == 0) return NG_OK;
-    Slot& s = b->slots[cand];
-    if (s.d.ncell > lim) return NG_OK;
-    if (s.dim == 2 && (b->rows[2] != kDefaultRows2D || b->waves[2] != kDefaultWaves2D ||
-                       b->small_limit >= 0 || b->graph_steps != kDefaultGraphSteps || !b->fused))
-        return NG_OK;
+    if (lim == 0 || b->res_nwg == 0) return NG_OK;
+    const bool two = live[2].size() == 1 && within[2] && b->rows[2] == kDefaultRows2D &&
+                     b->waves[2] == kDefaultWaves2D && b->small_limit < 0 &&
+                     b->graph_steps == kDefaultGraphSteps && b->fused;
+    const bool one = !live[1].empty() && within[1];
+    if (!one && !two) return NG_OK;
     if (b->dev_coop < 0) {
         int dev = 0, coop = 0, cus = 0;
         CK(b, hipGetDevice(&dev));
@@ -660,23 +749,54 @@ int choose_coop(ng_batch* b)
         b->dev_cus = cus;
     }
     if (!b->dev_coop || b->dev_cus < 1) return NG_OK;
-    ResLaunch r;
-    int per_cu = 0;
-    if (s.dim == 1) {
-        resident_shape(s.d, b->prec, b->dev_cus, r);
-        CK(b, resident_capacity(kind_of(b->prec), r.s, r.lds, r.waves, r.lds_bytes, &per_cu));
-    } else {
-        if (!resident_shape2d(s.d, b->prec, b->dev_cus,
-                              align_up((size_t)s.partial_cap * sizeof(Partial)), r))
-            return NG_OK;
-        CK(b, resident2d_capacity(kind_of(b->prec), r.s, r.grid > 1, r.waves, &per_cu));
+    if (two || (one && live[1].size() == 1)) {
+        // a lone solve of its dim
+        for (int dim = 1; dim <= 2; dim++) {
+            if (dim == 1 ? !(one && live[1].size() == 1) : !two) continue;
+            Slot& s = b->slots[live[dim][0]];
+            const size_t rec = align_up((size_t)s.partial_cap * sizeof(Partial));
+            ResLaunch r;
+            int per_cu = 0;
+            if (dim == 1) {
+                resident_shape(s.d, b->prec, b->dev_cus, r);
+                CK(b, resident_capacity(kind_of(b->prec), r.s, r.lds, r.waves, r.lds_bytes, &per_cu));
+            } else {
+                if (!resident_shape2d(s.d, b->prec, b->dev_cus, rec, r)) continue;
+                CK(b, resident2d_capacity(kind_of(b->prec), r.s, r.grid > 1, r.waves, &per_cu));
+            }
+            if ((int64_t)per_cu * b->dev_cus < r.grid || (size_t)r.grid > b->res_nwg ||
+                coop_space((uint64_t)r.grid) > rec)
+                continue;
+            r.one.inst = live[dim][0];
+            s.coop = true;
+            b->coop_dim[dim] = true;
+            b->res.push_back(r);
+        }
     }
-    if ((int64_t)per_cu * b->dev_cus < r.grid || (size_t)r.grid > b->res_nwg ||
-        coop_space((uint64_t)r.grid) > align_up((size_t)s.partial_cap * sizeof(Partial)))
-        return NG_OK;
-    r.one.inst = cand;
-    s.coop = true;
-    b->res.push_back(r);
+    if (one && live[1].size() > 1) {
+        // by kernel; the segments of a solve not yet shaped
+        std::map<int, std::vector<int>> kinds;
+        for (int i : live[1]) {
+            InstDesc& d = b->slots[i].d;
+            d.nstrips = (int32_t)cdiv(d.nx, seg_cells(d.scheme));
+            kinds[resident_kernel_of(d, b->prec)].push_back(i);
+        }
+        const size_t keep = b->res.size();
+        bool ok = true;
+        for (const auto& kv : kinds) {
+            int rc = resident_fleet(b, kv.second, &ok);
+            if (rc) return rc;
+            if (!ok) break;
+        }
+        if (!ok) {
+            b->res.resize(keep);
+            b->h_groups.clear();
+            b->h_refs.clear();
+        } else {
+            for (int i : live[1]) b->slots[i].coop = true;
+            b->coop_dim[1] = true;
+        }
+    }
     return NG_OK;
 }
 
@@ -691,7 +811,7 @@ int enqueue_coop(ng_batch* b, int64_t nsteps)
             // they can meet an old one
             b->res_steps += (uint64_t)n + 1;
             if (b->res_steps > (uint64_t(1) << 31)) {
-                CK(b, hipMemsetAsync(b->arena + b->L.res, 0, res_space(b->res_nwg), b->stream));
+                CK(b, launch_resident_clear(b->d_sync(), res_space(b->res_nwg), b->stream));
                 b->res_steps = (uint64_t)n + 1;
             }
             if (r.dim == 2) {
@@ -700,9 +820,12 @@ int enqueue_coop(ng_batch* b, int64_t nsteps)
                                         b->coop_spin, b->stream));
                 continue;
             }
-            CK(b, launch_resident(kind_of(b->prec), r.s, r.lds, b->d_descs(), b->d_ctrls(), nullptr,
-                                  nullptr, 1, r.one, b->d_sync(), r.grid, r.waves, r.lds_bytes, n,
-                                  b->coop_spin, b->stream));
+            const bool many = r.ngroups > 0;
+            CK(b, launch_resident(kind_of(b->prec), r.s, r.lds, b->d_descs(), b->d_ctrls(),
+                                  many ? (const ResGroup*)(b->arena + b->L.groups) + r.group0 : nullptr,
+                                  many ? (const BlockRef*)(b->arena + b->L.refs) + r.ref0 : nullptr,
+                                  many ? r.ngroups : 1, r.one, b->d_sync(), r.grid, r.waves,
+                                  r.lds_bytes, n, b->coop_spin, b->stream));
         }
         left -= n;
     }
@@ -798,6 +921,12 @@ int rebuild(ng_batch* b)
             CK(b, hipMemcpyAsync(b->d_blocks(dim), b->h_blocks[dim].data(),
                                  sizeof(BlockRef) * b->h_blocks[dim].size(),
                                  hipMemcpyHostToDevice, b->stream));
+    if (!b->h_refs.empty()) {
+        CK(b, hipMemcpyAsync(b->arena + b->L.groups, b->h_groups.data(),
+                             sizeof(ResGroup) * b->h_groups.size(), hipMemcpyHostToDevice, b->stream));
+        CK(b, hipMemcpyAsync(b->arena + b->L.refs, b->h_refs.data(),
+                             sizeof(BlockRef) * b->h_refs.size(), hipMemcpyHostToDevice, b->stream));
+    }
     CK(b, hipStreamSynchronize(b->stream));
     drop_graph(b);
     b->dirty = false;
@@ -814,11 +943,12 @@ hipEvent_t get_event(ng_batch* b, size_t i)
     return b->ev_pool[i];
 }
 
-// Enqueue the kernels of one step of every active solve on stream st.
-int enqueue_one(ng_batch* b, hipStream_t st)
+// Enqueue the kernels of one step of every active solve on stream st (of the
+// dims in skip: none).
+int enqueue_one(ng_batch* b, hipStream_t st, const bool* skip = nullptr)
 {
     for (int dim = 1; dim <= 2; dim++) {
-        if (!b->ninst[dim]) continue;
+        if (!b->ninst[dim] || (skip && skip[dim])) continue;
         CK(b, launch_step(dim, kind_of(b->prec), b->variant[dim], b->d_descs(), b->d_ctrls(),
                           b->d_blocks(dim), b->nblocks[dim], waves_of(b, dim, {}), b->remap, b->fused,
                           st));
@@ -840,7 +970,10 @@ int enqueue_small(ng_batch* b, int64_t nsteps, hipStream_t st)
     return NG_OK;
 }
 
-bool any_big(const ng_batch* b) { return b->ninst[1] + b->ninst[2] > 0; }
+bool any_big(const ng_batch* b, const bool* skip = nullptr)
+{
+    return (b->ninst[1] > 0 && !(skip && skip[1])) || (b->ninst[2] > 0 && !(skip && skip[2]));
+}
 bool any_small(const ng_batch* b) { return b->nsmall[1] + b->nsmall[2] > 0; }
 
 // Timed variant: the step and finalize kernels (big solves) of every
@@ -930,14 +1063,14 @@ int enqueue_timed(ng_batch* b, int64_t nsteps)
     return NG_OK;
 }
 
-int ensure_graph(ng_batch* b)
+int ensure_graph(ng_batch* b, const bool* skip)
 {
-    if (b->gexec && b->gsteps == b->graph_steps) return NG_OK;
+    if (b->gexec && b->gsteps == b->graph_steps && b->gskips == (skip != nullptr)) return NG_OK;
     drop_graph(b);
     if (!b->cap_stream) CK(b, hipStreamCreateWithFlags(&b->cap_stream, hipStreamNonBlocking));
     CK(b, hipStreamBeginCapture(b->cap_stream, hipStreamCaptureModeThreadLocal));
     int rc = NG_OK;
-    for (int i = 0; i < b->graph_steps && rc == NG_OK; i++) rc = enqueue_one(b, b->cap_stream);
+    for (int i = 0; i < b->graph_steps && rc == NG_OK; i++) rc = enqueue_one(b, b->cap_stream, skip);
     hipGraph_t g = nullptr;
     hipError_t e = hipStreamEndCapture(b->cap_stream, &g);
     if (rc != NG_OK) {
@@ -952,6 +1085,7 @@ int ensure_graph(ng_batch* b)
         return dev_err(b, e, "hipGraphInstantiate");
     }
     b->gsteps = b->graph_steps;
+    b->gskips = skip != nullptr;
     return NG_OK;
 }
 
@@ -963,12 +1097,17 @@ int enqueue_steps(ng_batch* b, int64_t nsteps)
     int rc = rebuild(b);
     if (rc) return rc;
     if (b->timing) return enqueue_timed(b, nsteps);
-    if (!b->res.empty() && nsteps >= kCoopMinSteps) return enqueue_coop(b, nsteps);
+    const bool* skip = nullptr;
+    if (!b->res.empty() && nsteps >= kCoopMinSteps) {
+        rc = enqueue_coop(b, nsteps);
+        if (rc) return rc;
+        skip = b->coop_dim;
+    }
     rc = enqueue_small(b, nsteps, b->stream);
-    if (rc || !any_big(b)) return rc;
+    if (rc || !any_big(b, skip)) return rc;
     int64_t left = nsteps;
     if (left >= b->graph_steps) {
-        rc = ensure_graph(b);
+        rc = ensure_graph(b, skip);
         if (rc) return rc;
         while (left >= b->gsteps) {
             CK(b, hipGraphLaunch(b->gexec, b->stream));
@@ -976,7 +1115,7 @@ int enqueue_steps(ng_batch* b, int64_t nsteps)
         }
     }
     for (int64_t i = 0; i < left; i++) {
-        rc = enqueue_one(b, b->stream);
+        rc = enqueue_one(b, b->stream, skip);
         if (rc) return rc;
     }
     return NG_OK;

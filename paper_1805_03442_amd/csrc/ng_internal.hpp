@@ -147,6 +147,7 @@ struct InstCtrl {
 // so words by step parity suffice.  The step numbers run on from launch to
 // launch (ResSync::base), so nothing is cleared in between.
 constexpr int kCoopFlat = 256;      // workgroups of one solve
+constexpr int kResMaxWgs = 768;     // workgroups of one launch (three per CU)
 constexpr int kCoopMaxWaves = 16;   // waves per workgroup, upper bound
 constexpr int kResEdge = 24;        // words of an edge (three FP64 cells)
 constexpr int kResSlot = 8;         // words from slot to slot, at most

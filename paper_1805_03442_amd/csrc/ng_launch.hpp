@@ -51,6 +51,8 @@ hipError_t launch_resident(int prec, int s, bool lds, const InstDesc* descs, Ins
                            const ResGroup& one, const ResSync& sync, int grid, int waves,
                            size_t lds_bytes, int64_t nsteps, int32_t spin_limit, hipStream_t st);
 
+// Clears the step number, the slots and the edges (bytes: res_space of them).
+hipError_t launch_resident_clear(const ResSync& sync, size_t bytes, hipStream_t st);
 // Folds the records of a cooperative launch into the control blocks of its
 // solves and moves the step number on.
 hipError_t launch_resident_after(const InstDesc* descs, InstCtrl* ctrls, const ResGroup* groups,

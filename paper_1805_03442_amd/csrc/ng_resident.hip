@@ -465,6 +465,21 @@ hipError_t launch_resident(int prec, int s, bool lds, const InstDesc* descs, Ins
     return launch_resident_after(descs, ctrls, groups, ngroups, one, sync.base, nsteps, st);
 }
 
+// (a kernel and not a memset, so that a caller's stream capture can hold it)
+__global__ void resident_clear_kernel(uint64_t* __restrict__ p, size_t words)
+{
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < words;
+         i += (size_t)gridDim.x * blockDim.x)
+        p[i] = 0;
+}
+
+hipError_t launch_resident_clear(const ResSync& sync, size_t bytes, hipStream_t st)
+{
+    hipLaunchKernelGGL(resident_clear_kernel, dim3(64), dim3(256), 0, st, (uint64_t*)sync.base,
+                       bytes / 8);
+    return hipGetLastError();
+}
+
 hipError_t launch_resident_after(const InstDesc* descs, InstCtrl* ctrls, const ResGroup* groups,
                                  int ngroups, const ResGroup& one, uint32_t* base, int64_t nsteps,
                                  hipStream_t st)
