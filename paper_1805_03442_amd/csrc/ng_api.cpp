@@ -94,6 +94,12 @@ constexpr int64_t kResSegs = 4;
 // workgroups (resident_fleet); its header has room for the workgroups of this
 // many full launches.
 constexpr size_t kResLaunches = 4;
+// ... in FP64 while they have at most this many segments: more keep the chip
+// full without it, and its two waves per SIMD then lose to three (us per step,
+// cooperative and one launch per step: 48 solves, 0.58 M cells 29 and 65; 130,
+// 2.0 M 97 and 121; 200, 3.1 M 163 and 160; 280, 5.1 M 316 and 233.  FP32 and
+// mixed: 3.1 M cells 30 and 56, 35 and 69; 5.1 M 51 and 72, 70 and 99).
+constexpr int64_t kResFleetSegs64 = 45000;
 // 2D: rows a wave takes at least.  Us per step with 2, 3 and 4 (FP32 / FP64):
 // 256^2 6.9 / 12.7, 6.8 / 11.2, 7.8 / 12.9; 600^2 9.7 / 18.5, 9.5 / 18.2, 10.5 /
 // 20.9 (2 rows: the launch's records then no longer fit the smallest grids).
@@ -656,10 +662,19 @@ int resident_fleet(ng_batch* b, const std::vector<int>& ids, bool* ok)
 {
     *ok = false;
     const int kind = kind_of(b->prec);
-    const int64_t cap = std::min<int64_t>((int64_t)b->res_nwg, 3LL * b->dev_cus);
     const size_t cell = 4 * real_size(b->prec);
+    const int kern = resident_kernel_of(b->slots[ids[0]].d, b->prec);
+    int per = 0;   // workgroups a CU holds by the kernel's registers
+    CK(b, resident_capacity(kind, kern, false, kResMinWaves, 2 * cell * (2 * kCsphHalo), &per));
+    const int64_t cap = std::min<int64_t>((int64_t)b->res_nwg, (int64_t)std::min(per, 3) * b->dev_cus);
+    if (cap < 1) return NG_OK;
+    int64_t all = 0;
+    for (int i : ids) all += b->slots[i].d.nstrips;
+    if (b->prec == NG_FP64 && all > kResFleetSegs64) return NG_OK;
+    // more solves than workgroups: equal launches
+    const size_t share = (size_t)cdiv((int64_t)ids.size(), cdiv((int64_t)ids.size(), cap));
     for (size_t at = 0; at < ids.size();) {
-        const size_t n = std::min<size_t>(ids.size() - at, (size_t)cap);
+        const size_t n = std::min(ids.size() - at, share);
         int64_t most = 1, w = 0;
         auto segs_of = [&](size_t i) { return (int64_t)b->slots[ids[at + i]].d.nstrips; };
         for (size_t i = 0; i < n; i++) most = std::max(most, segs_of(i));
@@ -678,7 +693,7 @@ int resident_fleet(ng_batch* b, const std::vector<int>& ids, bool* ok)
         const int64_t wgs = wgs_at(lo);
         if (wgs > cap) return NG_OK;
         ResLaunch r;
-        r.s = resident_kernel_of(b->slots[ids[at]].d, b->prec);
+        r.s = kern;
         r.waves = kResMinWaves;
         r.grid = (int)wgs;
         r.ngroups = (int)n;
@@ -1308,6 +1323,8 @@ void fill_desc(InstDesc& d, const ng_gas* gas, const ng_grid* grid, const ng_num
     d.cl_recipe = 0;
     if (prec == NG_FP64) {
         const double e[6] = {gas->tau_rho, gas->tau_T, gas->Q_rho, gas->Q_T, gas->I_rho, gas->I_T};
+        d.pow_forms = 0;
+        for (int q = 0; q < 6; q++) d.pow_forms |= pow_form(e[q]) << (4 * q);
         for (int r = 1; r <= ng::kRecipes64; r++) {
             bool same = true;
             for (int q = 0; q < 6; q++) same = same && 2.0 * e[q] == ng::kRecipe64[r][q];

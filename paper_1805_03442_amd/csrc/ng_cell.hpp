@@ -163,17 +163,19 @@ __device__ __forceinline__ double powh64(double x)
         return __builtin_fma(e, y, y);
     }
 }
-// the same for an exponent known at run time, others by pow.  The exponent is
-// the same for every lane.
-__device__ __forceinline__ double powr64(double x, double a)
+// the same for an exponent a known at run time with its form (pow_form), the
+// same for every lane: one scalar branch
+__device__ __forceinline__ double powr64(double x, int form, double a)
 {
-    if (a == 0.0) return 1.0;
-    if (a == 1.0) return x;
-    if (a == -1.0) return powh64<-2>(x);
-    if (a == 2.0) return x * x;
-    if (a == 0.5) return powh64<1>(x);
-    if (a == -1.5) return powh64<-3>(x);
-    return pow_general(x, a);
+    switch (form) {
+    case 0: return 1.0;
+    case 1: return x;
+    case 2: return powh64<-2>(x);
+    case 3: return x * x;
+    case 4: return powh64<1>(x);
+    case 5: return powh64<-3>(x);
+    default: return pow_general(x, a);
+    }
 }
 
 // tau, Q and I of eq. (6)
@@ -189,12 +191,22 @@ __device__ __forceinline__ Powers64 powers64(const K64& k, double r, double t)
     return {k.tau0 * powh64<e[0]>(r) * powh64<e[1]>(t), k.Q0 * powh64<e[2]>(r) * powh64<e[3]>(t),
             k.I0 * powh64<e[4]>(r) * powh64<e[5]>(t)};
 }
-// the same with the exponents known at run time; out of line, once per library
-__device__ __noinline__ Powers64 powers64_any(const InstDesc* d, double r, double t)
+// the same with the exponents known at run time; out of line, once per library.
+// The descriptor's address and the forms are made scalar again (arguments of a
+// call are not), so that the exponents are scalar loads and their selection
+// scalar branches: compared lane by lane, 36 branches cost more than the pow
+// (1024 cells with one general exponent 7.1 us per step, now 5.3).
+__device__ __noinline__ Powers64 powers64_any(const InstDesc* dv, double r, double t)
 {
-    return {d->tau0 * powr64(r, d->tau_rho) * powr64(t, d->tau_T),
-            d->Q0 * powr64(r, d->Q_rho) * powr64(t, d->Q_T),
-            d->I0 * powr64(r, d->I_rho) * powr64(t, d->I_T)};
+    const uint64_t p = (uint64_t)(uintptr_t)dv;
+    const uint64_t pu = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(p >> 32)) << 32) |
+                        (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)p);
+    typedef const __attribute__((address_space(4))) InstDesc CDesc;
+    const CDesc* d = (const CDesc*)pu;
+    const int f = d->pow_forms;
+    return {d->tau0 * powr64(r, f & 15, d->tau_rho) * powr64(t, (f >> 4) & 15, d->tau_T),
+            d->Q0 * powr64(r, (f >> 8) & 15, d->Q_rho) * powr64(t, (f >> 12) & 15, d->Q_T),
+            d->I0 * powr64(r, (f >> 16) & 15, d->I_rho) * powr64(t, (f >> 20) & 15, d->I_T)};
 }
 
 // closures of eq. (6) at (rho, p), and T (eq. (7)); y = recip64(rho).  The

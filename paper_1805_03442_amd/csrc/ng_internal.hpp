@@ -69,6 +69,13 @@ constexpr int kRecipe64[kRecipes64 + 1][6] = {
     {-2, -3, 0, 0, 0, 0},
 };
 
+// How the FP64 arithmetic takes x^a (powr64): 1, x, 1/x, x^2, x^1/2, x^-3/2, or
+// pow (6).
+constexpr int pow_form(double a)
+{
+    return a == 0.0 ? 0 : a == 1.0 ? 1 : a == -1.0 ? 2 : a == 2.0 ? 3 : a == 0.5 ? 4 : a == -1.5 ? 5 : 6;
+}
+
 // Run-constant description of one solve.
 struct InstDesc {
     int64_t nx, ny, ncell;
@@ -110,7 +117,7 @@ struct InstDesc {
     // > 0 names the compiled recipe whose exponents they are (kRecipeCodes).
     double cl_c[3], cl_a[3], cl_b[3];
     int32_t cl_recipe;        // (FP64 solves: the row of kRecipe64)
-    int32_t pad1;
+    int32_t pow_forms;        // pow_form of the six exponents of eq. (6), four bits each
     // rounded reciprocals of the run's constant denominators (FP64 arithmetic)
     double ih, igm1, iR, irho0, iT0;
 };
@@ -152,6 +159,7 @@ constexpr int kCoopMaxWaves = 16;   // waves per workgroup, upper bound
 constexpr int kResEdge = 24;        // words of an edge (three FP64 cells)
 constexpr int kResSlot = 8;         // words from slot to slot, at most
 constexpr int kResMinWaves = 4;     // the exchange takes three waves
+constexpr int kResEight = 8;        // waves of the FP64 kernels' roomier form
 // LDS a workgroup may take for its cells (160 KiB less the kernel's own)
 constexpr uint64_t kResLdsBytes = 156 * 1024;
 struct ResGroup {

@@ -62,8 +62,10 @@ struct alignas(16) ResCell {
 // 5 and 6 the CSPH-TVD step with the general closures and recipe 1.
 // groups/refs: the launch's solves and the (group, local workgroup) of each
 // workgroup; null: one solve, `one`.
-template <class P, int S, bool InLds>
-__global__ void __launch_bounds__(P::kResThreads) run_resident_kernel(
+// T: largest workgroup.  The FP64 kernels with calls or both HLL sides spill at
+// the 168 registers that twelve waves leave, so they have a form for eight.
+template <class P, int S, bool InLds, int T>
+__global__ void __launch_bounds__(T) run_resident_kernel(
     const InstDesc* __restrict__ descs, const InstCtrl* __restrict__ ctrls,
     const ResGroup* __restrict__ groups, const BlockRef* __restrict__ refs, ResGroup one,
     const uint32_t* __restrict__ base, uint64_t* __restrict__ slots, uint64_t* __restrict__ edges,
@@ -400,30 +402,46 @@ __global__ void __launch_bounds__(256) resident_after_kernel(const InstDesc* __r
 
 // ================================================================ launchers
 
-template <template <int> class Pol, bool InLds>
+template <template <int> class Pol, bool InLds, int T>
 static const void* kernel_of(int s)
 {
     using P = Pol<4>;
     switch (s) {
-    case 0: return (const void*)run_resident_kernel<P, 0, InLds>;
-    case 1: return (const void*)run_resident_kernel<P, 1, InLds>;
-    case 2: return (const void*)run_resident_kernel<P, 2, InLds>;
-    case 4: return (const void*)run_resident_kernel<P, 4, InLds>;
+    case 0: return (const void*)run_resident_kernel<P, 0, InLds, T>;
+    case 4: return (const void*)run_resident_kernel<P, 4, InLds, T>;
     default: break;
     }
+    if constexpr (T == P::kResThreads) {
+        if (s == 1) return (const void*)run_resident_kernel<P, 1, InLds, T>;
+        if (s == 2) return (const void*)run_resident_kernel<P, 2, InLds, T>;
+    }
     if constexpr (std::is_same<typename P::K, K64>::value) {
-        if (s == 3) return (const void*)run_resident_kernel<P, 3, InLds>;
-        if (s == 5) return (const void*)run_resident_kernel<P, 5, InLds>;
-        if (s == 6) return (const void*)run_resident_kernel<P, 6, InLds>;
+        if (s == 5) return (const void*)run_resident_kernel<P, 5, InLds, T>;
+        if constexpr (T == P::kResThreads) {
+            if (s == 3) return (const void*)run_resident_kernel<P, 3, InLds, T>;
+            if (s == 6) return (const void*)run_resident_kernel<P, 6, InLds, T>;
+        }
     }
     return nullptr;
 }
 
-static const void* kernel_of(int prec, int s, bool lds)
+// (FP64, up to eight waves: the form with registers to spare where there is one)
+template <template <int> class Pol>
+static const void* kernel_of(int s, bool lds, int waves)
 {
-    if (prec == 0) return lds ? kernel_of<Plain64, true>(s) : kernel_of<Plain64, false>(s);
-    if (prec == 1) return lds ? kernel_of<Dev32, true>(s) : kernel_of<Dev32, false>(s);
-    if (prec == 2) return lds ? kernel_of<Mix32, true>(s) : kernel_of<Mix32, false>(s);
+    constexpr int T = Pol<4>::kResThreads;
+    if constexpr (std::is_same<typename Pol<4>::K, K64>::value)
+        if (waves <= kResEight && (s == 0 || s == 4 || s == 5))
+            return lds ? kernel_of<Pol, true, kResEight * kWave>(s)
+                       : kernel_of<Pol, false, kResEight * kWave>(s);
+    return lds ? kernel_of<Pol, true, T>(s) : kernel_of<Pol, false, T>(s);
+}
+
+static const void* kernel_of(int prec, int s, bool lds, int waves)
+{
+    if (prec == 0) return kernel_of<Plain64>(s, lds, waves);
+    if (prec == 1) return kernel_of<Dev32>(s, lds, waves);
+    if (prec == 2) return kernel_of<Mix32>(s, lds, waves);
     return nullptr;
 }
 
@@ -436,7 +454,7 @@ int resident_max_waves(int prec)
 hipError_t resident_capacity(int prec, int s, bool lds, int waves, size_t lds_bytes,
                              int* blocks_per_cu)
 {
-    const void* k = kernel_of(prec, s, lds);
+    const void* k = kernel_of(prec, s, lds, waves);
     if (!k || waves < kResMinWaves || waves > resident_max_waves(prec)) return hipErrorInvalidValue;
     hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)kResLdsBytes);
@@ -449,7 +467,7 @@ hipError_t launch_resident(int prec, int s, bool lds, const InstDesc* descs, Ins
                            const ResGroup& one, const ResSync& sync, int grid, int waves,
                            size_t lds_bytes, int64_t nsteps, int32_t spin_limit, hipStream_t st)
 {
-    const void* k = kernel_of(prec, s, lds);
+    const void* k = kernel_of(prec, s, lds, waves);
     if (!k || grid < 1 || grid > sync.nwg || ngroups < 1 || waves < kResMinWaves ||
         waves > resident_max_waves(prec) || nsteps < 1 || nsteps > kCoopMaxSteps ||
         spin_limit < 0 || lds_bytes > kResLdsBytes)
