@@ -100,10 +100,6 @@ constexpr size_t kResLaunches = 4;
 // 2.0 M 97 and 121; 200, 3.1 M 163 and 160; 280, 5.1 M 316 and 233.  FP32 and
 // mixed: 3.1 M cells 30 and 56, 35 and 69; 5.1 M 51 and 72, 70 and 99).
 constexpr int64_t kResFleetSegs64 = 45000;
-// 2D: rows a wave takes at least.  Us per step with 2, 3 and 4 (FP32 / FP64):
-// 256^2 6.9 / 12.7, 6.8 / 11.2, 7.8 / 12.9; 600^2 9.7 / 18.5, 9.5 / 18.2, 10.5 /
-// 20.9 (2 rows: the launch's records then no longer fit the smallest grids).
-constexpr int64_t kRes2Rows = 3;
 // Pinned staging buffers of the initial-state upload (two, used in turn).
 constexpr size_t kStageBytes = size_t(16) << 20;
 // Host threads converting one staging chunk, and the cells each takes at least.
@@ -150,7 +146,7 @@ size_t solve_bytes(const ng_grid* g, int prec)
 // header): what resident_shape takes at most.
 size_t res_wgs_of(const ng_grid* g)
 {
-    if (g->ndim != 1) return (size_t)std::min<int64_t>(partial_cap_of(g), kCoopFlat);
+    if (g->ndim != 1) return (size_t)std::min<int64_t>(cdiv(strips_of(g) * g->ny, kResMinWaves), kCoopFlat);
     return (size_t)std::min<int64_t>(cdiv(strips_of(g), kResSegs), kCoopFlat);
 }
 // The same for a batch, whose slots and tables take at most 1/64 of its arena
@@ -430,6 +426,8 @@ struct ng_batch {
         y.base = (uint32_t*)p;
         y.slots = (uint64_t*)(p + 256);
         y.edges = y.slots + 2 * kResSlot * res_nwg;
+        y.recs = (CoopRec*)(y.edges + 2 * 2 * kResEdge * res_nwg);
+        y.views = (CoopView*)(y.recs + 2 * res_nwg);
         y.nwg = (int32_t)res_nwg;
         return y;
     }
@@ -626,19 +624,24 @@ void resident_shape(const InstDesc& d, int prec, int cus, ResLaunch& r)
                                      resident_max_waves(kind_of(prec)));
 }
 
-// Shape of a 2D solve's cooperative launch: every strip's rows in as many runs
-// of at least kRes2Rows rows as there are waves for, in workgroups of four waves
-// (one per SIMD of a CU) while there are CUs for them, then of more.  rec_bytes:
-// the solve's reduction space, which holds the workgroups' records.
-bool resident_shape2d(const InstDesc& d, int prec, int cus, size_t rec_bytes, ResLaunch& r)
+// Shape of a 2D solve's cooperative launch: one row per wave, or two, when that
+// gives every wave a SIMD of its own (workgroups of four waves); else every
+// strip's rows in as many runs as the largest workgroups have waves for.  A wave
+// needs four rows more than it updates, but the step then lasts as long as its
+// longest run.  Us per step with runs of 1, 2, 3 and 4 rows, FP32 / FP64: 48x40
+// 4.0 / 6.2, 4.7 / 8.1, 5.4 / 10.1, 6.1 / 11.9; 256^2 (five waves in some
+// workgroups at one row) 5.8 / 10.3, 5.4 / 9.1, 5.8 / 11.0, 6.2 / 12.6; 600^2
+// (as many waves as fit below 4) 8.7 / 18.0, the same, the same, 9.8 / 20.9.
+bool resident_shape2d(const InstDesc& d, int prec, int cus, ResLaunch& r)
 {
     const int64_t strips = cdiv(d.nx, kInterior), cap = std::min<int64_t>(cus, kCoopFlat);
     const int64_t maxw = resident2d_max_waves(kind_of(prec));
-    int64_t per = cdiv(d.ny, kRes2Rows);
+    int64_t per = d.ny;
+    if (strips * per > cap * kResMinWaves && strips * cdiv(per, 2) <= cap * kResMinWaves)
+        per = cdiv(per, 2);
     int64_t waves = kResMinWaves;
     if (strips * per > cap * waves) waves = std::min<int64_t>(maxw, cdiv(strips * per, cap));
     if (strips * per > cap * waves) per = cap * waves / strips;
-    while (per > 1 && coop_space((uint64_t)cdiv(strips * per, waves)) > rec_bytes) per--;
     if (per < 1) return false;
     r.dim = 2;
     r.chunks = (int)per;
@@ -708,8 +711,6 @@ int resident_fleet(ng_batch* b, const std::vector<int>& ids, bool* ok)
             g.G = (int)cdiv(segs_of(i), lo);
             g.first = first;
             g.pitch = (int)(cdiv(segs_of(i), g.G) * w + (kWave - w));
-            if (coop_space((uint64_t)g.G) > align_up((size_t)s.partial_cap * sizeof(Partial)))
-                return NG_OK;
             for (int j = 0; j < g.G; j++) b->h_refs.push_back(BlockRef{(int32_t)i, j});
             first += g.G;
             r.lds_bytes = std::max(r.lds_bytes, 2 * cell * (size_t)g.pitch);
@@ -769,19 +770,16 @@ int choose_coop(ng_batch* b)
         for (int dim = 1; dim <= 2; dim++) {
             if (dim == 1 ? !(one && live[1].size() == 1) : !two) continue;
             Slot& s = b->slots[live[dim][0]];
-            const size_t rec = align_up((size_t)s.partial_cap * sizeof(Partial));
             ResLaunch r;
             int per_cu = 0;
             if (dim == 1) {
                 resident_shape(s.d, b->prec, b->dev_cus, r);
                 CK(b, resident_capacity(kind_of(b->prec), r.s, r.lds, r.waves, r.lds_bytes, &per_cu));
             } else {
-                if (!resident_shape2d(s.d, b->prec, b->dev_cus, rec, r)) continue;
+                if (!resident_shape2d(s.d, b->prec, b->dev_cus, r)) continue;
                 CK(b, resident2d_capacity(kind_of(b->prec), r.s, r.grid > 1, r.waves, &per_cu));
             }
-            if ((int64_t)per_cu * b->dev_cus < r.grid || (size_t)r.grid > b->res_nwg ||
-                coop_space((uint64_t)r.grid) > rec)
-                continue;
+            if ((int64_t)per_cu * b->dev_cus < r.grid || (size_t)r.grid > b->res_nwg) continue;
             r.one.inst = live[dim][0];
             s.coop = true;
             b->coop_dim[dim] = true;

@@ -515,10 +515,9 @@ __device__ __noinline__ void source_ghost_at(const InstDesc& d, double t, int g,
 // source budgets of every accepted step folded from the records in workgroup
 // order.  A launch whose wait ran out leaves the solve stopped with
 // kStatusStall.
-__device__ __forceinline__ void coop_fold(const InstDesc& d, InstCtrl& c, int G)
+__device__ __forceinline__ void coop_fold(const InstDesc& d, InstCtrl& c, int G,
+                                          const CoopRec* recs, const CoopView* views, int nwg)
 {
-    const CoopRec* recs = (const CoopRec*)d.partials;
-    const CoopView* views = (const CoopView*)(recs + 2 * (size_t)G);
     __shared__ uint64_t s_key[4];
     __shared__ double sh[4][10];
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -548,7 +547,7 @@ __device__ __forceinline__ void coop_fold(const InstDesc& d, InstCtrl& c, int G)
     double v[10] = {0, 0, 0, 0, 0, 0, 0, 0, INFINITY, INFINITY};
     if (w.nacc > 0) {
         for (int j = t; j < G; j += blockDim.x) {
-            const CoopRec& r = recs[(size_t)p * G + j];
+            const CoopRec& r = recs[(size_t)p * nwg + j];
             for (int q = 0; q < 5; q++) v[q] += r.tot[q];
             v[5] += r.src[0];
             v[6] += r.src[1];

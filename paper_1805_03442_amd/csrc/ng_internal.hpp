@@ -168,17 +168,7 @@ struct ResGroup {
     int32_t first;    // ... from this slot on
     int32_t pitch;    // cells per LDS copy, ghosts included
 };
-struct ResSync {
-    uint32_t* base;     // last step number used
-    uint64_t* slots;    // [step parity][nwg][kResSlot]
-    uint64_t* edges;    // [step parity][nwg][side][kResEdge]
-    int32_t nwg;        // slots there are
-};
-// bytes of the slots and edges of nwg workgroups (after 256 bytes for base)
-constexpr uint64_t res_space(uint64_t nwg) { return 256 + nwg * 2 * 8 * (kResSlot + 2 * kResEdge); }
-
-// Per-workgroup data of a cooperative launch, in the solve's reduction space:
-// records of the workgroup's last two steps (by step parity), written when
+// Per-workgroup data of a cooperative launch: records of the workgroup's last two steps (by step parity), written when
 // the launch ends, and the workgroup's view of the solve's control when it
 // left.
 struct CoopRec {
@@ -194,10 +184,18 @@ struct CoopView {
     int32_t cur, status;
     uint32_t flags, stalled;   // ..., this workgroup's wait ran out
 };
-// bytes of reduction space a cooperative launch of G workgroups uses
-constexpr uint64_t coop_space(uint64_t G)
+struct ResSync {
+    uint32_t* base;     // last step number used
+    uint64_t* slots;    // [step parity][nwg][kResSlot]
+    uint64_t* edges;    // [step parity][nwg][side][kResEdge]
+    CoopRec* recs;      // [step parity][nwg]
+    CoopView* views;    // [nwg]
+    int32_t nwg;        // workgroups there is room for
+};
+// bytes of all that for nwg workgroups (after 256 bytes for base)
+constexpr uint64_t res_space(uint64_t nwg)
 {
-    return G * (2 * sizeof(CoopRec) + sizeof(CoopView));
+    return 256 + nwg * (2 * 8 * (kResSlot + 2 * kResEdge) + 2 * sizeof(CoopRec) + sizeof(CoopView));
 }
 
 // Status of a solve whose cooperative launch ended at a wait that ran out of

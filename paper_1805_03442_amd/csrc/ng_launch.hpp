@@ -56,7 +56,7 @@ hipError_t launch_resident_clear(const ResSync& sync, size_t bytes, hipStream_t 
 // Folds the records of a cooperative launch into the control blocks of its
 // solves and moves the step number on.
 hipError_t launch_resident_after(const InstDesc* descs, InstCtrl* ctrls, const ResGroup* groups,
-                                 int ngroups, const ResGroup& one, uint32_t* base, int64_t nsteps,
+                                 int ngroups, const ResGroup& one, const ResSync& sync, int64_t nsteps,
                                  hipStream_t st);
 // The same for one 2D solve: every strip's rows in `chunks` runs, a wave each.  s: 0..2 periodic HLLC with closure recipe s, 3 HLLC with any
 // ends, 4 the same with recipe 3 (FP64), 5 HLL.

@@ -27,7 +27,7 @@ __device__ __forceinline__ void flux_y(const typename P::K& k, const typename P:
 // One work item of the 2D step: rows [r0, r1) of a strip (60 columns + halo).
 // CL: closure recipe of the FP32 arithmetic (0: general).  Coh: agent-scope
 // state loads and stores (Planes).
-template <class P, int RS, bool BC, int CL = 0, bool Coh = false>
+template <class P, int RS, bool BC, int CL = 0, bool Coh = false, int Ring = 4>
 __device__ __forceinline__ void march2d(const InstDesc& d, const typename P::K& k, int cur,
                                         const double* gsrc, int strip, int r0, int r1, int lane,
                                         Acc<typename P::R>& acc)
@@ -110,19 +110,20 @@ __device__ __forceinline__ void march2d(const InstDesc& d, const typename P::K& 
     //   Np/Nn  north face states of rows i / i+1
     //   Gp/Gn  y-fluxes at faces i-1/2 / i+1/2
     //   Uc/Ux  raw row i+2 (arrived) / row i+3 (in flight)
-    // Policies that keep the raw rows hold four of them (rows i .. i+3) in a
-    // ring U0..U3, so U^n of row i is still in registers at its update;
-    // the others re-read it and use U2/U3 only.
+    // Policies that keep the raw rows hold Ring of them (rows i .. i+Ring-1, the
+    // last Ring - 3 in flight) in U[row - r0 mod Ring], so U^n of row i is still
+    // in registers at its update; the others re-read it and use U[2], U[3] only.
     R WA[NC + 1], WB[NC + 1], DA[NC], DB[NC], HA[NC], HB[NC], XA[NC], XB[NC];
     R NA[NC], NB[NC], GA[NC], GB[NC];
-    St U0[NC], U1[NC], U2[NC], U3[NC];
+    static_assert(Ring == 4 || (Ring == 6 && P::kKeepRows), "the unrolled loops below");
+    St U[Ring][NC];
 
     // prologue: rows r0-2 .. r0+1
     {
         R Wa[NC + 1], Wb[NC + 1], Wc[NC + 1], sy[NC], sx[NC], hb[NC], S[NC];
         St t[NC];
-        St* t0 = P::kKeepRows ? U0 : t;
-        St* t1 = P::kKeepRows ? U1 : t;
+        St* t0 = P::kKeepRows ? U[0] : t;
+        St* t1 = P::kKeepRows ? U[1] : t;
         src.load(boff(r0 - 2), t);
         ghost(r0 - 2, t);
         P::prim(k, t, Wa);
@@ -135,7 +136,11 @@ __device__ __forceinline__ void march2d(const InstDesc& d, const typename P::K& 
         src.load(boff(r0 + 1), t1);
         ghost(r0 + 1, t1);
         P::prim(k, t1, WA);
-        src.load(boff(r0 + 2), U2);
+        src.load(boff(r0 + 2), U[2]);
+        if constexpr (Ring == 6) {
+            src.load(boff(r0 + 3 < r1 + 1 ? r0 + 3 : r1 + 1), U[3]);
+            src.load(boff(r0 + 4 < r1 + 1 ? r0 + 4 : r1 + 1), U[4]);
+        }
         // row r0-1: its north face state
         slopes_x(Wb, sx);
         for (int c = 0; c < NC; c++) sy[c] = minmod(Wb[c] - Wa[c], Wc[c] - Wb[c]);
@@ -168,14 +173,14 @@ __device__ __forceinline__ void march2d(const InstDesc& d, const typename P::K& 
         St Ul[NC];
         St* Un = reread ? Ul : Uk;
         if (early) src.load(boff(i), Ul);
-        // row i+2 has arrived in Uc; put row i+3 in flight.  The load is
-        // issued on every row (on the chunk's last row it fetches row i+2
-        // again, from cache, into the unused buffer): a load on one path only
+        // row i+2 has arrived in Uc; put row i+Ring-1 in flight.  The load is
+        // issued on every row (on the chunk's last rows it fetches row r1+1
+        // again, from cache, into an unused buffer): a load on one path only
         // makes the compiler's wait counts assume the other path, so each row
         // would wait for the loads it has just issued
         ghost(i + 2, Uc);
         P::prim(k, Uc, We);
-        src.load(boff(i + 1 < r1 ? i + 3 : i + 2), Ux);
+        src.load(boff(i + Ring - 1 < r1 + 1 ? i + Ring - 1 : r1 + 1), Ux);
         // predictor of row i+1
         R sy[NC];
         slopes_x(Wd, x1s);
@@ -225,22 +230,36 @@ __device__ __forceinline__ void march2d(const InstDesc& d, const typename P::K& 
     };
 
     int i = r0;
-    if constexpr (P::kKeepRows) {
-        for (; i < r1; i += 4) {
-            row(i, WA, WB, DA, DB, HA, HB, XA, XB, NA, NB, GA, GB, U0, U2, U3);
+    if constexpr (P::kKeepRows && Ring == 6) {
+        for (; i < r1; i += 6) {
+            row(i, WA, WB, DA, DB, HA, HB, XA, XB, NA, NB, GA, GB, U[0], U[2], U[5]);
             if (i + 1 >= r1) break;
-            row(i + 1, WB, WA, DB, DA, HB, HA, XB, XA, NB, NA, GB, GA, U1, U3, U0);
+            row(i + 1, WB, WA, DB, DA, HB, HA, XB, XA, NB, NA, GB, GA, U[1], U[3], U[0]);
             if (i + 2 >= r1) break;
-            row(i + 2, WA, WB, DA, DB, HA, HB, XA, XB, NA, NB, GA, GB, U2, U0, U1);
+            row(i + 2, WA, WB, DA, DB, HA, HB, XA, XB, NA, NB, GA, GB, U[2], U[4], U[1]);
             if (i + 3 >= r1) break;
-            row(i + 3, WB, WA, DB, DA, HB, HA, XB, XA, NB, NA, GB, GA, U3, U1, U2);
+            row(i + 3, WB, WA, DB, DA, HB, HA, XB, XA, NB, NA, GB, GA, U[3], U[5], U[2]);
+            if (i + 4 >= r1) break;
+            row(i + 4, WA, WB, DA, DB, HA, HB, XA, XB, NA, NB, GA, GB, U[4], U[0], U[3]);
+            if (i + 5 >= r1) break;
+            row(i + 5, WB, WA, DB, DA, HB, HA, XB, XA, NB, NA, GB, GA, U[5], U[1], U[4]);
+        }
+    } else if constexpr (P::kKeepRows) {
+        for (; i < r1; i += 4) {
+            row(i, WA, WB, DA, DB, HA, HB, XA, XB, NA, NB, GA, GB, U[0], U[2], U[3]);
+            if (i + 1 >= r1) break;
+            row(i + 1, WB, WA, DB, DA, HB, HA, XB, XA, NB, NA, GB, GA, U[1], U[3], U[0]);
+            if (i + 2 >= r1) break;
+            row(i + 2, WA, WB, DA, DB, HA, HB, XA, XB, NA, NB, GA, GB, U[2], U[0], U[1]);
+            if (i + 3 >= r1) break;
+            row(i + 3, WB, WA, DB, DA, HB, HA, XB, XA, NB, NA, GB, GA, U[3], U[1], U[2]);
         }
     } else {
         for (; i + 1 < r1; i += 2) {
-            row(i, WA, WB, DA, DB, HA, HB, XA, XB, NA, NB, GA, GB, U0, U2, U3);
-            row(i + 1, WB, WA, DB, DA, HB, HA, XB, XA, NB, NA, GB, GA, U0, U3, U2);
+            row(i, WA, WB, DA, DB, HA, HB, XA, XB, NA, NB, GA, GB, U[0], U[2], U[3]);
+            row(i + 1, WB, WA, DB, DA, HB, HA, XB, XA, NB, NA, GB, GA, U[0], U[3], U[2]);
         }
-        if (i < r1) row(i, WA, WB, DA, DB, HA, HB, XA, XB, NA, NB, GA, GB, U0, U2, U3);
+        if (i < r1) row(i, WA, WB, DA, DB, HA, HB, XA, XB, NA, NB, GA, GB, U[0], U[2], U[3]);
     }
 }
 

@@ -69,7 +69,8 @@ __global__ void __launch_bounds__(T) run_resident_kernel(
     const InstDesc* __restrict__ descs, const InstCtrl* __restrict__ ctrls,
     const ResGroup* __restrict__ groups, const BlockRef* __restrict__ refs, ResGroup one,
     const uint32_t* __restrict__ base, uint64_t* __restrict__ slots, uint64_t* __restrict__ edges,
-    int32_t nwg, int64_t nsteps, int32_t spin_limit)
+    CoopRec* __restrict__ recs, CoopView* __restrict__ views, int32_t nwg, int64_t nsteps,
+    int32_t spin_limit)
 {
     using R = typename P::R;
     using St = typename P::St;
@@ -88,8 +89,6 @@ __global__ void __launch_bounds__(T) run_resident_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int nw = blockDim.x >> 6, tid = threadIdx.x, nthr = blockDim.x;
     const uint32_t gen0 = *base;
-    CoopRec* recs = (CoopRec*)d.partials;                // [parity][G]
-    CoopView* views = (CoopView*)(recs + 2 * (size_t)G);
 
     extern __shared__ __align__(16) unsigned char dyn[];
     __shared__ double s_sum[kCoopMaxWaves][10];
@@ -339,7 +338,7 @@ __global__ void __launch_bounds__(T) run_resident_kernel(
     }
     const bool stalled = s_c.stalled != 0;
     auto put_rec = [&](const Acc<R>& a, double b0, double b1, int step) {
-        put_record(a, b0, b1, step, recs + (size_t)(step & 1) * G + b, s_sum, wave, lane, nw);
+        put_record(a, b0, b1, step, recs + (size_t)(step & 1) * nwg + me, s_sum, wave, lane, nw);
     };
     if (st_c >= 0) {
         if (cur_ok) {
@@ -382,7 +381,7 @@ __global__ void __launch_bounds__(T) run_resident_kernel(
     // and its view of the control
     if (tid == 0) {
         if (s_edge_out) s_c.stalled = 1;
-        s_c.view(cur0, views[b]);
+        s_c.view(cur0, views[me]);
     }
 }
 
@@ -392,11 +391,14 @@ __global__ void __launch_bounds__(256) resident_after_kernel(const InstDesc* __r
                                                              InstCtrl* __restrict__ ctrls,
                                                              const ResGroup* __restrict__ groups,
                                                              ResGroup one,
+                                                             const CoopRec* __restrict__ recs,
+                                                             const CoopView* __restrict__ views,
+                                                             int32_t nwg,
                                                              uint32_t* __restrict__ base,
                                                              uint32_t nsteps)
 {
     const ResGroup gr = groups ? groups[blockIdx.x] : one;
-    coop_fold(descs[gr.inst], ctrls[gr.inst], gr.G);
+    coop_fold(descs[gr.inst], ctrls[gr.inst], gr.G, recs + gr.first, views + gr.first, nwg);
     if (blockIdx.x == 0 && threadIdx.x == 0) *base += nsteps + 1u;
 }
 
@@ -474,13 +476,14 @@ hipError_t launch_resident(int prec, int s, bool lds, const InstDesc* descs, Ins
         return hipErrorInvalidValue;
     void* args[] = {(void*)&descs,      (void*)&ctrls,      (void*)&groups,
                     (void*)&refs,       (void*)&one,        (void*)&sync.base,
-                    (void*)&sync.slots, (void*)&sync.edges, (void*)&sync.nwg,
-                    (void*)&nsteps,     (void*)&spin_limit};
+                    (void*)&sync.slots, (void*)&sync.edges, (void*)&sync.recs,
+                    (void*)&sync.views, (void*)&sync.nwg,   (void*)&nsteps,
+                    (void*)&spin_limit};
     hipError_t e = hipLaunchCooperativeKernel(k, dim3((unsigned)grid),
                                               dim3((unsigned)(waves * kWave)), args,
                                               (unsigned)lds_bytes, st);
     if (e != hipSuccess) return e;
-    return launch_resident_after(descs, ctrls, groups, ngroups, one, sync.base, nsteps, st);
+    return launch_resident_after(descs, ctrls, groups, ngroups, one, sync, nsteps, st);
 }
 
 // (a kernel and not a memset, so that a caller's stream capture can hold it)
@@ -499,11 +502,11 @@ hipError_t launch_resident_clear(const ResSync& sync, size_t bytes, hipStream_t 
 }
 
 hipError_t launch_resident_after(const InstDesc* descs, InstCtrl* ctrls, const ResGroup* groups,
-                                 int ngroups, const ResGroup& one, uint32_t* base, int64_t nsteps,
+                                 int ngroups, const ResGroup& one, const ResSync& sync, int64_t nsteps,
                                  hipStream_t st)
 {
     hipLaunchKernelGGL(resident_after_kernel, dim3((unsigned)ngroups), dim3(256), 0, st, descs,
-                       ctrls, groups, one, base, (uint32_t)nsteps);
+                       ctrls, groups, one, sync.recs, sync.views, sync.nwg, sync.base, (uint32_t)nsteps);
     return hipGetLastError();
 }
 
