@@ -306,7 +306,7 @@ const char* ng_last_error(const ng_solver* s);
  * (or, with num->scheme = NG_CSPH_TVD, one CSPH-TVD step of section 2.3) on an
  * FP64 state in caller device memory, calling no hipMalloc, hipFree or
  * other allocating routine.  Its scratch -- the solve's descriptor and control
- * block, the workgroup table and the per-workgroup reduction records -- lives
+ * block and the per-workgroup reduction records -- lives
  * in a static device array of 2 MiB that each GPU the library runs on holds
  * until the process ends; a grid whose launch needs more (about 20000
  * workgroups, e.g. beyond 8192^2 cells in 2D) is refused with NG_ENOMEM.

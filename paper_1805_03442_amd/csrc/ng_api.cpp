@@ -1918,10 +1918,11 @@ int ng_kernel_time(ng_solver* s, double* step_ms, double* finalize_ms, int64_t* 
 // --------------------------------------------- one step without allocation
 
 // The entry point for callers that cannot allocate: one FP64 step from U_in to
-// U_out with the descriptor, control block, workgroup table and reduction
-// records in the library's static scratch (ng_kernels.hip).  The launch shape
-// is the automatic one of a lone solve, so the state equals ng_step's.
+// U_out with the descriptor, control block and reduction records in the
+// library's static scratch (ng_kernels.hip).  A cell's arithmetic does not
+// depend on the launch shape, so the state equals ng_step's.
 static thread_local std::string g_static_err;
+constexpr int64_t kStaticFewItems = 640;
 
 int ng_step_static(const ng_gas* gas, const ng_grid* grid, const ng_numerics* num,
                    const void* U_in, void* U_out, double t, double t_end, void* hip_stream,
@@ -1945,6 +1946,16 @@ int ng_step_static(const ng_gas* gas, const ng_grid* grid, const ng_numerics* nu
     fill_desc(d, gas, grid, num, NG_FP64);
     const int dim = grid->ndim;
     d.rows_per_item = auto_rows(dim, {{d.nx, d.ny}});
+    // one or two rows per item while the grid cannot fill the GPU at four: the
+    // chain of rows is the launch's length (per call: 50^2 cells 26.1 us at
+    // four rows, 21.0 at one; 150^2 27.7 and 24.0; 250^2 32.3, two rows 30.2;
+    // 380x400 no gain; 600^2 one row loses 16 %)
+    if (dim == 2)
+        for (int r = 1; r <= 2; r++)
+            if (items_at(2, d.nx, d.ny, r) <= kStaticFewItems) {
+                d.rows_per_item = r;
+                break;
+            }
     d.nstrips = (int32_t)cdiv(d.nx, dim == 2 ? kInterior : seg_cells(d.scheme));
     d.nchunks = (int32_t)(dim == 2 ? cdiv(d.ny, d.rows_per_item) : cdiv(d.nstrips, d.rows_per_item));
     d.nitems = dim == 2 ? (int64_t)d.nstrips * d.nchunks : (int64_t)d.nchunks;
@@ -1952,12 +1963,17 @@ int ng_step_static(const ng_gas* gas, const ng_grid* grid, const ng_numerics* nu
     d.nblocks = cdiv(d.nitems, d.waves_per_block);
     d.fused = d.nblocks <= kFusedMaxBlocks ? 1 : 0;
     // scratch layout: descriptor, control block, finalize index list,
-    // workgroup table, per-workgroup records
+    // per-workgroup records (behind room for a table of the workgroups, so
+    // that the largest grid is that of the launches that read one)
     const size_t o_ctrl = align_up(sizeof(InstDesc));
     const size_t o_insts = o_ctrl + align_up(sizeof(InstCtrl));
-    const size_t o_blocks = o_insts + kAlign;
-    const size_t o_parts = o_blocks + align_up(sizeof(BlockRef) * (size_t)d.nblocks);
-    const size_t need = o_parts + sizeof(Partial) * (size_t)d.nblocks;
+    const size_t o_parts = o_insts + kAlign + align_up(sizeof(BlockRef) * (size_t)d.nblocks);
+    // the priming pass pays for each workgroup's release and count (380x400
+    // cells per call: 38.7 us at 512 workgroups, 33.2 at 192, 31.6 at 128),
+    // large grids need them for the read (1200x1000: 76.4, 73.0 and 75.2 us)
+    const int64_t nprime = std::min(cdiv(d.ncell, 256),
+                                    std::clamp(cdiv(d.ncell, 4096), (int64_t)128, kStaticPrimeBlocks));
+    const size_t need = o_parts + sizeof(Partial) * (size_t)std::max(d.nblocks, nprime);
     if (need > kStaticScratchBytes) {
         g_static_err = "ng_step_static: the grid needs " + std::to_string(need) +
                        " bytes of scratch (" + std::to_string(d.nblocks) +
@@ -1975,24 +1991,14 @@ int ng_step_static(const ng_gas* gas, const ng_grid* grid, const ng_numerics* nu
     InstDesc* descs = (InstDesc*)sc;
     InstCtrl* ctrls = (InstCtrl*)(sc + o_ctrl);
     int32_t* insts = (int32_t*)(sc + o_insts);
-    BlockRef* blocks = (BlockRef*)(sc + o_blocks);
     d.buf[0] = (uint64_t)(uintptr_t)U_in;
     d.buf[1] = (uint64_t)(uintptr_t)U_out;
     d.partials = (uint64_t)(uintptr_t)(sc + o_parts);
-    InstCtrl c;
-    memset(&c, 0, sizeof(c));
-    c.t = t;
-    c.t_end = t_end > t ? t_end : INFINITY;
-    c.max_steps = 1;
     const int variant = variant_of(d);
     hipStream_t st = (hipStream_t)hip_stream;
-    e = launch_static_setup(d, c, descs, ctrls, insts, blocks, d.nblocks, st);
+    e = launch_static_prime(dim, d, t, t_end > t ? t_end : INFINITY, descs, ctrls, insts, nprime, st);
     if (e == hipSuccess)
-        e = launch_prime(dim, kind_of(NG_FP64), descs, ctrls, nullptr, 0, d.nblocks,
-                         d.waves_per_block, st);
-    if (e == hipSuccess) e = launch_finalize(descs, ctrls, insts, 1, 1, st);
-    if (e == hipSuccess)
-        e = launch_step(dim, kind_of(NG_FP64), variant, descs, ctrls, blocks, d.nblocks,
+        e = launch_step(dim, kind_of(NG_FP64), variant, descs, ctrls, nullptr, d.nblocks,
                         d.waves_per_block, 1, d.fused, st);
     if (e == hipSuccess && !d.fused) e = launch_finalize(descs, ctrls, insts, 1, 0, st);
     if (e != hipSuccess) {

@@ -138,7 +138,7 @@ struct InstCtrl {
     double budget[2];         // sum over steps and cells of the source increments
     double rho_min, p_min, smax;
     uint32_t arrive;          // workgroups of the current step that have finished
-    uint32_t pad;
+    uint32_t primed;          // workgroups of the static priming pass that have finished
     double src_ghost[3][5];   // forced source: full conserved state of the ghosts
                               // x = -h/2, -3h/2, -5h/2 at time t (set with t;
                               // the third for the CSPH-TVD step's particles)

@@ -175,6 +175,17 @@ __device__ void last_block_accept(const InstDesc& d, InstCtrl& c, const StepCtl&
     }
 }
 
+// The workgroup's solve and its number there.  Without a table (the step of
+// ng_step_static) the launch is solve 0's; it then zeroes the counter of the
+// priming pass before it, which that pass left at zero unless overlapping
+// calls raced: such a race does not outlive them.
+__device__ __forceinline__ BlockRef block_ref(const BlockRef* blocks, int64_t bid, InstCtrl* ctrls)
+{
+    if (blocks) return blocks[bid];
+    if (bid == 0 && threadIdx.x == 0) ctrls[0].primed = 0u;
+    return BlockRef{0, (int32_t)bid};
+}
+
 // ================================================================ 2D step
 
 // periodic solves take the plain wrap-around indexing; solves with a wall or
@@ -236,7 +247,7 @@ __global__ void __launch_bounds__(256, P::kMinWaves) step2d_kernel(const InstDes
     using R = typename P::R;
     const int64_t G = gridDim.x;
     const int64_t bid = remap ? xcd_remap(blockIdx.x, G) : (int64_t)blockIdx.x;
-    const BlockRef br = blocks[bid];
+    const BlockRef br = block_ref(blocks, bid, ctrls);
     const InstDesc& d = descs[br.inst];
     const StepCtl sc = read_ctl(ctrls[br.inst]);
     if (!sc.active) return;
@@ -434,7 +445,7 @@ __global__ void __launch_bounds__(256, P::kMinWaves1D) step1d_kernel(const InstD
     using R = typename P::R;
     const int64_t G = gridDim.x;
     const int64_t bid = remap ? xcd_remap(blockIdx.x, G) : (int64_t)blockIdx.x;
-    const BlockRef br = blocks[bid];
+    const BlockRef br = block_ref(blocks, bid, ctrls);
     const InstDesc& d = descs[br.inst];
     const StepCtl sc = read_ctl(ctrls[br.inst]);
     if (!sc.active) return;
@@ -650,8 +661,8 @@ __global__ void __launch_bounds__(512) run_small_kernel(const InstDesc* __restri
 
 // Device memory of the entry point for callers that cannot allocate
 // (ng_step_static): the solve's descriptor and control block, the index list
-// of the finalize kernel, the workgroup table and the per-workgroup reduction
-// records, in one file-scope array of kStaticScratchBytes that each GPU holds
+// of the finalize kernel and the per-workgroup reduction records, in one
+// file-scope array of kStaticScratchBytes that each GPU holds
 // until the process ends.  Host code never uses the array's name as an
 // address: static_scratch() takes each device's own address of it once.
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
@@ -675,29 +686,81 @@ hipError_t static_scratch(void** ptr)
     return hipSuccess;
 }
 
-// Fill the static scratch for one solve: descriptor, control block and index
-// list from the arguments (no host staging), and the workgroup table
-// (workgroup j of the launch is workgroup j of solve 0).
-__global__ void static_setup_kernel(InstDesc d, InstCtrl c, InstDesc* __restrict__ descs,
-                                    InstCtrl* __restrict__ ctrls, int32_t* __restrict__ insts,
-                                    BlockRef* __restrict__ blocks, int64_t nblocks)
+// Priming pass of the entry point that allocates nothing.  The solve's
+// descriptor and control come as arguments and are left in the scratch for the
+// step's launch.  Each thread takes cells a launch apart (a record needs no
+// strips or rows), and the last workgroup folds the records (as
+// last_block_accept, with a counter of its own that it leaves at zero): two
+// launches where setting up, priming, folding, stepping and folding were five.
+// Latency bounds it on small grids, the read of the state on large ones (a call
+// back to back, before and now: 150x150 cells 32.2 and 23.1 us, 380x400 35.4
+// and 31.6, 10^6 cells in 1D 58.0 and 49.7).
+template <class P, int NC>
+__global__ void __launch_bounds__(256) static_prime_kernel(InstDesc d, double t, double t_end,
+                                                           InstDesc* __restrict__ descs,
+                                                           InstCtrl* __restrict__ ctrls,
+                                                           int32_t* __restrict__ insts)
 {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i == 0) {
+    using R = typename P::R;
+    using St = typename P::St;
+    __shared__ int last;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
         descs[0] = d;
-        ctrls[0] = c;
         insts[0] = 0;
     }
-    for (; i < nblocks; i += (int64_t)gridDim.x * blockDim.x) blocks[i] = BlockRef{0, (int32_t)i};
+    const typename P::K k = P::make(d, 0.0);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const St* __restrict__ src = (const St*)d.buf[0];
+    Acc<R> acc;
+    acc_init(acc);
+    const int64_t step = (int64_t)gridDim.x * 256;
+#pragma unroll 2
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < d.ncell; i += step) {
+        St U[NC];
+        R W[NC + 1];
+        load_cell_cached<St, NC>(src, d.ncell, i, U);
+        P::prim(k, U, W);
+        const R s = P::speed(k, W);
+        acc_cell<P, NC>(acc, k, U, W, s, (R)0, (R)0);
+    }
+    acc_finish<P>(acc, k);
+    block_reduce_store(acc, (Partial*)d.partials + blockIdx.x, wave, lane, 4);
+    if (threadIdx.x == 0) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        const uint32_t prev = __hip_atomic_fetch_add(&ctrls[0].primed, 1u, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT);
+        last = prev == gridDim.x - 1;
+    }
+    __syncthreads();
+    if (!last) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    double v[10];
+    uint32_t flags;
+    // descs[0], which workgroup 0 released with its record: a late use of the
+    // argument puts a copy of it into every thread's scratch memory at entry
+    // (380x400 cells: 38 to 61 us per call)
+    fold_partials(descs[0], gridDim.x, v, &flags);
+    if (threadIdx.x == 0) {
+        InstCtrl& c = ctrls[0];
+        c = InstCtrl{};
+        c.t = t;
+        c.t_end = t_end;
+        c.max_steps = 1;
+        accept_step(descs[0], c, read_ctl(c), v, flags, 1);
+    }
 }
 
-hipError_t launch_static_setup(const InstDesc& d, const InstCtrl& c, InstDesc* descs,
-                               InstCtrl* ctrls, int32_t* insts, BlockRef* blocks,
-                               int64_t nblocks, hipStream_t s)
+hipError_t launch_static_prime(int dim, const InstDesc& d, double t, double t_end, InstDesc* descs,
+                               InstCtrl* ctrls, int32_t* insts, int64_t nblocks, hipStream_t s)
 {
-    const int64_t g = nblocks < 256 * 64 ? (nblocks + 255) / 256 : 64;
-    hipLaunchKernelGGL(static_setup_kernel, dim3((unsigned)(g > 0 ? g : 1)), dim3(256), 0, s, d,
-                       c, descs, ctrls, insts, blocks, nblocks);
+    if (nblocks < 1 || nblocks > kStaticPrimeBlocks) return hipErrorInvalidValue;
+    dim3 g((unsigned)nblocks), b(256);
+    if (dim == 2)
+        hipLaunchKernelGGL((static_prime_kernel<Plain64<5>, 5>), g, b, 0, s, d, t, t_end, descs, ctrls,
+                           insts);
+    else
+        hipLaunchKernelGGL((static_prime_kernel<Plain64<4>, 4>), g, b, 0, s, d, t, t_end, descs, ctrls,
+                           insts);
     return hipGetLastError();
 }
 

@@ -14,6 +14,7 @@ namespace ng {
 // variant: 0 for any set of solves; 1 + r when every solve of the launch is
 // periodic with the HLLC flux and closure recipe r (a kernel with that path
 // only); kVariantCsph (dim 1, FP64) when every solve takes the CSPH-TVD step.
+// blocks == nullptr: the launch covers solve 0's workgroups 0..nblocks-1.
 hipError_t launch_step(int dim, int prec, int variant, const InstDesc* descs, InstCtrl* ctrls,
                        const BlockRef* blocks, int64_t nblocks, int waves, int remap, int fused,
                        hipStream_t s, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
@@ -67,14 +68,16 @@ hipError_t launch_resident2d(int prec, int s, const InstDesc* descs, InstCtrl* c
                              int32_t spin_limit, hipStream_t st);
 
 // Static scratch of the entry point that allocates nothing: its device
-// address on the current device (looked up once per device), and the kernel
-// that writes one solve's descriptor, control block, finalize index list and
-// workgroup table into it.
+// address on the current device (looked up once per device), and the priming
+// pass that leaves one solve's descriptor, control block (one step from t, the
+// first dt included)
+// and finalize index list in it; nblocks <= kStaticPrimeBlocks workgroups,
+// each with a record at d.partials.
 constexpr size_t kStaticScratchBytes = size_t(2) << 20;
+constexpr int64_t kStaticPrimeBlocks = 192;
 constexpr int kMaxDevices = 64;
 hipError_t static_scratch(void** ptr);
-hipError_t launch_static_setup(const InstDesc& d, const InstCtrl& c, InstDesc* descs,
-                               InstCtrl* ctrls, int32_t* insts, BlockRef* blocks,
-                               int64_t nblocks, hipStream_t s);
+hipError_t launch_static_prime(int dim, const InstDesc& d, double t, double t_end, InstDesc* descs,
+                               InstCtrl* ctrls, int32_t* insts, int64_t nblocks, hipStream_t s);
 
 }  // namespace ng
