@@ -187,7 +187,8 @@ const char* ng_strerror(int code);
 /* ------------------------------------------------------------ one solve */
 
 /* Device bytes that ng_init_state needs for this grid and precision: two state
- * buffers of (ndim + 3) planes plus per-step reduction space.  Returns NG_EINVAL
+ * buffers of (ndim + 3) planes plus per-step reduction space and the exchange
+ * of the cooperative path (at most 300 KB).  Returns NG_EINVAL
  * for an invalid grid. */
 int ng_state_bytes(const ng_grid* grid, const ng_numerics* num, size_t* bytes);
 
@@ -256,19 +257,23 @@ int ng_set_graph_steps(ng_solver* s, int32_t steps);
  * which one workgroup runs many steps per launch (no launch or host round trip
  * per step); larger ones take one launch per step over the whole GPU.  -1
  * restores the default (4096 cells in FP32, 2048 in FP64), 0 turns the
- * persistent path off.  Both paths give bitwise the same state. */
+ * persistent path off.  Both paths give bitwise the same state.  Solves that
+ * take the cooperative path (ng_set_coop) do not come here. */
 int ng_set_small_limit(ng_solver* s, int64_t max_cells);
 
 /* Cooperative path (the time loop of eq. (15) with the dt of eq. (16) chosen
- * after every step).  A solve that is alone in its object, 1D and of at most
+ * after every step).  A solve that is alone in its object and of at most
  * max_cells cells is advanced by one cooperative launch per call (up to 65536
  * steps each): every step, its workgroups -- all resident together -- update
- * their segments, publish their largest signal speed and failure flags in
- * device memory, and each reads those of all the others and accepts or
+ * their segments (1D: kept in LDS) or rows (2D), publish their largest signal
+ * speed and failure flags in device memory (1D: and their edge cells), and
+ * each reads those of all the others and accepts or
  * rejects the step and takes the next dt alike (a forced source's ghosts
  * follow its own t).  No launch or host round trip per step; the state, t
  * and dt are bitwise those of one launch per step (only the summation order
- * of the FP64 totals differs).
+ * of the FP64 totals differs).  Calls of fewer than three steps launch each
+ * step.  A 2D solve takes the path only while its launch shape, persistent
+ * limit, graph length and acceptance are the defaults and steps are not timed.
  * max_cells: -1 restores the default (4194304), 0 turns the path off (the
  * persistent one-workgroup path or one launch per step take over).
  * spin_limit: polls of memory (about a microsecond each) a workgroup spends
@@ -404,8 +409,12 @@ int ng_batch_set_fused_accept(ng_batch* b, int32_t on);
 /* Persistent-path size limit of a batch (see ng_set_small_limit). */
 int ng_batch_set_small_limit(ng_batch* b, int64_t max_cells);
 
-/* Cooperative path of a batch (see ng_set_coop): taken only while the batch
- * holds exactly one live solve that qualifies. */
+/* Cooperative path of a batch (see ng_set_coop): a batch's only live solve
+ * takes it as a lone solve does; several 1D solves take it side by side, in up
+ * to four cooperative launches per call whose workgroups are dealt by solve
+ * size, while each has at most max_cells cells, in FP64 their segments (60
+ * cells) number at most 45000, and the arena has at least 4 MiB (1/64 of it
+ * holds the exchange). */
 int ng_batch_set_coop(ng_batch* b, int64_t max_cells, int32_t spin_limit);
 
 /* Launch shape of the batched step kernels (see ng_set_launch). */

@@ -66,11 +66,12 @@ constexpr int64_t kFusedMaxBlocks = 256;
 // A batch's only solve, when it has at most this many cells, runs in the
 // cooperative kernels: many steps per launch over many workgroups, with one
 // exchange per step instead of two launches.  2D, us per step with one launch
-// per step and cooperative (FP32; FP64; mixed): 48x40 13 and 6.0, 32 and 10.1, 14
-// and 6.2; 600^2 16.3 and 9.5, 26 and 18.2, 17 and 10.5; 1024^2 27 and 19.1, 58
-// and 44.8, 36 and 22.6; 2048^2 60 and 52, 146 and 141, 98 and 87.  3000^2 is a
-// draw and 4096^2 slower (212 and 226, 532 and 555, 323 and 381): there the waves
-// have work for many times the launch's cost, and plain loads use the L2.
+// per step and cooperative (FP32; FP64; mixed): 48x40 13 and 4.0, 32 and 6.2, 14
+// and 4.5; 600^2 16.4 and 8.9, 26 and 18.5, 17 and 10.3; 1024^2 27 and 18.5, 59
+// and 44.8, 36 and 22.2; 2048^2 60 and 51, 145 and 142, 99 and 88.  3000^2 is a
+// draw (115 and 113, 301 and 293, 184 and 186) and 4096^2 slower (212 and 226, 532
+// and 555, 323 and 381): there the waves have work for many times the launch's
+// cost, and plain loads use the L2.
 constexpr int64_t kCoopCells = int64_t(1) << 22;
 // Calls of fewer steps launch them one by one: a cooperative launch and the fold
 // of its records cost about three steps (one step of 200 to 600^2 cells 47 to 57

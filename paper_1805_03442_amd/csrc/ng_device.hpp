@@ -461,12 +461,6 @@ __device__ __forceinline__ void source_cell(const InstDesc& d, const double* g, 
 }
 
 template <class R, int NC>
-__device__ __forceinline__ void load_cell(const R* __restrict__ base, int64_t ncell, int64_t idx,
-                                          R* U)
-{
-    for (int c = 0; c < NC; c++) U[c] = base[c * ncell + idx];
-}
-template <class R, int NC>
 __device__ __forceinline__ void load_cell_cached(const R* __restrict__ base, int64_t ncell,
                                                  int64_t idx, R* U)
 {

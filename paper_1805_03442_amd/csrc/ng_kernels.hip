@@ -5,7 +5,7 @@
 // Work decomposition.  A wavefront owns a strip of 64 consecutive x-cells: the
 // 60 cells it updates plus 2 halo cells on each side, one cell per lane, so
 // every x-neighbour (slopes, face states, fluxes) is one lane away and moves
-// through ds_bpermute without LDS allocation or barriers.
+// with a DPP lane shift, without LDS or barriers.
 //   2D: a work item is (strip, chunk of rows).  The wave marches up the chunk
 //       one row per iteration, keeping the rows it still needs (primitive
 //       states of three rows, the half-step state and x-slopes of the row being

@@ -22,9 +22,9 @@
 // What it measured (us per step; before: a kernel that kept the state in memory,
 // with agent-scope loads and stores, and met at a barrier of 24-byte messages):
 //   cells            200        1024       16384      2^17       2^20
-//   FP32          2.81 1.35   2.92 2.18  3.27 2.48  5.37 3.68  11.97 9.6
-//   FP64          5.46 1.96   5.60 2.85  5.90 3.27 11.03 5.75  40.2  22.9
-//   CSPH-TVD      6.02 2.1    6.19 3.2   6.67 3.8  12.5  7.4   47.0  27
+//   FP32          2.81 1.35   2.92 2.18  3.27 2.48  5.37 3.68  11.97 8.7
+//   FP64          5.46 1.96   5.60 2.85  5.90 3.27 11.03 5.75  40.2  22.6
+//   CSPH-TVD      6.02 2.1    6.19 3.2   6.67 3.6  12.5  6.6   47.0  27
 // (the FP64 rows with the new divisions too; 2^20 FP64 cells are beyond LDS).
 // What is left at 200 cells is one segment's chain of dependent operations, at
 // 2^20 the vector ALUs (5.7 segments per wave, three waves per SIMD).

@@ -10,8 +10,8 @@
 // workgroup needs none of that (Coh = false).
 //
 // It replaces two launches per step (the step and its acceptance) on grids that
-// do not fill the chip for long: see coop_shape2d in ng_api.cpp for where it is
-// taken and what both cost.
+// do not fill the chip for long: kCoopCells in ng_api.cpp says where the line
+// lies and what both cost.
 //
 // Per-cell arithmetic, t and dt follow the step kernels and the finalize kernel
 // operation for operation, so the state, t and dt are bitwise those of one

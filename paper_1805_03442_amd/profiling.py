@@ -25,6 +25,11 @@ import sys
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 KERNEL_SOURCES = ["paper_1805_03442_amd/csrc/ng_kernels.hip",
+                  "paper_1805_03442_amd/csrc/ng_resident.hip",
+                  "paper_1805_03442_amd/csrc/ng_resident2d.hip",
+                  "paper_1805_03442_amd/csrc/ng_device.hpp",
+                  "paper_1805_03442_amd/csrc/ng_exchange.hpp",
+                  "paper_1805_03442_amd/csrc/ng_march2d.hpp",
                   "paper_1805_03442_amd/csrc/ng_cell.hpp",
                   "paper_1805_03442_amd/csrc/ng_csph.hpp",
                   "paper_1805_03442_amd/csrc/ng_internal.hpp"]
