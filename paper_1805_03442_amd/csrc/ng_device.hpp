@@ -582,10 +582,12 @@ __device__ __forceinline__ void coop_fold(const InstDesc& d, InstCtrl& c, int G,
         c.flags = 0u;
         if (d.bc[0] == kBcSource) source_ghosts(d, c);
     }
+    // a solve that had failed before the launch keeps its status and flags
+    if (c.status != 0) return;
     if (w.status != 0) {
         c.status = w.status;
         c.flags = w.flags;
-    } else if (stall != 0 && c.status == 0) {
+    } else if (stall != 0) {
         c.status = kStatusStall;
     }
 }
