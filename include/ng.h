@@ -280,8 +280,10 @@ int ng_set_small_limit(ng_solver* s, int64_t max_cells);
  * in one barrier wait before it gives up (-1: the default, 1048576); a wait
  * that runs out ends the launch early with every kernel exiting, and the
  * next synchronising call reports NG_ESTALL.  Cooperative launches must be
- * supported by the device (else the other paths run).  Synchronising;
- * NG_EINVAL for values below -1. */
+ * supported by the device (else the other paths run).  A device gives its
+ * cooperative queue to one process at a time: an object whose first cooperative
+ * launch is refused takes the other paths until the next ng_set_coop.
+ * Synchronising; NG_EINVAL for values below -1. */
 int ng_set_coop(ng_solver* s, int64_t max_cells, int32_t spin_limit);
 
 /* Step acceptance inside the step kernel (1, default) or by a separate

@@ -371,6 +371,7 @@ struct ng_batch {
     int64_t small_limit = -1;  // cells; -1: by precision, 0: persistent path off
     int64_t coop_limit = -1;   // cells; -1: kCoopCells, 0: cooperative path off
     int32_t coop_spin = kCoopSpin;
+    bool coop_off = false;     // the runtime refused a cooperative launch
     // the cooperative launches of one call (none: the other paths run)
     std::vector<ResLaunch> res;
     std::vector<ResGroup> h_groups;   // tables of the launches of several solves
@@ -751,7 +752,7 @@ int choose_coop(ng_batch* b)
         live[s.dim].push_back(i);
         if (s.d.ncell > lim) within[s.dim] = false;
     }
-    if (lim == 0 || b->res_nwg == 0) return NG_OK;
+    if (lim == 0 || b->res_nwg == 0 || b->coop_off) return NG_OK;
     const bool two = live[2].size() == 1 && within[2] && b->rows[2] == kDefaultRows2D &&
                      b->waves[2] == kDefaultWaves2D && b->small_limit < 0 &&
                      b->graph_steps == kDefaultGraphSteps && b->fused;
@@ -815,9 +816,13 @@ int choose_coop(ng_batch* b)
 }
 
 // Enqueue the cooperative launches for nsteps steps (each of at most
-// kCoopMaxSteps steps).
-int enqueue_coop(ng_batch* b, int64_t nsteps)
+// kCoopMaxSteps steps).  *ran: false when the runtime refused the first of them
+// and nothing was enqueued -- the device gives its cooperative queue to one
+// process at a time.  The object then keeps to the other paths, whose tables
+// hold the same solves, until the next ng_batch_set_coop.
+int enqueue_coop(ng_batch* b, int64_t nsteps, bool* ran)
 {
+    *ran = false;
     for (int64_t left = nsteps; left > 0;) {
         const int64_t n = std::min<int64_t>(left, kCoopMaxSteps);
         for (const ResLaunch& r : b->res) {
@@ -828,18 +833,27 @@ int enqueue_coop(ng_batch* b, int64_t nsteps)
                 CK(b, launch_resident_clear(b->d_sync(), res_space(b->res_nwg), b->stream));
                 b->res_steps = (uint64_t)n + 1;
             }
-            if (r.dim == 2) {
-                CK(b, launch_resident2d(kind_of(b->prec), r.s, b->d_descs(), b->d_ctrls(),
-                                        r.one.inst, b->d_sync(), r.grid, r.chunks, r.waves, n,
-                                        b->coop_spin, b->stream));
-                continue;
-            }
             const bool many = r.ngroups > 0;
-            CK(b, launch_resident(kind_of(b->prec), r.s, r.lds, b->d_descs(), b->d_ctrls(),
-                                  many ? (const ResGroup*)(b->arena + b->L.groups) + r.group0 : nullptr,
-                                  many ? (const BlockRef*)(b->arena + b->L.refs) + r.ref0 : nullptr,
-                                  many ? r.ngroups : 1, r.one, b->d_sync(), r.grid, r.waves,
-                                  r.lds_bytes, n, b->coop_spin, b->stream));
+            const ResGroup* groups = many ? (const ResGroup*)(b->arena + b->L.groups) + r.group0 : nullptr;
+            const BlockRef* refs = many ? (const BlockRef*)(b->arena + b->L.refs) + r.ref0 : nullptr;
+            const int ngroups = many ? r.ngroups : 1;
+            const hipError_t e =
+                r.dim == 2 ? launch_resident2d(kind_of(b->prec), r.s, b->d_descs(), b->d_ctrls(),
+                                               r.one.inst, b->d_sync(), r.grid, r.chunks, r.waves, n,
+                                               b->coop_spin, b->stream)
+                           : launch_resident(kind_of(b->prec), r.s, r.lds, b->d_descs(), b->d_ctrls(),
+                                             groups, refs, r.one, b->d_sync(), r.grid, r.waves,
+                                             r.lds_bytes, n, b->coop_spin, b->stream);
+            if (e != hipSuccess && !*ran) {
+                (void)hipGetLastError();
+                b->coop_off = true;
+                b->dirty = true;
+                return NG_OK;
+            }
+            if (e != hipSuccess) return dev_err(b, e, "cooperative launch");
+            *ran = true;
+            CK(b, launch_resident_after(b->d_descs(), b->d_ctrls(), groups, ngroups, r.one, b->d_sync(),
+                                        n, b->stream));
         }
         left -= n;
     }
@@ -1004,16 +1018,19 @@ int enqueue_timed(ng_batch* b, int64_t nsteps)
         hipEvent_t e0 = get_event(b, 0), e1 = get_event(b, 1);
         if (!e0 || !e1) return dev_err(b, hipErrorOutOfMemory, "hipEventCreate");
         CK(b, hipEventRecord(e0, b->stream));
-        int rc = enqueue_coop(b, nsteps);
+        bool ran = false;
+        int rc = enqueue_coop(b, nsteps, &ran);
         if (rc) return rc;
-        CK(b, hipEventRecord(e1, b->stream));
-        CK(b, hipStreamSynchronize(b->stream));
-        float ms = 0.f;
-        CK(b, hipEventElapsedTime(&ms, e0, e1));
-        b->t_step_ms = nsteps > 0 ? ms / nsteps : 0.0;
-        b->t_fin_ms = 0.0;
-        b->t_launches = cdiv(nsteps, kCoopMaxSteps);
-        return NG_OK;
+        if (ran) {
+            CK(b, hipEventRecord(e1, b->stream));
+            CK(b, hipStreamSynchronize(b->stream));
+            float ms = 0.f;
+            CK(b, hipEventElapsedTime(&ms, e0, e1));
+            b->t_step_ms = nsteps > 0 ? ms / nsteps : 0.0;
+            b->t_fin_ms = 0.0;
+            b->t_launches = cdiv(nsteps, kCoopMaxSteps);
+            return NG_OK;
+        }
     }
     if (any_small(b)) {
         hipEvent_t e0 = get_event(b, 0), e1 = get_event(b, 1);
@@ -1113,9 +1130,10 @@ int enqueue_steps(ng_batch* b, int64_t nsteps)
     if (b->timing) return enqueue_timed(b, nsteps);
     const bool* skip = nullptr;
     if (!b->res.empty() && nsteps >= kCoopMinSteps) {
-        rc = enqueue_coop(b, nsteps);
+        bool ran = false;
+        rc = enqueue_coop(b, nsteps, &ran);
         if (rc) return rc;
-        skip = b->coop_dim;
+        if (ran) skip = b->coop_dim;
     }
     rc = enqueue_small(b, nsteps, b->stream);
     if (rc || !any_big(b, skip)) return rc;
@@ -2214,6 +2232,7 @@ int ng_batch_set_coop(ng_batch* b, int64_t max_cells, int32_t spin_limit)
     if (!b || max_cells < -1 || spin_limit < -1) return NG_EINVAL;
     b->coop_limit = max_cells;
     b->coop_spin = spin_limit < 0 ? kCoopSpin : spin_limit;
+    b->coop_off = false;
     b->dirty = true;
     return rebuild(b);
 }

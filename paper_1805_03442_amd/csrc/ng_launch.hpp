@@ -40,17 +40,17 @@ hipError_t launch_set_limits(InstCtrl* ctrls, const int32_t* insts, int n, doubl
 // a grid that does not fit).  s: 0..3 HLLC with closure recipe s, 4 HLL, 5 and
 // 6 CSPH-TVD with the general closures and recipe 1 (3, 5, 6: FP64).  lds: the
 // cells stay in LDS (lds_bytes of it), else in the state buffers.  One solve:
-// `one`, groups and refs null; more: ngroups solves in groups, refs[w] the
-// (group, workgroup of it) of workgroup w.  resident_capacity gives the
-// workgroups of that shape a CU holds at once.
+// `one`, groups and refs null; more: in groups, refs[w] the (group, workgroup of
+// it) of workgroup w.  launch_resident_after has to follow.  resident_capacity
+// gives the workgroups of that shape a CU holds at once.
 constexpr int64_t kCoopMaxSteps = int64_t(1) << 16;
 int resident_max_waves(int prec);
 hipError_t resident_capacity(int prec, int s, bool lds, int waves, size_t lds_bytes,
                              int* blocks_per_cu);
 hipError_t launch_resident(int prec, int s, bool lds, const InstDesc* descs, InstCtrl* ctrls,
-                           const ResGroup* groups, const BlockRef* refs, int ngroups,
-                           const ResGroup& one, const ResSync& sync, int grid, int waves,
-                           size_t lds_bytes, int64_t nsteps, int32_t spin_limit, hipStream_t st);
+                           const ResGroup* groups, const BlockRef* refs, const ResGroup& one,
+                           const ResSync& sync, int grid, int waves, size_t lds_bytes,
+                           int64_t nsteps, int32_t spin_limit, hipStream_t st);
 
 // Clears the step number, the slots and the edges (bytes: res_space of them).
 hipError_t launch_resident_clear(const ResSync& sync, size_t bytes, hipStream_t st);
@@ -59,8 +59,9 @@ hipError_t launch_resident_clear(const ResSync& sync, size_t bytes, hipStream_t 
 hipError_t launch_resident_after(const InstDesc* descs, InstCtrl* ctrls, const ResGroup* groups,
                                  int ngroups, const ResGroup& one, const ResSync& sync, int64_t nsteps,
                                  hipStream_t st);
-// The same for one 2D solve: every strip's rows in `chunks` runs, a wave each.  s: 0..2 periodic HLLC with closure recipe s, 3 HLLC with any
-// ends, 4 the same with recipe 3 (FP64), 5 HLL.
+// The cooperative launch of one 2D solve: every strip's rows in `chunks` runs, a
+// wave each.  s: 0..2 periodic HLLC with closure recipe s, 3 HLLC with any ends,
+// 4 the same with recipe 3 (FP64), 5 HLL.
 int resident2d_max_waves(int prec);
 hipError_t resident2d_capacity(int prec, int s, bool coh, int waves, int* blocks_per_cu);
 hipError_t launch_resident2d(int prec, int s, const InstDesc* descs, InstCtrl* ctrls, int inst,

@@ -465,12 +465,12 @@ hipError_t resident_capacity(int prec, int s, bool lds, int waves, size_t lds_by
 }
 
 hipError_t launch_resident(int prec, int s, bool lds, const InstDesc* descs, InstCtrl* ctrls,
-                           const ResGroup* groups, const BlockRef* refs, int ngroups,
-                           const ResGroup& one, const ResSync& sync, int grid, int waves,
-                           size_t lds_bytes, int64_t nsteps, int32_t spin_limit, hipStream_t st)
+                           const ResGroup* groups, const BlockRef* refs, const ResGroup& one,
+                           const ResSync& sync, int grid, int waves, size_t lds_bytes,
+                           int64_t nsteps, int32_t spin_limit, hipStream_t st)
 {
     const void* k = kernel_of(prec, s, lds, waves);
-    if (!k || grid < 1 || grid > sync.nwg || ngroups < 1 || waves < kResMinWaves ||
+    if (!k || grid < 1 || grid > sync.nwg || waves < kResMinWaves ||
         waves > resident_max_waves(prec) || nsteps < 1 || nsteps > kCoopMaxSteps ||
         spin_limit < 0 || lds_bytes > kResLdsBytes)
         return hipErrorInvalidValue;
@@ -479,11 +479,8 @@ hipError_t launch_resident(int prec, int s, bool lds, const InstDesc* descs, Ins
                     (void*)&sync.slots, (void*)&sync.edges, (void*)&sync.recs,
                     (void*)&sync.views, (void*)&sync.nwg,   (void*)&nsteps,
                     (void*)&spin_limit};
-    hipError_t e = hipLaunchCooperativeKernel(k, dim3((unsigned)grid),
-                                              dim3((unsigned)(waves * kWave)), args,
-                                              (unsigned)lds_bytes, st);
-    if (e != hipSuccess) return e;
-    return launch_resident_after(descs, ctrls, groups, ngroups, one, sync, nsteps, st);
+    return hipLaunchCooperativeKernel(k, dim3((unsigned)grid), dim3((unsigned)(waves * kWave)), args,
+                                      (unsigned)lds_bytes, st);
 }
 
 // (a kernel and not a memset, so that a caller's stream capture can hold it)
@@ -505,6 +502,7 @@ hipError_t launch_resident_after(const InstDesc* descs, InstCtrl* ctrls, const R
                                  int ngroups, const ResGroup& one, const ResSync& sync, int64_t nsteps,
                                  hipStream_t st)
 {
+    if (ngroups < 1) return hipErrorInvalidValue;
     hipLaunchKernelGGL(resident_after_kernel, dim3((unsigned)ngroups), dim3(256), 0, st, descs,
                        ctrls, groups, one, sync.recs, sync.views, sync.nwg, sync.base, (uint32_t)nsteps);
     return hipGetLastError();

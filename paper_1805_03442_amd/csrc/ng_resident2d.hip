@@ -206,11 +206,8 @@ hipError_t launch_resident2d(int prec, int s, const InstDesc* descs, InstCtrl* c
                     (void*)&chunks,    (void*)&sync.base,  (void*)&sync.slots,
                     (void*)&sync.recs, (void*)&sync.views, (void*)&sync.nwg,
                     (void*)&nsteps,    (void*)&spin_limit};
-    hipError_t e = hipLaunchCooperativeKernel(k, dim3((unsigned)grid),
-                                              dim3((unsigned)(waves * kWave)), args, 0, st);
-    if (e != hipSuccess) return e;
-    ResGroup one{inst, grid, 0, 0};
-    return launch_resident_after(descs, ctrls, nullptr, 1, one, sync, nsteps, st);
+    return hipLaunchCooperativeKernel(k, dim3((unsigned)grid), dim3((unsigned)(waves * kWave)), args,
+                                      0, st);
 }
 
 }  // namespace ng
