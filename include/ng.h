@@ -54,8 +54,9 @@ extern "C" {
 #define NG_EDEVICE (-4) /* a HIP runtime call failed                           */
 #define NG_EFULL (-5)   /* batch: no free slot or no room in the arena         */
 #define NG_ESTALL (-6)  /* a cooperative launch's grid-barrier wait ran out of
-                           polls (see ng_set_coop); the solve keeps its last
-                           accepted step and stops, like NG_EPHYS              */
+                           polls and the solve could not go on otherwise (see
+                           ng_set_coop); it keeps its last accepted step and
+                           stops, like NG_EPHYS                                */
 
 /* ------------------------------------------------------- enumerated options */
 #define NG_BC_PERIODIC 0 /* wrap-around ghost cells                             */
@@ -277,9 +278,14 @@ int ng_set_small_limit(ng_solver* s, int64_t max_cells);
  * max_cells: -1 restores the default (4194304), 0 turns the path off (the
  * persistent one-workgroup path or one launch per step take over).
  * spin_limit: polls of memory (about a microsecond each) a workgroup spends
- * in one barrier wait before it gives up (-1: the default, 1048576); a wait
- * that runs out ends the launch early with every kernel exiting, and the
- * next synchronising call reports NG_ESTALL.  Cooperative launches must be
+ * in one barrier wait before it gives up (-1: the default, 1048576).  A wait
+ * that runs out (the workgroups were kept off the GPU by a long kernel of
+ * another stream or process) ends the launch early with every kernel exiting.
+ * The next call that reads diagnostics, a state or the finished solves then
+ * runs the missing steps on the other paths before it returns, and the object
+ * keeps to those until the next ng_set_coop.  Only with a limit of 0, or once
+ * steps were captured into a caller's graph (whose replays are not counted),
+ * does that call report NG_ESTALL instead.  Cooperative launches must be
  * supported by the device (else the other paths run).  A device gives its
  * cooperative queue to one process at a time: an object whose first cooperative
  * launch is refused takes the other paths until the next ng_set_coop.

@@ -334,6 +334,9 @@ struct Slot {
     bool small = false;     // advanced by the persistent one-workgroup kernel
     bool coop = false;      // advanced by the cooperative kernel
     bool reported = false;
+    int64_t owed = 0;       // steps enqueued since the control blocks were last read,
+    int64_t seen = 0;       // the solve's steps then
+    bool stalled = false;   // stopped for good by a launch that stalled
 };
 
 // One cooperative launch: its solve, kernel and shape (launch_resident,
@@ -371,7 +374,8 @@ struct ng_batch {
     int64_t small_limit = -1;  // cells; -1: by precision, 0: persistent path off
     int64_t coop_limit = -1;   // cells; -1: kCoopCells, 0: cooperative path off
     int32_t coop_spin = kCoopSpin;
-    bool coop_off = false;     // the runtime refused a cooperative launch
+    bool coop_off = false;     // the runtime refused a cooperative launch, or one stalled
+    bool captured = false;     // steps went into a caller's graph, which may replay them
     // the cooperative launches of one call (none: the other paths run)
     std::vector<ResLaunch> res;
     std::vector<ResGroup> h_groups;   // tables of the launches of several solves
@@ -393,8 +397,10 @@ struct ng_batch {
     int gsteps = 0;
     bool gskips = false;       // captured without the cooperative dims
     int graph_steps = kDefaultGraphSteps;
-    // pinned read-back of the control blocks
+    // pinned read-back of the control blocks, and of the status of a solve that
+    // is read out
     InstCtrl* h_ctrls = nullptr;
+    int32_t* h_status = nullptr;
     // initial-state uploads run on a second stream, so that admitting a solve
     // overlaps the steps in flight: chunks are converted into two pinned
     // staging buffers in turn; descriptor and control block go through pinned
@@ -1120,13 +1126,12 @@ int ensure_graph(ng_batch* b, const bool* skip)
     return NG_OK;
 }
 
-// Enqueue nsteps steps: the cooperative solve in cooperative launches; else
-// the small solves in one persistent launch, the big ones as whole captured
-// graphs, then single launches for the rest.
-int enqueue_steps(ng_batch* b, int64_t nsteps)
+// Enqueue nsteps steps by the planned paths: the cooperative solves in
+// cooperative launches; else the small solves in one persistent launch, the big
+// ones as whole captured graphs, then single launches for the rest.
+int enqueue_planned(ng_batch* b, int64_t nsteps)
 {
-    int rc = rebuild(b);
-    if (rc) return rc;
+    int rc = NG_OK;
     if (b->timing) return enqueue_timed(b, nsteps);
     const bool* skip = nullptr;
     if (!b->res.empty() && nsteps >= kCoopMinSteps) {
@@ -1153,11 +1158,105 @@ int enqueue_steps(ng_batch* b, int64_t nsteps)
     return NG_OK;
 }
 
-int read_ctrls(ng_batch* b)
+// The stream is being captured into a caller's graph.
+bool capturing(const ng_batch* b)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (!b->stream) return false;   // the default stream cannot be
+    if (hipStreamIsCapturing(b->stream, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return st != hipStreamCaptureStatusNone;
+}
+
+// Enqueue nsteps steps of every live solve.
+int enqueue_steps(ng_batch* b, int64_t nsteps)
+{
+    int rc = rebuild(b);
+    if (rc) return rc;
+    if (capturing(b))
+        b->captured = true;
+    else
+        for (Slot& s : b->slots)
+            if (s.live) s.owed = s.owed > INT64_MAX - nsteps ? INT64_MAX : s.owed + nsteps;
+    return enqueue_planned(b, nsteps);
+}
+
+int fetch_ctrls(ng_batch* b)
 {
     CK(b, hipMemcpyAsync(b->h_ctrls, b->d_ctrls(), sizeof(InstCtrl) * b->capacity,
                          hipMemcpyDeviceToHost, b->stream));
     CK(b, hipStreamSynchronize(b->stream));
+    return NG_OK;
+}
+
+// A cooperative launch whose workgroups were kept off the GPU (by a kernel of
+// another stream or process that held CUs for about a second) has ended early.
+// Its solves have kept their last accepted step, so the steps they were asked
+// for since are run on the other paths, which need no workgroups to be resident
+// together, and later calls take those too.  Not so with a spin limit of 0, which
+// asks for the stall, or when a caller's graph may have replayed steps that
+// nothing here counted: then the solves stay stopped (NG_ESTALL).
+bool resumes(const ng_batch* b) { return b->coop_spin > 0 && !b->captured; }
+
+// Nothing is owed any more at the control blocks just read.
+void settle(ng_batch* b)
+{
+    for (int i = 0; i < b->capacity; i++) {
+        b->slots[i].owed = 0;
+        b->slots[i].seen = b->h_ctrls[i].steps;
+    }
+}
+
+// (the stream is idle, h_ctrls has just been fetched)
+int resume(ng_batch* b)
+{
+    std::vector<int64_t> limit(b->capacity);
+    int64_t most = 0;
+    for (int i = 0; i < b->capacity; i++) {
+        Slot& s = b->slots[i];
+        if (!s.live) continue;
+        InstCtrl& c = b->h_ctrls[i];
+        limit[i] = c.max_steps;
+        int64_t more = 0;   // the others wait
+        if (c.status == kStatusStall && !s.stalled) {
+            c.status = 0;
+            more = std::max<int64_t>(0, s.owed - (c.steps - s.seen));
+            most = std::max(most, more);
+        }
+        if (more < limit[i] - c.steps) c.max_steps = c.steps + more;
+    }
+    auto put = [&]() -> int {
+        CK(b, hipMemcpyAsync(b->d_ctrls(), b->h_ctrls, sizeof(InstCtrl) * b->capacity,
+                             hipMemcpyHostToDevice, b->stream));
+        CK(b, hipStreamSynchronize(b->stream));
+        return NG_OK;
+    };
+    b->coop_off = true;
+    b->dirty = true;
+    int rc = put();
+    if (!rc) rc = rebuild(b);
+    if (!rc) rc = enqueue_planned(b, most);
+    if (!rc) rc = fetch_ctrls(b);
+    if (rc) return rc;
+    for (int i = 0; i < b->capacity; i++)
+        if (b->slots[i].live) b->h_ctrls[i].max_steps = limit[i];
+    settle(b);
+    return put();
+}
+
+int read_ctrls(ng_batch* b)
+{
+    int rc = fetch_ctrls(b);
+    if (rc) return rc;
+    for (int i = 0; i < b->capacity; i++) {
+        Slot& s = b->slots[i];
+        if (!s.live || s.stalled || b->h_ctrls[i].status != kStatusStall) continue;
+        if (resumes(b)) return resume(b);
+        s.stalled = true;
+    }
+    settle(b);
     return NG_OK;
 }
 
@@ -1200,7 +1299,8 @@ int batch_new(int32_t capacity, int32_t precision, void* dev_buf, size_t dev_byt
     b->res_nwg = nwg;
     b->slots.resize(capacity);
     if (dev_bytes > L.heap) b->free_list[L.heap] = dev_bytes - L.heap;
-    hipError_t e = hipHostMalloc((void**)&b->h_ctrls, sizeof(InstCtrl) * capacity, 0);
+    hipError_t e = hipHostMalloc((void**)&b->h_ctrls, sizeof(InstCtrl) * capacity + sizeof(int32_t), 0);
+    if (e == hipSuccess) b->h_status = (int32_t*)(b->h_ctrls + capacity);
     if (e == hipSuccess) e = hipHostMalloc((void**)&b->h_desc_up, sizeof(InstDesc) * capacity, 0);
     if (e == hipSuccess) e = hipHostMalloc((void**)&b->h_ctrl_up, sizeof(InstCtrl) * capacity, 0);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&b->up_stream, hipStreamNonBlocking);
@@ -1653,12 +1753,14 @@ int read_planes(ng_batch* b, int slot, double* const* planes, bool prim)
         return NG_EDEVICE;
     }
     // (both buffers are idle once the last uploads have left them; the event of
-    // a buffer then marks the kernel that fills it)
+    // a buffer then marks the kernel that fills it; the first leaves the solve's
+    // status too)
     auto fill = [&](int k, int64_t i0) -> hipError_t {
         hipError_t e = hipEventSynchronize(b->ev_stage[k]);
         if (e == hipSuccess)
             e = launch_readout(s.dim, kind_of(b->prec), b->d_descs(), b->d_ctrls(), slot, i0,
-                               std::min(per, n - i0), prim ? 1 : 0, (double*)b->stage[k], b->stream);
+                               std::min(per, n - i0), prim ? 1 : 0, (double*)b->stage[k],
+                               i0 ? nullptr : b->h_status, b->stream);
         if (e == hipSuccess) e = hipEventRecord(b->ev_stage[k], b->stream);
         return e;
     };
@@ -1667,6 +1769,11 @@ int read_planes(ng_batch* b, int slot, double* const* planes, bool prim)
     for (int64_t i0 = 0; i0 < n; i0 += per, k ^= 1) {
         if (i0 + per < n) CK(b, fill(k ^ 1, i0 + per));
         CK(b, hipEventSynchronize(b->ev_stage[k]));
+        if (i0 == 0 && *(volatile int32_t*)b->h_status == kStatusStall && !s.stalled &&
+            resumes(b)) {
+            int rc = read_ctrls(b);
+            return rc ? rc : read_planes(b, slot, planes, prim);
+        }
         unstage((const double*)b->stage[k], std::min(per, n - i0), nc, planes, i0);
     }
     return NG_OK;

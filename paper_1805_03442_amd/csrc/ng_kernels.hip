@@ -540,14 +540,16 @@ __global__ void __launch_bounds__(256) prime_kernel(const InstDesc* __restrict__
 // at out (pinned host memory: the kernel's stores cross the bus themselves):
 // conserved, or primitive by eq. (5).  The reference of a deviation state is
 // added back and its energy slot made E again; every operation is one IEEE
-// operation in a fixed order.
+// operation in a fixed order.  status (null: none): receives the solve's.
 template <class St, int NC, bool Split>
 __global__ void __launch_bounds__(256) readout_kernel(const InstDesc* __restrict__ descs,
                                                       const InstCtrl* __restrict__ ctrls, int inst,
                                                       int64_t i0, int64_t m, int prim,
-                                                      double* __restrict__ out)
+                                                      double* __restrict__ out,
+                                                      int32_t* __restrict__ status)
 {
     const InstDesc& d = descs[inst];
+    if (status && blockIdx.x == 0 && threadIdx.x == 0) *status = ctrls[inst].status;
     const St* __restrict__ src = (const St*)d.buf[ctrls[inst].cur];
     constexpr int iE = NC == 5 ? 3 : 2, iV = NC - 1;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m;
@@ -893,13 +895,14 @@ hipError_t launch_small(int dim, int prec, const InstDesc* descs, InstCtrl* ctrl
 }
 
 hipError_t launch_readout(int dim, int prec, const InstDesc* descs, const InstCtrl* ctrls, int inst,
-                          int64_t i0, int64_t m, int prim, double* out, hipStream_t s)
+                          int64_t i0, int64_t m, int prim, double* out, int32_t* status,
+                          hipStream_t s)
 {
     if (m <= 0) return hipErrorInvalidValue;
     const int64_t g = (m + 255) / 256;
     dim3 gr((unsigned)(g < 1024 ? g : 1024)), b(256);
     auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, gr, b, 0, s, descs, ctrls, inst, i0, m, prim, out);
+        hipLaunchKernelGGL(kernel, gr, b, 0, s, descs, ctrls, inst, i0, m, prim, out, status);
     };
     if (dim == 2) {
         if (prec == 0) go(readout_kernel<double, 5, false>);

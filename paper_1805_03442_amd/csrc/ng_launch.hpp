@@ -29,9 +29,11 @@ hipError_t launch_finalize(const InstDesc* descs, InstCtrl* ctrls, const int32_t
 hipError_t launch_small(int dim, int prec, const InstDesc* descs, InstCtrl* ctrls,
                         const int32_t* insts, int n, int waves, int64_t nsteps, hipStream_t s);
 // Cells [i0, i0 + m) of a solve's current state as FP64 planes of m values at
-// out (memory the device can write), conserved or primitive.
+// out (memory the device can write), conserved or primitive; status (may be
+// null, likewise) receives the solve's status.
 hipError_t launch_readout(int dim, int prec, const InstDesc* descs, const InstCtrl* ctrls, int inst,
-                          int64_t i0, int64_t m, int prim, double* out, hipStream_t s);
+                          int64_t i0, int64_t m, int prim, double* out, int32_t* status,
+                          hipStream_t s);
 hipError_t launch_set_limits(InstCtrl* ctrls, const int32_t* insts, int n, double t_end,
                              int64_t max_steps_from_now, hipStream_t s);
 
