@@ -347,6 +347,7 @@ struct ResLaunch {
     int s = 0;
     bool lds = false;
     int grid = 0, waves = 0;
+    int64_t rounds = 0;     // segments (1D) or rows (2D) a wave takes per step, at most
     size_t lds_bytes = 0;
     ResGroup one{};
     int ngroups = 0;        // several solves: their groups and workgroups from
@@ -608,17 +609,17 @@ int resident_kernel_of(const InstDesc& d, int prec)
     return prec != NG_FP64 && d.any_bc ? 0 : d.cl_recipe;
 }
 
-// Shape of a solve's cooperative launch: its workgroups, the waves of each (a
-// wave per segment while there are enough, at least kResMinWaves), and where
-// the cells stay.
-void resident_shape(const InstDesc& d, int prec, int cus, ResLaunch& r)
+// Shape of a solve's cooperative launch on at most `cap` workgroups: its
+// workgroups, the waves of each (a wave per segment while there are enough, at
+// least kResMinWaves), and where the cells stay.
+void resident_shape(const InstDesc& d, int prec, int64_t cap, ResLaunch& r)
 {
     const int64_t w = seg_cells(d.scheme), halo = (kWave - w) / 2;
     const int64_t segs = cdiv(d.nx, w);
-    const int64_t cap = std::min<int64_t>(cus, kCoopFlat);
     const int64_t solo = prec == NG_FP64 ? kResSolo64 : kResSolo32;
     const int64_t G = segs <= solo ? 1 : std::min<int64_t>(cdiv(segs, kResSegs), cap);
     const int64_t most = cdiv(segs, G);   // segments of the largest share
+    r.rounds = cdiv(most, resident_max_waves(kind_of(prec)));
     const size_t cell = 4 * real_size(prec);
     r.s = resident_kernel_of(d, prec);
     r.one.G = (int32_t)G;
@@ -632,7 +633,7 @@ void resident_shape(const InstDesc& d, int prec, int cus, ResLaunch& r)
                                      resident_max_waves(kind_of(prec)));
 }
 
-// Shape of a 2D solve's cooperative launch: one row per wave, or two, when that
+// Shape of a 2D solve's cooperative launch on at most `cap` workgroups: one row per wave, or two, when that
 // gives every wave a SIMD of its own (workgroups of four waves); else every
 // strip's rows in as many runs as the largest workgroups have waves for.  A wave
 // needs four rows more than it updates, but the step then lasts as long as its
@@ -640,9 +641,9 @@ void resident_shape(const InstDesc& d, int prec, int cus, ResLaunch& r)
 // 4.0 / 6.2, 4.7 / 8.1, 5.4 / 10.1, 6.1 / 11.9; 256^2 (five waves in some
 // workgroups at one row) 5.8 / 10.3, 5.4 / 9.1, 5.8 / 11.0, 6.2 / 12.6; 600^2
 // (as many waves as fit below 4) 8.7 / 18.0, the same, the same, 9.8 / 20.9.
-bool resident_shape2d(const InstDesc& d, int prec, int cus, ResLaunch& r)
+bool resident_shape2d(const InstDesc& d, int prec, int64_t cap, ResLaunch& r)
 {
-    const int64_t strips = cdiv(d.nx, kInterior), cap = std::min<int64_t>(cus, kCoopFlat);
+    const int64_t strips = cdiv(d.nx, kInterior);
     const int64_t maxw = resident2d_max_waves(kind_of(prec));
     int64_t per = d.ny;
     if (strips * per > cap * kResMinWaves && strips * cdiv(per, 2) <= cap * kResMinWaves)
@@ -656,6 +657,7 @@ bool resident_shape2d(const InstDesc& d, int prec, int cus, ResLaunch& r)
     r.waves = (int)waves;
     r.grid = (int)cdiv(strips * per, waves);
     r.one.G = r.grid;
+    r.rounds = cdiv(d.ny, per);
     r.s = d.riemann == NG_HLL ? 5
           : d.any_bc          ? (prec == NG_FP64 && d.cl_recipe == 3 ? 4 : 3)
                               : (d.cl_recipe <= 2 ? d.cl_recipe : 0);
@@ -778,16 +780,24 @@ int choose_coop(ng_batch* b)
         for (int dim = 1; dim <= 2; dim++) {
             if (dim == 1 ? !(one && live[1].size() == 1) : !two) continue;
             Slot& s = b->slots[live[dim][0]];
-            ResLaunch r;
+            // on as many workgroups as the exchange has room for, while that at
+            // most doubles the work of a wave (a few units more cost less than
+            // the launches of the other paths)
+            const int64_t all = std::min<int64_t>(b->dev_cus, kCoopFlat);
+            const int64_t cap = std::min<int64_t>(all, (int64_t)b->res_nwg);
+            ResLaunch r, full;
             int per_cu = 0;
             if (dim == 1) {
-                resident_shape(s.d, b->prec, b->dev_cus, r);
+                resident_shape(s.d, b->prec, all, full);
+                resident_shape(s.d, b->prec, cap, r);
                 CK(b, resident_capacity(kind_of(b->prec), r.s, r.lds, r.waves, r.lds_bytes, &per_cu));
             } else {
-                if (!resident_shape2d(s.d, b->prec, b->dev_cus, r)) continue;
+                if (!resident_shape2d(s.d, b->prec, all, full) ||
+                    !resident_shape2d(s.d, b->prec, cap, r))
+                    continue;
                 CK(b, resident2d_capacity(kind_of(b->prec), r.s, r.grid > 1, r.waves, &per_cu));
             }
-            if ((int64_t)per_cu * b->dev_cus < r.grid || (size_t)r.grid > b->res_nwg) continue;
+            if ((int64_t)per_cu * b->dev_cus < r.grid || r.rounds > 2 * full.rounds + 2) continue;
             r.one.inst = live[dim][0];
             s.coop = true;
             b->coop_dim[dim] = true;
