@@ -92,8 +92,8 @@ constexpr int64_t kResSolo64 = 4;
 constexpr int64_t kResSolo32 = 8;
 constexpr int64_t kResSegs = 4;
 // A batch's 1D solves run side by side in cooperative launches of four-wave
-// workgroups (resident_fleet); its header has room for the workgroups of this
-// many full launches.
+// workgroups (resident_fleet), which together have at most this many times the
+// workgroups of one launch.
 constexpr size_t kResLaunches = 4;
 // ... in FP64 while they have at most this many segments: more keep the chip
 // full without it, and its two waves per SIMD then lose to three (us per step,
@@ -150,18 +150,28 @@ size_t res_wgs_of(const ng_grid* g)
     if (g->ndim != 1) return (size_t)std::min<int64_t>(cdiv(strips_of(g) * g->ny, kResMinWaves), kCoopFlat);
     return (size_t)std::min<int64_t>(cdiv(strips_of(g), kResSegs), kCoopFlat);
 }
-// The same for a batch, whose slots and tables take at most 1/64 of its arena
-// (none in an arena below 4 MB)
-size_t res_wgs_of(size_t arena_bytes)
-{
-    const size_t n = std::min<size_t>(arena_bytes / 64 / res_space(1), kResMaxWgs);
-    return n < 64 ? 0 : n;
-}
 // entries of a batch's workgroup table for its cooperative launches
 size_t res_refs_of(int capacity, size_t nwg) { return capacity > 1 ? kResLaunches * nwg : 0; }
+// bytes of a batch's exchange of nwg workgroups with the tables of its launches
+size_t exchange_bytes(int capacity, size_t nwg)
+{
+    return align_up(res_space(nwg)) + (capacity > 1 ? align_up(sizeof(ResGroup) * capacity) : 0) +
+           align_up(sizeof(BlockRef) * res_refs_of(capacity, nwg));
+}
+// most workgroups whose exchange fits in `bytes`, up to `most`
+size_t exchange_fits(int capacity, size_t bytes, size_t most)
+{
+    size_t lo = 0, hi = most;
+    while (lo < hi) {
+        const size_t mid = (lo + hi + 1) / 2;
+        if (exchange_bytes(capacity, mid) <= bytes) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
 
 struct Layout {
-    size_t descs, ctrls, insts, iota, res, groups, refs, blocks1, blocks2, heap;
+    size_t descs, ctrls, insts, iota, res, blocks1, blocks2, heap;
 };
 
 Layout header_layout(int capacity, size_t tcap1, size_t tcap2, size_t nwg)
@@ -178,10 +188,6 @@ Layout header_layout(int capacity, size_t tcap1, size_t tcap2, size_t nwg)
     o += align_up(sizeof(int32_t) * capacity);
     L.res = o;
     if (nwg) o += align_up(res_space(nwg));
-    L.groups = o;
-    if (nwg && capacity > 1) o += align_up(sizeof(ResGroup) * capacity);
-    L.refs = o;
-    if (nwg) o += align_up(sizeof(BlockRef) * res_refs_of(capacity, nwg));
     L.blocks1 = o;
     o += align_up(sizeof(BlockRef) * tcap1);
     L.blocks2 = o;
@@ -382,7 +388,15 @@ struct ng_batch {
     std::vector<ResGroup> h_groups;   // tables of the launches of several solves
     std::vector<BlockRef> h_refs;
     bool coop_dim[3] = {false, false, false};   // dims whose solves they advance
-    size_t res_nwg = 0;        // workgroups the arena header has slots for
+    // the exchange of the cooperative launches: a lone solver's in its header; a
+    // batch's in free arena space, [res_off, res_off + res_len), which the free
+    // list does not know of and a new solve may take back; or, where the arena
+    // has no such space, in the reduction records of the batch's only solve
+    // (cleared for every call then)
+    enum { kResNone, kResHeader, kResFree, kResLent } res_kind = kResNone;
+    char* res_ptr = nullptr;
+    size_t res_nwg = 0;        // workgroups it has room for
+    size_t res_off = 0, res_len = 0;
     uint64_t res_steps = 0;    // step numbers used since the slots were cleared
     int dev_coop = -1;         // cooperative launch supported (-1: not asked yet)
     int dev_cus = 0;
@@ -430,7 +444,7 @@ struct ng_batch {
     int32_t* d_iota() { return (int32_t*)(arena + L.iota); }
     ResSync d_sync()
     {
-        char* p = arena + L.res;
+        char* p = res_ptr;
         ResSync y;
         y.base = (uint32_t*)p;
         y.slots = (uint64_t*)(p + 256);
@@ -440,6 +454,9 @@ struct ng_batch {
         y.nwg = (int32_t)res_nwg;
         return y;
     }
+    // tables of a batch's launches, behind its exchange
+    ResGroup* d_groups() { return (ResGroup*)(res_ptr + align_up(res_space(res_nwg))); }
+    BlockRef* d_refs() { return (BlockRef*)((char*)d_groups() + align_up(sizeof(ResGroup) * capacity)); }
     BlockRef* d_blocks(int dim) { return (BlockRef*)(arena + (dim == 1 ? L.blocks1 : L.blocks2)); }
 };
 
@@ -739,6 +756,69 @@ int resident_fleet(ng_batch* b, const std::vector<int>& ids, bool* ok)
     return NG_OK;
 }
 
+// Room for the exchange of `want` workgroups, or of as many as there is room for
+// (res_nwg).  A batch's exchange lies in arena space that no solve has: at the
+// end of the last free block that holds the largest launch's, else in the largest
+// block.  Where that is too small the batch's only solve (lone, or null) lends its
+// reduction records, which its cooperative launches do not use.
+int place_exchange(ng_batch* b, size_t want, const Slot* lone)
+{
+    if (b->res_kind == ng_batch::kResHeader) return NG_OK;
+    if (b->res_kind == ng_batch::kResLent) {
+        b->res_kind = ng_batch::kResNone;
+        b->res_nwg = 0;
+    }
+    if (b->res_nwg >= want) return NG_OK;
+    const size_t most = b->capacity > 1 ? (size_t)kResMaxWgs : (size_t)kCoopFlat;
+    size_t n = 0, end = 0;
+    for (const auto& f : b->free_list) {
+        const size_t stop = (f.first + f.second) / kAlign * kAlign;
+        const size_t fits = exchange_fits(b->capacity, stop - f.first, most);
+        if (fits >= n) {
+            n = fits;
+            end = stop;
+        }
+    }
+    size_t lent = 0;
+    if (lone && b->res_nwg < want && n < want) {
+        const size_t space = align_up((size_t)lone->partial_cap * sizeof(Partial));
+        while (lent < most && res_space(lent + 1) <= space) lent++;
+    }
+    if (n <= b->res_nwg && lent <= b->res_nwg) return NG_OK;
+    if (b->res_kind == ng_batch::kResFree) {
+        // launches in flight may still use the old one
+        CK(b, hipStreamSynchronize(b->stream));
+        b->res_len = 0;
+    }
+    if (lent > n) {
+        b->res_kind = ng_batch::kResLent;
+        b->res_ptr = (char*)lone->d.partials;
+        b->res_nwg = lent;
+        return NG_OK;
+    }
+    b->res_kind = ng_batch::kResFree;
+    b->res_len = exchange_bytes(b->capacity, n);
+    b->res_off = end - b->res_len;
+    b->res_ptr = b->arena + b->res_off;
+    b->res_nwg = n;
+    b->res_steps = 0;
+    CK(b, launch_resident_clear(b->d_sync(), res_space(n), b->stream));
+    return NG_OK;
+}
+
+// A new solve has been given [off, off + bytes): an exchange there goes, once the
+// launches in flight have ended, and is placed anew at the next run.
+int yield_exchange(ng_batch* b, size_t off, size_t bytes)
+{
+    if (b->res_kind != ng_batch::kResFree || off >= b->res_off + b->res_len || b->res_off >= off + bytes)
+        return NG_OK;
+    CK(b, hipStreamSynchronize(b->stream));
+    b->res_kind = ng_batch::kResNone;
+    b->res_nwg = b->res_len = 0;
+    b->dirty = true;
+    return NG_OK;
+}
+
 // The cooperative path, on a device that supports cooperative launches: the 1D
 // solves when each has at most coop_limit cells, and a 2D solve that is the
 // only 2D one, unless the caller has asked for the shape of another path
@@ -760,7 +840,7 @@ int choose_coop(ng_batch* b)
         live[s.dim].push_back(i);
         if (s.d.ncell > lim) within[s.dim] = false;
     }
-    if (lim == 0 || b->res_nwg == 0 || b->coop_off) return NG_OK;
+    if (lim == 0 || b->coop_off) return NG_OK;
     const bool two = live[2].size() == 1 && within[2] && b->rows[2] == kDefaultRows2D &&
                      b->waves[2] == kDefaultWaves2D && b->small_limit < 0 &&
                      b->graph_steps == kDefaultGraphSteps && b->fused;
@@ -775,6 +855,35 @@ int choose_coop(ng_batch* b)
         b->dev_cus = cus;
     }
     if (!b->dev_coop || b->dev_cus < 1) return NG_OK;
+    const int64_t all = std::min<int64_t>(b->dev_cus, kCoopFlat);
+    // the kernels of several 1D solves (and the segments of one not yet shaped)
+    std::map<int, std::vector<int>> kinds;
+    size_t want = 0;
+    if (one && live[1].size() > 1) {
+        for (int i : live[1]) {
+            InstDesc& d = b->slots[i].d;
+            d.nstrips = (int32_t)cdiv(d.nx, seg_cells(d.scheme));
+            kinds[resident_kernel_of(d, b->prec)].push_back(i);
+        }
+        for (const auto& kv : kinds) {
+            int64_t wgs = 0;
+            for (int i : kv.second) wgs += cdiv(b->slots[i].d.nstrips, kResSegs);
+            want = std::max(want, (size_t)std::min<int64_t>(wgs, kResMaxWgs));
+        }
+    } else if (one) {
+        ResLaunch r;
+        resident_shape(b->slots[live[1][0]].d, b->prec, all, r);
+        want = (size_t)r.grid;
+    }
+    if (two) {
+        ResLaunch r;
+        if (resident_shape2d(b->slots[live[2][0]].d, b->prec, all, r))
+            want = std::max(want, (size_t)r.grid);
+    }
+    const bool alone = live[1].size() + live[2].size() == 1;
+    int rc = place_exchange(b, want, !alone ? nullptr : &b->slots[live[1].empty() ? live[2][0] : live[1][0]]);
+    if (rc) return rc;
+    if (!b->res_nwg) return NG_OK;
     if (two || (one && live[1].size() == 1)) {
         // a lone solve of its dim
         for (int dim = 1; dim <= 2; dim++) {
@@ -783,7 +892,6 @@ int choose_coop(ng_batch* b)
             // on as many workgroups as the exchange has room for, while that at
             // most doubles the work of a wave (a few units more cost less than
             // the launches of the other paths)
-            const int64_t all = std::min<int64_t>(b->dev_cus, kCoopFlat);
             const int64_t cap = std::min<int64_t>(all, (int64_t)b->res_nwg);
             ResLaunch r, full;
             int per_cu = 0;
@@ -804,18 +912,23 @@ int choose_coop(ng_batch* b)
             b->res.push_back(r);
         }
     }
-    if (one && live[1].size() > 1) {
-        // by kernel; the segments of a solve not yet shaped
-        std::map<int, std::vector<int>> kinds;
-        for (int i : live[1]) {
-            InstDesc& d = b->slots[i].d;
-            d.nstrips = (int32_t)cdiv(d.nx, seg_cells(d.scheme));
-            kinds[resident_kernel_of(d, b->prec)].push_back(i);
+    // (several solves while the room there is at most doubles a wave's segments)
+    bool room = !kinds.empty();
+    for (const auto& kv : kinds) {
+        int64_t wgs = 0, segs = 0;
+        for (int i : kv.second) {
+            wgs += cdiv(b->slots[i].d.nstrips, kResSegs);
+            segs += b->slots[i].d.nstrips;
         }
+        wgs = std::min<int64_t>(wgs, kResMaxWgs);
+        const int64_t n = std::min<int64_t>(wgs, (int64_t)b->res_nwg);
+        room = room && cdiv(segs, n * kResMinWaves) <= 2 * cdiv(segs, wgs * kResMinWaves) + 2;
+    }
+    if (room) {
         const size_t keep = b->res.size();
         bool ok = true;
         for (const auto& kv : kinds) {
-            int rc = resident_fleet(b, kv.second, &ok);
+            rc = resident_fleet(b, kv.second, &ok);
             if (rc) return rc;
             if (!ok) break;
         }
@@ -839,6 +952,10 @@ int choose_coop(ng_batch* b)
 int enqueue_coop(ng_batch* b, int64_t nsteps, bool* ran)
 {
     *ran = false;
+    if (b->res_kind == ng_batch::kResLent) {
+        CK(b, launch_resident_clear(b->d_sync(), res_space(b->res_nwg), b->stream));
+        b->res_steps = 0;
+    }
     for (int64_t left = nsteps; left > 0;) {
         const int64_t n = std::min<int64_t>(left, kCoopMaxSteps);
         for (const ResLaunch& r : b->res) {
@@ -850,8 +967,8 @@ int enqueue_coop(ng_batch* b, int64_t nsteps, bool* ran)
                 b->res_steps = (uint64_t)n + 1;
             }
             const bool many = r.ngroups > 0;
-            const ResGroup* groups = many ? (const ResGroup*)(b->arena + b->L.groups) + r.group0 : nullptr;
-            const BlockRef* refs = many ? (const BlockRef*)(b->arena + b->L.refs) + r.ref0 : nullptr;
+            const ResGroup* groups = many ? b->d_groups() + r.group0 : nullptr;
+            const BlockRef* refs = many ? b->d_refs() + r.ref0 : nullptr;
             const int ngroups = many ? r.ngroups : 1;
             const hipError_t e =
                 r.dim == 2 ? launch_resident2d(kind_of(b->prec), r.s, b->d_descs(), b->d_ctrls(),
@@ -966,9 +1083,9 @@ int rebuild(ng_batch* b)
                                  sizeof(BlockRef) * b->h_blocks[dim].size(),
                                  hipMemcpyHostToDevice, b->stream));
     if (!b->h_refs.empty()) {
-        CK(b, hipMemcpyAsync(b->arena + b->L.groups, b->h_groups.data(),
+        CK(b, hipMemcpyAsync(b->d_groups(), b->h_groups.data(),
                              sizeof(ResGroup) * b->h_groups.size(), hipMemcpyHostToDevice, b->stream));
-        CK(b, hipMemcpyAsync(b->arena + b->L.refs, b->h_refs.data(),
+        CK(b, hipMemcpyAsync(b->d_refs(), b->h_refs.data(),
                              sizeof(BlockRef) * b->h_refs.size(), hipMemcpyHostToDevice, b->stream));
     }
     CK(b, hipStreamSynchronize(b->stream));
@@ -1306,7 +1423,11 @@ int batch_new(int32_t capacity, int32_t precision, void* dev_buf, size_t dev_byt
     b->L = L;
     b->tcap[1] = tcap1;
     b->tcap[2] = tcap2;
-    b->res_nwg = nwg;
+    if (nwg) {
+        b->res_kind = ng_batch::kResHeader;
+        b->res_ptr = b->arena + L.res;
+        b->res_nwg = nwg;
+    }
     b->slots.resize(capacity);
     if (dev_bytes > L.heap) b->free_list[L.heap] = dev_bytes - L.heap;
     hipError_t e = hipHostMalloc((void**)&b->h_ctrls, sizeof(InstCtrl) * capacity + sizeof(int32_t), 0);
@@ -1424,6 +1545,23 @@ void fill_desc(InstDesc& d, const ng_gas* gas, const ng_grid* grid, const ng_num
         d.H_r = d.e1_r + p_r;
         d.D_r = gas->Cv / gas->R * p_r - ev_r;
     }
+    d.cl_recipe = 0;
+    if (prec == NG_FP64) {
+        d.ih = 1.0 / d.h;
+        d.igm1 = 1.0 / d.gm1;
+        d.iR = 1.0 / d.R;
+        d.irho0 = 1.0 / d.rho0;
+        d.iT0 = 1.0 / d.T0;
+        const double e[6] = {gas->tau_rho, gas->tau_T, gas->Q_rho, gas->Q_T, gas->I_rho, gas->I_T};
+        d.pow_forms = 0;
+        for (int q = 0; q < 6; q++) d.pow_forms |= pow_form(e[q]) << (4 * q);
+        for (int r = 1; r <= ng::kRecipes64; r++) {
+            bool same = true;
+            for (int q = 0; q < 6; q++) same = same && 2.0 * e[q] == ng::kRecipe64[r][q];
+            if (same) d.cl_recipe = r;
+        }
+        return;
+    }
     // eq. (6) with T = p / (R rho): (rho/rho0)^x (T/T0)^y =
     // rho0^-x (R T0)^-y rho^(x - y) p^y; 1/tau takes the negated exponents
     const double RT0 = gas->R * gas->T0;
@@ -1441,23 +1579,6 @@ void fill_desc(InstDesc& d, const ng_gas* gas, const ng_grid* grid, const ng_num
             if (e2 != nearbyint(e2) || fabs(e2) > 4.0) half = false;
             else codes[2 * i + j] = (int)e2;
         }
-    }
-    d.ih = 1.0 / d.h;
-    d.igm1 = 1.0 / d.gm1;
-    d.iR = 1.0 / d.R;
-    d.irho0 = 1.0 / d.rho0;
-    d.iT0 = 1.0 / d.T0;
-    d.cl_recipe = 0;
-    if (prec == NG_FP64) {
-        const double e[6] = {gas->tau_rho, gas->tau_T, gas->Q_rho, gas->Q_T, gas->I_rho, gas->I_T};
-        d.pow_forms = 0;
-        for (int q = 0; q < 6; q++) d.pow_forms |= pow_form(e[q]) << (4 * q);
-        for (int r = 1; r <= ng::kRecipes64; r++) {
-            bool same = true;
-            for (int q = 0; q < 6; q++) same = same && 2.0 * e[q] == ng::kRecipe64[r][q];
-            if (same) d.cl_recipe = r;
-        }
-        return;
     }
     for (int r = 1; half && r <= ng::kRecipes; r++) {
         bool same = true;
@@ -1644,6 +1765,11 @@ int add_solve(ng_batch* b, const ng_gas* gas, const ng_grid* grid, const ng_nume
     if (!arena_alloc(b, sb, &off)) {
         b->err = "no room in the device arena";
         return NG_EFULL;
+    }
+    rc = yield_exchange(b, off, sb);
+    if (rc) {
+        arena_free(b, off, sb);
+        return rc;
     }
     Slot& s = b->slots[slot];
     s = Slot();
@@ -2200,7 +2326,7 @@ int ng_batch_create(int32_t capacity, int32_t precision, void* dev_buf, size_t d
     size_t tcap = dev_bytes / per + 64 * (size_t)capacity;
     std::string err;
     return batch_new(capacity, precision, dev_buf, dev_bytes, hip_stream, tcap, tcap / 4 + 64 * capacity,
-                     res_wgs_of(dev_bytes), out, err);
+                     0, out, err);
 }
 
 int ng_batch_solve_bytes(const ng_grid* grid, int32_t precision, size_t* bytes)

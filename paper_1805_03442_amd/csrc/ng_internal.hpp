@@ -112,14 +112,21 @@ struct InstDesc {
     double src_yc, src_hw;    // 2D: the source drives rows with |y - yc| <= hw
     // 2D sector run: pump and sink only for x >= x0, |y - y0| <= (x - x0) tan
     double wedge_x0, wedge_y0, wedge_tan;   // tan <= 0: everywhere
-    // The closures of eq. (6) in terms of (rho, p) for the FP32 arithmetic:
-    // 1/tau, Q and I = cl_c rho^cl_a p^cl_b (with T = p / (R rho)); cl_recipe
-    // > 0 names the compiled recipe whose exponents they are (kRecipeCodes).
-    double cl_c[3], cl_a[3], cl_b[3];
+    // constants of the solve's own arithmetic, and no other's
+    union {
+        // FP32, mixed: the closures of eq. (6) in terms of (rho, p): 1/tau, Q and
+        // I = cl_c rho^cl_a p^cl_b (with T = p / (R rho)); cl_recipe > 0 names the
+        // compiled recipe whose exponents they are (kRecipeCodes)
+        struct {
+            double cl_c[3], cl_a[3], cl_b[3];
+        };
+        // FP64: rounded reciprocals of the run's constant denominators
+        struct {
+            double ih, igm1, iR, irho0, iT0;
+        };
+    };
     int32_t cl_recipe;        // (FP64 solves: the row of kRecipe64)
-    int32_t pow_forms;        // pow_form of the six exponents of eq. (6), four bits each
-    // rounded reciprocals of the run's constant denominators (FP64 arithmetic)
-    double ih, igm1, iR, irho0, iT0;
+    int32_t pow_forms;        // FP64: pow_form of the six exponents of eq. (6), four bits each
 };
 
 // Mutable per-solve state, advanced by the finalize kernel.
