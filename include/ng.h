@@ -421,10 +421,12 @@ int ng_batch_set_small_limit(ng_batch* b, int64_t max_cells);
  * takes it as a lone solve does; several 1D solves take it side by side, in up
  * to four cooperative launches per call whose workgroups are dealt by solve
  * size, while each has at most max_cells cells and in FP64 their segments (60
- * cells) number at most 45000.  The launches' exchange (1.1 KB per workgroup, at
- * most 0.9 MB) lies in arena space that no solve has; a new solve that needs the
- * space gets it.  With less room than that, fewer workgroups take the work, or
- * the other paths; a lone solve's exchange then lies in its own reduction space. */
+ * cells) number at most 45000, in calls of at least four to fifteen steps per
+ * launch (shorter calls take the persistent path or one launch per step).  The
+ * launches' exchange (1.1 KB per workgroup, at most 0.9 MB) lies in arena space
+ * that no solve has; a new solve that needs the space gets it.  With less room
+ * than that, fewer workgroups take the work, or the other paths; a lone solve's
+ * exchange then lies in its own reduction space. */
 int ng_batch_set_coop(ng_batch* b, int64_t max_cells, int32_t spin_limit);
 
 /* Launch shape of the batched step kernels (see ng_set_launch). */

@@ -77,6 +77,31 @@ constexpr int64_t kCoopCells = int64_t(1) << 22;
 // of its records cost about three steps (one step of 200 to 600^2 cells 47 to 57
 // us against 34 to 42 us; four steps 54 to 85 against 56 to 99).
 constexpr int64_t kCoopMinSteps = 3;
+// The same for a batch's 1D solves side by side, per cooperative launch of the
+// call: against one launch per step for all, and against the persistent kernel
+// for more solves than CUs (it then takes them in turns).  Us per call of 3 and 4
+// steps, cooperative and not: four FP32 solves of 20000 cells 42 and 35, 45 and
+// 47 (FP64 45 and 37, 49 and 49), 512 of 200 cells 39 and 31, 42 and 39 (five
+// steps: 43 and 48).
+constexpr int64_t kFleetMinSteps = 4;
+constexpr int64_t kFleetMinStepsMany = 5;
+// Solves that the persistent kernel takes all at once cost there, per step, 3.3 +
+// r us in FP32 and mixed and 2.7 + 2.5 r in FP64 for r segments per wave; side by
+// side 1.5 to 3 us after 30 for the launch (with a full launch's workgroups 4.4
+// after 36); with one launch per step 10 us, or what more than 4000 segments
+// take.  Us per call, cooperative and persistent: two FP32 solves of 200 cells (r
+// = 1) 8 steps 41 and 37, 10 steps 44 and 45, 64 of 300 cells 10 steps 55 and 50,
+// 12 steps 59 and 59; eight of 1000 (r = 3) 8 steps 51 and 53; three of 2000 (r =
+// 5) 6 steps 46 and 51; 200 of 1500 (r = 4) 12 steps 89 and 92; FP64, r = 1, 8
+// steps 47 and 45, r = 3, 4 steps 44 and 44.  One launch per step and persistent,
+// FP64, one step: three solves of 2000 cells 10 and 18, eight of 1000 10 and 13,
+// 200 of 1500 21 and 17.
+constexpr int64_t kFleetSmallSteps32 = 12;
+constexpr int64_t kFleetSmallSteps64 = 11;
+constexpr int64_t kFleetFullSteps = 4;
+constexpr int64_t kFleetSmallSegs32 = 6;    // segments per wave
+constexpr int64_t kFleetSmallSegs64 = 2;
+constexpr int64_t kFleetManySegs = 4000;    // segments of all solves
 // polls of an exchange's wait before it gives up (each a memory round trip
 // of about a microsecond and a short sleep: about a second)
 constexpr int32_t kCoopSpin = 1 << 20;
@@ -387,7 +412,9 @@ struct ng_batch {
     std::vector<ResLaunch> res;
     std::vector<ResGroup> h_groups;   // tables of the launches of several solves
     std::vector<BlockRef> h_refs;
-    bool coop_dim[3] = {false, false, false};   // dims whose solves they advance
+    bool coop_dim[3] = {false, false, false};   // dims whose solves they advance,
+    int64_t coop_least[3] = {0, 0, 0};          // in calls of at least this many steps
+    bool fleet_small = false;  // 1D solves side by side: the persistent kernel takes shorter calls
     // the exchange of the cooperative launches: a lone solver's in its header; a
     // batch's in free arena space, [res_off, res_off + res_len), which the free
     // list does not know of and a new solve may take back; or, where the arena
@@ -410,7 +437,7 @@ struct ng_batch {
     // captured step sequence
     hipGraphExec_t gexec = nullptr;
     int gsteps = 0;
-    bool gskips = false;       // captured without the cooperative dims
+    int gskips = 0;            // captured without these dims (a bit each)
     int graph_steps = kDefaultGraphSteps;
     // pinned read-back of the control blocks, and of the status of a solve that
     // is read out
@@ -614,6 +641,13 @@ void shape_solve(ng_batch* b, Slot& s, bool alone = true)
     d.nitems = dim == 2 ? (int64_t)d.nstrips * d.nchunks : (int64_t)d.nchunks;
     d.nblocks = cdiv(d.nitems, d.waves_per_block);
     d.fused = (b->fused && alone && !s.small && d.nblocks <= kFusedMaxBlocks) ? 1 : 0;
+}
+
+// Most cells of a solve on the persistent one-workgroup path.
+int64_t small_limit_of(const ng_batch* b)
+{
+    return b->small_limit >= 0 ? b->small_limit
+                               : (b->prec != NG_FP64 ? kSmallCells32 : kSmallCells64);
 }
 
 // Kernel of a 1D solve on the cooperative path (launch_resident).  The FP32
@@ -829,7 +863,7 @@ int choose_coop(ng_batch* b)
     b->res.clear();
     b->h_groups.clear();
     b->h_refs.clear();
-    b->coop_dim[1] = b->coop_dim[2] = false;
+    b->coop_dim[1] = b->coop_dim[2] = b->fleet_small = false;
     const int64_t lim = b->coop_limit >= 0 ? b->coop_limit : kCoopCells;
     std::vector<int> live[3];
     bool within[3] = {true, true, true};
@@ -909,6 +943,7 @@ int choose_coop(ng_batch* b)
             r.one.inst = live[dim][0];
             s.coop = true;
             b->coop_dim[dim] = true;
+            b->coop_least[dim] = kCoopMinSteps;
             b->res.push_back(r);
         }
     }
@@ -937,19 +972,34 @@ int choose_coop(ng_batch* b)
             b->h_groups.clear();
             b->h_refs.clear();
         } else {
-            for (int i : live[1]) b->slots[i].coop = true;
+            int64_t least = kFleetMinSteps, cells = 0, segs = 0;
+            for (int i : live[1]) {
+                b->slots[i].coop = true;
+                cells = std::max(cells, b->slots[i].d.ncell);
+                segs += b->slots[i].d.nstrips;
+            }
+            const bool f64 = b->prec == NG_FP64, many = (int64_t)live[1].size() > b->dev_cus;
+            const int64_t r = cdiv(cdiv(cells, kInterior), kSmallWaves);
+            b->fleet_small = cells <= small_limit_of(b) &&
+                             (many || segs > kFleetManySegs || r <= (f64 ? kFleetSmallSegs64 : kFleetSmallSegs32));
+            if (many)
+                least = kFleetMinStepsMany;
+            else if (b->fleet_small)
+                least = std::max(least, f64 ? kFleetSmallSteps64 - 3 * r : kFleetSmallSteps32 - r) +
+                        (segs > kResSegs * kResMaxWgs ? kFleetFullSteps : 0);
             b->coop_dim[1] = true;
+            b->coop_least[1] = least * (int64_t)(b->res.size() - keep);
         }
     }
     return NG_OK;
 }
 
-// Enqueue the cooperative launches for nsteps steps (each of at most
-// kCoopMaxSteps steps).  *ran: false when the runtime refused the first of them
+// Enqueue the cooperative launches of the dims in `dims` (a bit each) for nsteps
+// steps (each of at most kCoopMaxSteps steps).  *ran: false when the runtime refused the first of them
 // and nothing was enqueued -- the device gives its cooperative queue to one
 // process at a time.  The object then keeps to the other paths, whose tables
 // hold the same solves, until the next ng_batch_set_coop.
-int enqueue_coop(ng_batch* b, int64_t nsteps, bool* ran)
+int enqueue_coop(ng_batch* b, int64_t nsteps, int dims, bool* ran)
 {
     *ran = false;
     if (b->res_kind == ng_batch::kResLent) {
@@ -959,6 +1009,7 @@ int enqueue_coop(ng_batch* b, int64_t nsteps, bool* ran)
     for (int64_t left = nsteps; left > 0;) {
         const int64_t n = std::min<int64_t>(left, kCoopMaxSteps);
         for (const ResLaunch& r : b->res) {
+            if (!(dims >> r.dim & 1)) continue;
             // the step numbers are 32 bits wide: start them over long before
             // they can meet an old one
             b->res_steps += (uint64_t)n + 1;
@@ -1007,8 +1058,7 @@ int rebuild(ng_batch* b)
     }
     // per dim: the workgroups of big solves first (the per-step launch covers
     // exactly those), then those of small solves (used by the priming pass only)
-    const int64_t lim = b->small_limit >= 0 ? b->small_limit
-                                            : (b->prec != NG_FP64 ? kSmallCells32 : kSmallCells64);
+    const int64_t lim = small_limit_of(b);
     int rc = choose_coop(b);
     if (rc) return rc;
     int nbig[3] = {0, 0, 0};
@@ -1016,7 +1066,7 @@ int rebuild(ng_batch* b)
     for (int i = 0; i < b->capacity; i++)
         if (b->slots[i].live) {
             Slot& s = b->slots[i];
-            s.small = !s.coop && s.d.ncell <= lim;
+            s.small = (!s.coop || (s.dim == 1 && b->fleet_small)) && s.d.ncell <= lim;
             if (!s.small) {
                 nbig[s.dim]++;
                 grids[s.dim].push_back({s.d.nx, s.d.ny});
@@ -1105,11 +1155,11 @@ hipEvent_t get_event(ng_batch* b, size_t i)
 }
 
 // Enqueue the kernels of one step of every active solve on stream st (of the
-// dims in skip: none).
-int enqueue_one(ng_batch* b, hipStream_t st, const bool* skip = nullptr)
+// dims in skip, a bit each: none).
+int enqueue_one(ng_batch* b, hipStream_t st, int skip = 0)
 {
     for (int dim = 1; dim <= 2; dim++) {
-        if (!b->ninst[dim] || (skip && skip[dim])) continue;
+        if (!b->ninst[dim] || (skip >> dim & 1)) continue;
         CK(b, launch_step(dim, kind_of(b->prec), b->variant[dim], b->d_descs(), b->d_ctrls(),
                           b->d_blocks(dim), b->nblocks[dim], waves_of(b, dim, {}), b->remap, b->fused,
                           st));
@@ -1121,19 +1171,19 @@ int enqueue_one(ng_batch* b, hipStream_t st, const bool* skip = nullptr)
 }
 
 // Launch the persistent kernel of the small solves for nsteps steps.
-int enqueue_small(ng_batch* b, int64_t nsteps, hipStream_t st)
+int enqueue_small(ng_batch* b, int64_t nsteps, hipStream_t st, int skip = 0)
 {
     for (int dim = 1; dim <= 2; dim++) {
-        if (!b->nsmall[dim]) continue;
+        if (!b->nsmall[dim] || (skip >> dim & 1)) continue;
         CK(b, launch_small(dim, kind_of(b->prec), b->d_descs(), b->d_ctrls(),
                            b->d_small(dim), b->nsmall[dim], kSmallWaves, nsteps, st));
     }
     return NG_OK;
 }
 
-bool any_big(const ng_batch* b, const bool* skip = nullptr)
+bool any_big(const ng_batch* b, int skip = 0)
 {
-    return (b->ninst[1] > 0 && !(skip && skip[1])) || (b->ninst[2] > 0 && !(skip && skip[2]));
+    return (b->ninst[1] > 0 && !(skip >> 1 & 1)) || (b->ninst[2] > 0 && !(skip >> 2 & 1));
 }
 bool any_small(const ng_batch* b) { return b->nsmall[1] + b->nsmall[2] > 0; }
 
@@ -1152,7 +1202,7 @@ int enqueue_timed(ng_batch* b, int64_t nsteps)
         if (!e0 || !e1) return dev_err(b, hipErrorOutOfMemory, "hipEventCreate");
         CK(b, hipEventRecord(e0, b->stream));
         bool ran = false;
-        int rc = enqueue_coop(b, nsteps, &ran);
+        int rc = enqueue_coop(b, nsteps, 1 << 1, &ran);
         if (rc) return rc;
         if (ran) {
             CK(b, hipEventRecord(e1, b->stream));
@@ -1227,9 +1277,9 @@ int enqueue_timed(ng_batch* b, int64_t nsteps)
     return NG_OK;
 }
 
-int ensure_graph(ng_batch* b, const bool* skip)
+int ensure_graph(ng_batch* b, int skip)
 {
-    if (b->gexec && b->gsteps == b->graph_steps && b->gskips == (skip != nullptr)) return NG_OK;
+    if (b->gexec && b->gsteps == b->graph_steps && b->gskips == skip) return NG_OK;
     drop_graph(b);
     if (!b->cap_stream) CK(b, hipStreamCreateWithFlags(&b->cap_stream, hipStreamNonBlocking));
     CK(b, hipStreamBeginCapture(b->cap_stream, hipStreamCaptureModeThreadLocal));
@@ -1249,7 +1299,7 @@ int ensure_graph(ng_batch* b, const bool* skip)
         return dev_err(b, e, "hipGraphInstantiate");
     }
     b->gsteps = b->graph_steps;
-    b->gskips = skip != nullptr;
+    b->gskips = skip;
     return NG_OK;
 }
 
@@ -1260,14 +1310,16 @@ int enqueue_planned(ng_batch* b, int64_t nsteps)
 {
     int rc = NG_OK;
     if (b->timing) return enqueue_timed(b, nsteps);
-    const bool* skip = nullptr;
-    if (!b->res.empty() && nsteps >= kCoopMinSteps) {
+    int skip = 0;
+    for (int dim = 1; dim <= 2; dim++)
+        if (b->coop_dim[dim] && nsteps >= b->coop_least[dim]) skip |= 1 << dim;
+    if (skip) {
         bool ran = false;
-        rc = enqueue_coop(b, nsteps, &ran);
+        rc = enqueue_coop(b, nsteps, skip, &ran);
         if (rc) return rc;
-        if (ran) skip = b->coop_dim;
+        if (!ran) skip = 0;
     }
-    rc = enqueue_small(b, nsteps, b->stream);
+    rc = enqueue_small(b, nsteps, b->stream, skip);
     if (rc || !any_big(b, skip)) return rc;
     int64_t left = nsteps;
     if (left >= b->graph_steps) {
@@ -1585,14 +1637,6 @@ void fill_desc(InstDesc& d, const ng_gas* gas, const ng_grid* grid, const ng_num
         for (int q = 0; q < 6; q++) same = same && codes[q] == ng::kRecipeCodes[r][q];
         if (same) d.cl_recipe = r;
     }
-}
-
-// Validate and upload a solve's conserved state into the slot's buffer 0, run
-// the priming pass (first dt, totals, checks).  Synchronising.
-int64_t small_limit_of(const ng_batch* b)
-{
-    return b->small_limit >= 0 ? b->small_limit
-                               : (b->prec != NG_FP64 ? kSmallCells32 : kSmallCells64);
 }
 
 // Pinned staging of at least `bytes` (at most kStageBytes), both buffers idle.
