@@ -213,7 +213,8 @@ int ng_init_conserved(const ng_gas* gas, const ng_grid* grid, const ng_numerics*
                       void* hip_stream, ng_solver** out);
 
 /* Enqueue nsteps steps of eq. (15), each with dt from eq. (16) evaluated on the
- * state it starts from (no end time).  Asynchronous. */
+ * state it starts from (no end time).  Asynchronous; not under stream capture
+ * (NG_EDEVICE; ng_batch_run and ng_step_static can be captured). */
 int ng_step(ng_solver* s, int64_t nsteps);
 
 /* Advance until t_end (the last dt is shortened to land on it) or until

@@ -2089,6 +2089,12 @@ int ng_step(ng_solver* s, int64_t nsteps)
 {
     if (!s || nsteps < 0) return NG_EINVAL;
     if (nsteps == 0) return NG_OK;
+    // whether the limits of ng_run_to_time have to go is known here only: a
+    // graph's replays would step under whichever limits they find
+    if (capturing(s->b)) {
+        s->b->err = "ng_step: the stream is being captured";
+        return solver_rc(s, NG_EDEVICE);
+    }
     // a new solver has no limits; ng_run_to_time leaves its own
     int rc = s->limited ? set_limits(s->b, s->slot, INFINITY, -1) : NG_OK;
     if (!rc) {
