@@ -284,9 +284,10 @@ int ng_set_small_limit(ng_solver* s, int64_t max_cells);
  * another stream or process) ends the launch early with every kernel exiting.
  * The next call that reads diagnostics, a state or the finished solves then
  * runs the missing steps on the other paths before it returns, and the object
- * keeps to those until the next ng_set_coop.  Only with a limit of 0, or once
- * steps were captured into a caller's graph (whose replays are not counted),
- * does that call report NG_ESTALL instead.  Cooperative launches must be
+ * keeps to those until the next ng_set_coop.  With a limit of 0 that call reports
+ * NG_ESTALL instead; so it does for the only 1D solve of a batch once steps were
+ * captured into a caller's graph, whose replays are not counted (other batches
+ * then keep to the other paths).  Cooperative launches must be
  * supported by the device (else the other paths run).  A device gives its
  * cooperative queue to one process at a time: an object whose first cooperative
  * launch is refused takes the other paths until the next ng_set_coop.

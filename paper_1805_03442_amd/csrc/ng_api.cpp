@@ -414,13 +414,14 @@ struct ng_batch {
     std::vector<BlockRef> h_refs;
     bool coop_dim[3] = {false, false, false};   // dims whose solves they advance,
     int64_t coop_least[3] = {0, 0, 0};          // in calls of at least this many steps
+    bool lone1d = false;       // a 1D solve, the only one
     bool fleet_small = false;  // 1D solves side by side: the persistent kernel takes shorter calls
     // the exchange of the cooperative launches: a lone solver's in its header; a
     // batch's in free arena space, [res_off, res_off + res_len), which the free
     // list does not know of and a new solve may take back; or, where the arena
     // has no such space, in the reduction records of the batch's only solve
     // (cleared for every call then)
-    enum { kResNone, kResHeader, kResFree, kResLent } res_kind = kResNone;
+    enum { kResNone, kResHeader, kResFree, kResLent } res_kind = kResNone;   // (kResHeader: fixed)
     char* res_ptr = nullptr;
     size_t res_nwg = 0;        // workgroups it has room for
     size_t res_off = 0, res_len = 0;
@@ -853,6 +854,18 @@ int yield_exchange(ng_batch* b, size_t off, size_t bytes)
     return NG_OK;
 }
 
+// An exchange whose address goes into a caller's graph stays where it is.
+void keep_exchange(ng_batch* b)
+{
+    if (b->res_kind != ng_batch::kResFree) return;
+    auto it = std::prev(b->free_list.upper_bound(b->res_off));
+    const size_t from = it->first, to = it->first + it->second, end = b->res_off + b->res_len;
+    b->free_list.erase(it);
+    if (b->res_off > from) b->free_list[from] = b->res_off - from;
+    if (to > end) b->free_list[end] = to - end;
+    b->res_kind = ng_batch::kResHeader;
+}
+
 // The cooperative path, on a device that supports cooperative launches: the 1D
 // solves when each has at most coop_limit cells, and a 2D solve that is the
 // only 2D one, unless the caller has asked for the shape of another path
@@ -863,7 +876,7 @@ int choose_coop(ng_batch* b)
     b->res.clear();
     b->h_groups.clear();
     b->h_refs.clear();
-    b->coop_dim[1] = b->coop_dim[2] = b->fleet_small = false;
+    b->coop_dim[1] = b->coop_dim[2] = b->fleet_small = b->lone1d = false;
     const int64_t lim = b->coop_limit >= 0 ? b->coop_limit : kCoopCells;
     std::vector<int> live[3];
     bool within[3] = {true, true, true};
@@ -874,6 +887,7 @@ int choose_coop(ng_batch* b)
         live[s.dim].push_back(i);
         if (s.d.ncell > lim) within[s.dim] = false;
     }
+    b->lone1d = live[1].size() == 1 && live[2].empty();
     if (lim == 0 || b->coop_off) return NG_OK;
     const bool two = live[2].size() == 1 && within[2] && b->rows[2] == kDefaultRows2D &&
                      b->waves[2] == kDefaultWaves2D && b->small_limit < 0 &&
@@ -1313,7 +1327,11 @@ int enqueue_planned(ng_batch* b, int64_t nsteps)
     int skip = 0;
     for (int dim = 1; dim <= 2; dim++)
         if (b->coop_dim[dim] && nsteps >= b->coop_least[dim]) skip |= 1 << dim;
+    // steps in a caller's graph cannot be resumed after a stall: then only a lone
+    // 1D solve, which always took it, keeps the cooperative path
+    if (b->captured && !b->lone1d) skip = 0;
     if (skip) {
+        if (b->captured) keep_exchange(b);
         bool ran = false;
         rc = enqueue_coop(b, nsteps, skip, &ran);
         if (rc) return rc;

@@ -87,3 +87,41 @@ def test_batch_run_is_recorded(sizes, n):
     assert out[0][0] == out[1][0]
     for U, V in zip(out[0][1], out[1][1]):
         assert np.array_equal(U, V)
+
+
+def test_a_recorded_launch_keeps_its_room():
+    """The exchange of a cooperative launch in a graph is not given to solves that
+    are added later: a replay before the next call leaves them as they are."""
+    import torch
+    from paper_1805_03442_amd import ng
+    n = 9000
+    need = ng.Batch.solve_bytes(n, 1, ng.NG_FP64)
+    st = torch.cuda.Stream()
+    b = ng.Batch(9, 7 * need + need // 2, precision=ng.NG_FP64, stream=st)
+    slots = [b.add(GAS, n, 1, start(n), 1e9)]
+    b.run(20)
+    b.poll()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=st, capture_error_mode="thread_local"):
+        b.run(20)
+    while True:
+        k = b.add(GAS, n, 1, start(n), 1e9)
+        if k is None:
+            break
+        slots.append(k)
+    assert len(slots) >= 3
+    print("replay beside", len(slots), "solves", flush=True)
+    before = [b.conserved(i) for i in slots[1:]]
+    with torch.cuda.stream(st):
+        for _ in range(3):
+            g.replay()
+    assert b.diagnostics(slots[0])["steps"] == 80
+    assert all(np.array_equal(U, b.conserved(i)) for U, i in zip(before, slots[1:]))
+    b.run(20)
+    r = ng.Solver(GAS, n, 1, W=start(n), precision=ng.NG_FP64)
+    r.step(20)
+    assert all(np.array_equal(r.conserved(), b.conserved(i)) for i in slots[1:])
+    r.step(80)
+    assert np.array_equal(r.conserved(), b.conserved(slots[0]))
+    r.close()
+    b.close()
