@@ -69,17 +69,22 @@ struct K64 {
 // operations and a reciprocal for each quotient: scaling of both operands,
 // two Newton steps, the quotient, its correction, special cases) and square
 // root.  The operands here are densities, pressures, speeds and times, far
-// from the ends of the exponent range, so the scaling is left out; quotients
-// with one denominator share its reciprocal; and denominators constant over a
-// run have theirs rounded on the host.  The results are the correctly rounded
-// ones: the last operation adds the exact remainder, times the reciprocal, to
-// a quotient that is off by less than two units in the last place.  (Measured
-// on 2^34 random operand pairs of exponents within +-300: equal to the
-// compiler's division and root in every bit.)  With the closures compiled per
-// exponent set and one side's state in the HLLC flux this takes half of the
-// step's instructions away.  Us per step before and after: 1000x601 cells
-// 60 and 36, 1024 cells 5.6 and 4.4, CSPH-TVD on 100003 cells 9.7 and 7.6,
-// section 3's gas (its -3/2 power by pow before) on 1600 cells 7.6 and 5.3.
+// from the ends of the exponent range, so the scaling and the special cases are
+// left out; quotients with one denominator share its reciprocal; and
+// denominators constant over a run have theirs rounded on the host.  The last
+// operation adds the exact remainder, times the reciprocal, to a quotient that
+// is off by less than two units in the last place, which gives the correctly
+// rounded one while operands, quotient and remainder are normal numbers: whole
+// steps equal the oracle's, with IEEE divisions, bit for bit.  Outside that the
+// last bit may differ, a negative zero as numerator gives a positive one, and a
+// zero denominator NaN, where a flux discards the quotient or the step fails
+// either way; the exceptions, which a step survives, are a relaxation time of
+// zero or infinity (quot64_any) and a temperature of zero (powh64).  With the
+// closures compiled per exponent set and one side's state in the HLLC flux this
+// takes half of the step's instructions away.  Us per step before and after:
+// 1000x601 cells 60 and 36, 1024 cells 5.6 and 4.4, CSPH-TVD on 100003 cells 9.7
+// and 7.6, section 3's gas (its -3/2 power by pow before) on 1600 cells 7.6 and
+// 5.3.
 
 // 1/b to about half a unit in the last place: the hardware's approximation
 // (2^-23) and one third-order Newton step (error 2^-69 before the rounding)
@@ -102,11 +107,13 @@ __device__ __forceinline__ double quot64_any(double a, double b, double y)
 {
     return __builtin_amdgcn_div_fixup(quot64(a, b, y), b, a);
 }
-// 1/b, correctly rounded
+// 1/b, correctly rounded; Any: also for b zero or infinite
+template <bool Any>
 __device__ __forceinline__ double inv64(double b)
 {
     const double y = recip64(b);
-    return __builtin_fma(__builtin_fma(-b, y, 1.0), y, y);
+    const double q = __builtin_fma(__builtin_fma(-b, y, 1.0), y, y);
+    return Any ? __builtin_amdgcn_div_fixup(q, b, 1.0) : q;
 }
 // recip64(a b) for b near a constant's multiple: from a first approximation
 // y of relative error below 2^-50 (a product of two reciprocals)
@@ -141,15 +148,17 @@ __device__ __noinline__ double pow_general(double x, double a) { return pow(x, a
 // 0, 1, -1, 2 and 1/2 by the correctly rounded IEEE operations (the exact
 // power rounded once); -3/2 (section 3's relaxation time) as the reciprocal
 // of x sqrt(x) carried to twice the precision and rounded once (about 20
-// operations against some 200 of pow).
-template <int C>
+// operations against some 200 of pow).  Any: x may be zero, as the temperature of
+// a half step whose sink takes all the pressure, and a relaxation time then
+// infinite.
+template <int C, bool Any>
 __device__ __forceinline__ double powh64(double x)
 {
     static_assert(C == 0 || C == 2 || C == -2 || C == 4 || C == 1 || C == -3,
                   "exponent code without a short form");
     if constexpr (C == 0) return 1.0;
     else if constexpr (C == 2) return x;
-    else if constexpr (C == -2) return inv64(x);
+    else if constexpr (C == -2) return inv64<Any>(x);
     else if constexpr (C == 4) return x * x;
     else if constexpr (C == 1) return sqrt64(x);
     else {
@@ -160,20 +169,22 @@ __device__ __forceinline__ double powh64(double x)
         const double dm = __builtin_fma(x, s, -m) + x * ds;
         const double y = recip64(m);
         const double e = __builtin_fma(-y, dm, __builtin_fma(-m, y, 1.0));
-        return __builtin_fma(e, y, y);
+        const double q = __builtin_fma(e, y, y);
+        return Any ? __builtin_amdgcn_div_fixup(q, x, 1.0) : q;
     }
 }
 // the same for an exponent a known at run time with its form (pow_form), the
 // same for every lane: one scalar branch
+template <bool Any>
 __device__ __forceinline__ double powr64(double x, int form, double a)
 {
     switch (form) {
     case 0: return 1.0;
     case 1: return x;
-    case 2: return powh64<-2>(x);
+    case 2: return powh64<-2, Any>(x);
     case 3: return x * x;
-    case 4: return powh64<1>(x);
-    case 5: return powh64<-3>(x);
+    case 4: return powh64<1, Any>(x);
+    case 5: return powh64<-3, Any>(x);
     default: return pow_general(x, a);
     }
 }
@@ -188,8 +199,9 @@ template <int CL>
 __device__ __forceinline__ Powers64 powers64(const K64& k, double r, double t)
 {
     constexpr const int* e = kRecipe64[CL];
-    return {k.tau0 * powh64<e[0]>(r) * powh64<e[1]>(t), k.Q0 * powh64<e[2]>(r) * powh64<e[3]>(t),
-            k.I0 * powh64<e[4]>(r) * powh64<e[5]>(t)};
+    return {k.tau0 * powh64<e[0], false>(r) * powh64<e[1], true>(t),
+            k.Q0 * powh64<e[2], false>(r) * powh64<e[3], true>(t),
+            k.I0 * powh64<e[4], false>(r) * powh64<e[5], true>(t)};
 }
 // the same with the exponents known at run time; out of line, once per library.
 // The descriptor's address and the forms are made scalar again (arguments of a
@@ -204,9 +216,9 @@ __device__ __noinline__ Powers64 powers64_any(const InstDesc* dv, double r, doub
     typedef const __attribute__((address_space(4))) InstDesc CDesc;
     const CDesc* d = (const CDesc*)pu;
     const int f = d->pow_forms;
-    return {d->tau0 * powr64(r, f & 15, d->tau_rho) * powr64(t, (f >> 4) & 15, d->tau_T),
-            d->Q0 * powr64(r, (f >> 8) & 15, d->Q_rho) * powr64(t, (f >> 12) & 15, d->Q_T),
-            d->I0 * powr64(r, (f >> 16) & 15, d->I_rho) * powr64(t, (f >> 20) & 15, d->I_T)};
+    return {d->tau0 * powr64<false>(r, f & 15, d->tau_rho) * powr64<true>(t, (f >> 4) & 15, d->tau_T),
+            d->Q0 * powr64<false>(r, (f >> 8) & 15, d->Q_rho) * powr64<true>(t, (f >> 12) & 15, d->Q_T),
+            d->I0 * powr64<false>(r, (f >> 16) & 15, d->I_rho) * powr64<true>(t, (f >> 20) & 15, d->I_T)};
 }
 
 // closures of eq. (6) at (rho, p), and T (eq. (7)); y = recip64(rho).  The
