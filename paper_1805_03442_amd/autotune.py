@@ -5,14 +5,18 @@ item (2D: rows a wavefront marches through; 1D: 60-cell segments per work
 item) and wavefronts per workgroup.  Every cell's arithmetic is the same for
 all shapes, so tuning never changes results (only the summation order of the
 FP64 totals).  The tuner times each candidate with HIP events on a throwaway
-solve of the target shape and caches the winner per (dimension, precision,
-size bucket) in ``tuning.json`` next to this file.
+solve of the target shape, then the winner and a solve without a shape against
+each other by the clock: a shape keeps a 2D solve off the cooperative path, which
+is the faster one up to 2^22 cells, and its launches cannot be timed one by one.
+A winner that is faster is cached per (dimension, precision, size bucket) in
+``tuning.json`` next to this file.
 """
 from __future__ import annotations
 
 import json
 import math
 import os
+import time
 
 import numpy as np
 
@@ -65,10 +69,25 @@ def apply(solver: "ng.Solver", path: str = CACHE) -> bool:
     return True
 
 
+def us_per_step(solver: "ng.Solver", steps: int, repeats: int = 5) -> float:
+    """Least time per step of ``steps`` steps by the clock, as a program runs them."""
+    import torch
+    solver.step(steps)
+    best = math.inf
+    for _ in range(repeats):
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        solver.step(steps)
+        torch.cuda.synchronize()
+        best = min(best, time.perf_counter() - t)
+    return 1e6 * best / steps
+
+
 def tune(nx: int, ny: int, precision: int, gas: dict | None = None, W=None, steps: int = 30,
          warmup: int = 5, candidates=None, path: str | None = CACHE, verbose: bool = False):
-    """Time every candidate shape on a throwaway solve; cache and return the
-    fastest as dict(rows, waves, step_ms, table)."""
+    """Time every candidate shape on a throwaway solve and return the fastest as
+    dict(rows, waves, step_ms, table, us_per_step, untuned_us_per_step, kept); it is
+    cached (kept) if it beats a solve without a shape, else the shape's entry goes."""
     import torch
     gas = dict(gas or dict(wl.BASE_GAS, Q_T=2.0))
     if W is None:
@@ -99,10 +118,22 @@ def tune(nx: int, ny: int, precision: int, gas: dict | None = None, W=None, step
     finally:
         s.close()
     rows, waves, ms = min(table, key=lambda t: t[2])
-    res = dict(rows=rows, waves=waves, step_ms=ms, table=table)
+    us = []
+    for shape in ((rows, waves), None):
+        s = ng.Solver(gas, nx, ny, W=W, precision=precision)
+        try:
+            if shape:
+                s.set_launch(*shape)
+            us.append(us_per_step(s, max(steps, 128)))
+        finally:
+            s.close()
+    res = dict(rows=rows, waves=waves, step_ms=ms, table=table, us_per_step=us[0],
+               untuned_us_per_step=us[1], kept=us[0] < us[1])
     if path:
         cache = load_cache(path)
-        cache[key(nx, ny, precision)] = dict(rows=rows, waves=waves, step_ms=ms)
+        cache.pop(key(nx, ny, precision), None)
+        if res["kept"]:
+            cache[key(nx, ny, precision)] = dict(rows=rows, waves=waves, step_ms=ms)
         tmp = path + ".tmp"
         with open(tmp, "w") as f:
             json.dump(cache, f, indent=1, sort_keys=True)
@@ -129,7 +160,8 @@ def main():
         print(f"[tune] {shape} {p}", flush=True)
         r = tune(nx, ny, prec, steps=args.steps, verbose=True, path=args.out)
         print(f"[tune] {shape} {p}: rows {r['rows']} waves {r['waves']} "
-              f"{1e3 * r['step_ms']:.1f} us/step", flush=True)
+              f"{r['us_per_step']:.1f} us/step, untuned {r['untuned_us_per_step']:.1f}: "
+              f"{'kept' if r['kept'] else 'not kept'}", flush=True)
 
 
 if __name__ == "__main__":
