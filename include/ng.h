@@ -339,7 +339,8 @@ const char* ng_last_error(const ng_solver* s);
  *          was rejected).
  * The state is bitwise that of ng_init_conserved(U_in) + ng_step(1).  Every
  * call on a GPU shares that GPU's scratch (each call writes all of it that it
- * reads): calls that overlap on one GPU race, so enqueue them on one stream.
+ * reads, except a counter of finished workgroups, which it finds and leaves at
+ * zero): calls that overlap on one GPU race, so enqueue them on one stream.
  * Errors: NG_EINVAL (invalid arguments, as ng_init_state, or another
  * precision), NG_ENOMEM (grid beyond the scratch), NG_EDEVICE; the text is
  * returned by ng_static_last_error (per host thread). */
