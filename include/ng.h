@@ -421,15 +421,19 @@ int ng_batch_set_fused_accept(ng_batch* b, int32_t on);
 int ng_batch_set_small_limit(ng_batch* b, int64_t max_cells);
 
 /* Cooperative path of a batch (see ng_set_coop): a batch's only live solve
- * takes it as a lone solve does; several 1D solves take it side by side, in up
- * to four cooperative launches per call whose workgroups are dealt by solve
- * size, while each has at most max_cells cells and in FP64 their segments (60
- * cells) number at most 45000, in calls of at least four to fifteen steps per
- * launch (shorter calls take the persistent path or one launch per step).  The
- * launches' exchange (1.1 KB per workgroup, at most 0.9 MB) lies in arena space
- * that no solve has; a new solve that needs the space gets it.  With less room
- * than that, fewer workgroups take the work, or the other paths; a lone solve's
- * exchange then lies in its own reduction space. */
+ * takes it as a lone solve does; several 1D solves take it side by side, in
+ * launches whose workgroups are dealt by solve size, while each has at most
+ * max_cells cells.  Solves of one kernel (scheme, flux, and the closures that
+ * are compiled in: four kernels in FP32 and mixed, seven in FP64) share a
+ * launch, or several where they are more than its 768 workgroups; the launches
+ * of a call follow one another.  Together they have at most 3072 workgroups, and
+ * in FP64 the solves of one kernel at most 45000 segments (60 cells); else the
+ * other paths run.  So do calls of fewer than four to fifteen steps per launch
+ * (the persistent path or one launch per step).  The launches' exchange (1.1 KB
+ * per workgroup, at most 0.9 MB) lies in arena space that no solve has; a new
+ * solve that needs the space gets it.  With less room than that, fewer
+ * workgroups take the work, or the other paths; a lone solve's exchange then
+ * lies in its own reduction space. */
 int ng_batch_set_coop(ng_batch* b, int64_t max_cells, int32_t spin_limit);
 
 /* Launch shape of the batched step kernels (see ng_set_launch). */

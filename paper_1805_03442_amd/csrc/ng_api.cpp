@@ -120,11 +120,15 @@ constexpr int64_t kResSegs = 4;
 // workgroups (resident_fleet), which together have at most this many times the
 // workgroups of one launch.
 constexpr size_t kResLaunches = 4;
-// ... in FP64 while they have at most this many segments: more keep the chip
-// full without it, and its two waves per SIMD then lose to three (us per step,
-// cooperative and one launch per step: 48 solves, 0.58 M cells 29 and 65; 130,
-// 2.0 M 97 and 121; 200, 3.1 M 163 and 160; 280, 5.1 M 316 and 233.  FP32 and
-// mixed: 3.1 M cells 30 and 56, 35 and 69; 5.1 M 51 and 72, 70 and 99).
+// ... in FP64 while those of one kernel have at most this many segments: more
+// keep the chip full without it, and its two waves per SIMD then lose to three
+// (us per step, cooperative and one launch per step: 48 solves, 0.58 M cells 29
+// and 65; 130, 2.0 M 97 and 121; 200, 3.1 M 163 and 160; 280, 5.1 M 316 and 233.
+// FP32 and mixed: 3.1 M cells 30 and 56, 35 and 69; 5.1 M 51 and 72, 70 and 99).
+// Each kernel for itself, since a launch per step of several kernels' solves is
+// the general kernel's, which costs more too: two, three and four kernels with
+// 12000 segments each 39 and 62, 58 and 80, 76 and 100; with 22000 62 and 92, 100
+// and 120, 137 and 156; with 40000 115 and 140, 179 and 193, 244 and 255.
 constexpr int64_t kResFleetSegs64 = 45000;
 // Pinned staging buffers of the initial-state upload (two, used in turn).
 constexpr size_t kStageBytes = size_t(16) << 20;
