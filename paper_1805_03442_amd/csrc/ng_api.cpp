@@ -73,6 +73,14 @@ constexpr int64_t kFusedMaxBlocks = 256;
 // and 555, 323 and 381): there the waves have work for many times the launch's
 // cost, and plain loads use the L2.
 constexpr int64_t kCoopCells = int64_t(1) << 22;
+// The same for the FP64 kernels of 2D solves whose closures are not compiled in
+// (any exponents, or ends or the HLL flux with the paper's): with both the row
+// march and the call they spill a hundred registers, one launch per step forty.
+// Us per step, cooperative and one launch per step, general closures, walls, HLL:
+// 300^2 23 and 30, 18 and 20, 19 and 22; 450^2 29 and 32, 23 and 23, 24 and 24;
+// 600^2 39 and 40, 30 and 28, 32 and 31; 800^2 63 and 60, 48 and 43, 52 and 46;
+// 2048^2 342 and 271, 259 and 154, 288 and 191.
+constexpr int64_t kCoopCellsSpill = 450 * 450;
 // Calls of fewer steps launch them one by one: a cooperative launch and the fold
 // of its records cost about three steps (one step of 200 to 600^2 cells 47 to 57
 // us against 34 to 42 us; four steps 54 to 85 against 56 to 99).
@@ -954,6 +962,9 @@ int choose_coop(ng_batch* b)
             } else {
                 if (!resident_shape2d(s.d, b->prec, all, full) ||
                     !resident_shape2d(s.d, b->prec, cap, r))
+                    continue;
+                if (b->prec == NG_FP64 && (r.s == 0 || r.s == 3 || r.s == 5) &&
+                    b->coop_limit < 0 && s.d.ncell > kCoopCellsSpill)
                     continue;
                 CK(b, resident2d_capacity(kind_of(b->prec), r.s, r.waves, &per_cu));
             }
