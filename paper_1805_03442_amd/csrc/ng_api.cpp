@@ -73,14 +73,23 @@ constexpr int64_t kFusedMaxBlocks = 256;
 // and 555, 323 and 381): there the waves have work for many times the launch's
 // cost, and plain loads use the L2.
 constexpr int64_t kCoopCells = int64_t(1) << 22;
-// The same for the FP64 kernels of 2D solves whose closures are not compiled in
-// (any exponents, or ends or the HLL flux with the paper's): with both the row
-// march and the call they spill a hundred registers, one launch per step forty.
-// Us per step, cooperative and one launch per step, general closures, walls, HLL:
-// 300^2 23 and 30, 18 and 20, 19 and 22; 450^2 29 and 32, 23 and 23, 24 and 24;
-// 600^2 39 and 40, 30 and 28, 32 and 31; 800^2 63 and 60, 48 and 43, 52 and 46;
-// 2048^2 342 and 271, 259 and 154, 288 and 191.
-constexpr int64_t kCoopCellsSpill = 450 * 450;
+// Earlier where a 2D kernel is slower than that.  The FP64 kernels but those with
+// compiled closures for the solve's ends (launch_resident2d's 0, 3 and 5) spill a
+// hundred registers, one launch per step forty: only with at most so many rows of
+// a column strip, two on a SIMD, some more with closures picked at run time and no
+// end.  Where they have general exponents, which cost both alike, up to
+// kCoopCellsGeneral cells.  Us per step, cooperative and one launch per step,
+// walls, HLL, closures of the section 3 gas without ends, general closures: 4000x30
+// (2010 rows) 18.9 and 21.8, 20.6 and 23.3, 17.0 and 21.3, 24 and 31; 360^2 (2160)
+// 21.3 and 20.8, 23.2 and 22.9, 19.6 and 20.1, 27 and 30; 4000x40 (2680) 22.8 and
+// 21.6, 24.6 and 23.3, 19.8 and 21.0, 28 and 31; 1000x180 (3060) 24.1 and 21.9,
+// 25.2 and 23.7, 21.8 and 21.0, 30 and 31; 800^2 48 and 43, 52 and 46, general 63
+// and 60.  FP32 with the HLL flux: 4096x900 57 and 61, 2900x1400 62.1 and 61.6,
+// 8192x512 66 and 63.
+constexpr int64_t kCoopRowsSpill = 2048;
+constexpr int64_t kCoopRowsSpillPicked = 2800;
+constexpr int64_t kCoopCellsGeneral = 450 * 450;
+constexpr int64_t kCoopCellsHll32 = int64_t(7) << 19;
 // Calls of fewer steps launch them one by one: a cooperative launch and the fold
 // of its records cost about three steps (one step of 200 to 600^2 cells 47 to 57
 // us against 34 to 42 us; four steps 54 to 85 against 56 to 99).
@@ -728,6 +737,18 @@ bool resident_shape2d(const InstDesc& d, int prec, int64_t cap, ResLaunch& r)
     return true;
 }
 
+// Whether a 2D solve of at most kCoopCells cells is faster on the cooperative
+// path, by its kernel (resident_shape2d's r.s).
+bool coop2d_pays(const InstDesc& d, int prec, int kernel)
+{
+    if (prec == NG_FP64 && (kernel == 0 || kernel == 3 || kernel == 5)) {
+        if (d.cl_recipe == 0) return d.ncell <= kCoopCellsGeneral;
+        return cdiv(d.nx, kInterior) * d.ny <=
+               (kernel == 0 ? kCoopRowsSpillPicked : kCoopRowsSpill);
+    }
+    return !(prec == NG_FP32 && kernel == 5 && d.ncell > kCoopCellsHll32);
+}
+
 // The cooperative launches of several 1D solves side by side (slots in `ids`, all
 // of one kernel): four-wave workgroups, three to a CU at most, each with a run
 // of segments of one solve; the runs are as short as lets all solves into one
@@ -963,9 +984,7 @@ int choose_coop(ng_batch* b)
                 if (!resident_shape2d(s.d, b->prec, all, full) ||
                     !resident_shape2d(s.d, b->prec, cap, r))
                     continue;
-                if (b->prec == NG_FP64 && (r.s == 0 || r.s == 3 || r.s == 5) &&
-                    b->coop_limit < 0 && s.d.ncell > kCoopCellsSpill)
-                    continue;
+                if (b->coop_limit < 0 && !coop2d_pays(s.d, b->prec, full.s)) continue;
                 CK(b, resident2d_capacity(kind_of(b->prec), r.s, r.waves, &per_cu));
             }
             if ((int64_t)per_cu * b->dev_cus < r.grid || r.rounds > 2 * full.rounds + 2) continue;
