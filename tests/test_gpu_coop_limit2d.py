@@ -1,8 +1,7 @@
 """GPU: how many cells a lone 2D solve may have on the cooperative path.  The FP64
 kernels without compiled closures leave it earlier, the FP32 HLL kernel somewhat; a
-limit set by the caller
-holds for all.  Whether a call was cooperative shows at a spin limit of 0, where it
-stalls at its first wait and no other path does."""
+limit set by the caller holds for all.  Whether a call was cooperative shows at a
+spin limit of 0, where it stalls at its first wait and no other path does."""
 import numpy as np
 import pytest
 
