@@ -985,7 +985,7 @@ int choose_coop(ng_batch* b)
                     !resident_shape2d(s.d, b->prec, cap, r))
                     continue;
                 if (b->coop_limit < 0 && !coop2d_pays(s.d, b->prec, full.s)) continue;
-                CK(b, resident2d_capacity(kind_of(b->prec), r.s, r.waves, &per_cu));
+                CK(b, resident2d_capacity(kind_of(b->prec), r.s, r.grid > 1, r.waves, &per_cu));
             }
             if ((int64_t)per_cu * b->dev_cus < r.grid || r.rounds > 2 * full.rounds + 2) continue;
             r.one.inst = live[dim][0];

@@ -65,7 +65,7 @@ hipError_t launch_resident_after(const InstDesc* descs, InstCtrl* ctrls, const R
 // wave each.  s: 0..2 periodic HLLC with closure recipe s, 3 HLLC with any ends,
 // 4 the same with recipe 3 (FP64), 5 HLL.
 int resident2d_max_waves(int prec);
-hipError_t resident2d_capacity(int prec, int s, int waves, int* blocks_per_cu);
+hipError_t resident2d_capacity(int prec, int s, bool coh, int waves, int* blocks_per_cu);
 hipError_t launch_resident2d(int prec, int s, const InstDesc* descs, InstCtrl* ctrls, int inst,
                              const ResSync& sync, int grid, int chunks, int waves, int64_t nsteps,
                              int32_t spin_limit, hipStream_t st);

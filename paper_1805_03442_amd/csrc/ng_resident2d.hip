@@ -6,7 +6,11 @@
 // two state buffers; loads and stores are agent-scope (a step's loads must see
 // what workgroups on other XCDs stored), and a wave's stores have reached memory
 // before its workgroup publishes the step's signal speed.  All workgroups then
-// take the next dt of eq. (16) alike (ng_exchange.hpp).
+// take the next dt of eq. (16) alike (ng_exchange.hpp).  A grid alone in one
+// workgroup (60x4 at most) needs none of that and has a form of its own (Coh =
+// false): us per step at 60x4 and, in the others' form, at 48x40 and 600^2, FP32,
+// 2.79, 3.98, 8.62; with one form whose exchange a test skips 2.88, 4.03, 8.68;
+// with one form that always exchanges 3.53, 3.98, 8.62.
 //
 // It replaces two launches per step (the step and its acceptance) on grids that
 // do not fill the chip for long: kCoopCells in ng_api.cpp says where the line
@@ -33,7 +37,7 @@ __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)
 // S: 0..2 the periodic HLLC step with closure recipe S (0: general), 3 the HLLC
 // step with any ends and the general closures, 4 the same with recipe 3 (FP64),
 // 5 the HLL step with any ends.
-template <class P, int S>
+template <class P, int S, bool Coh>
 __global__ void __launch_bounds__(P::kRes2Threads) run_resident2d_kernel(
     const InstDesc* __restrict__ descs, const InstCtrl* __restrict__ ctrls, int inst, int chunks,
     const uint32_t* __restrict__ base, uint64_t* __restrict__ slots, CoopRec* __restrict__ recs,
@@ -84,10 +88,10 @@ __global__ void __launch_bounds__(P::kRes2Threads) run_resident2d_kernel(
         acc_init(acc);
         if (work && r0 < r1) {
             if constexpr (S <= 2)
-                march2d<P, 0, false, S, true, kRing>(d, k, cur, gsrc, strip, r0, r1, lane, acc);
+                march2d<P, 0, false, S, Coh, kRing>(d, k, cur, gsrc, strip, r0, r1, lane, acc);
             else
-                march2d<P, S == 5 ? 1 : 0, true, S == 4 ? 3 : 0, true, kRing>(d, k, cur, gsrc, strip, r0, r1,
-                                                                      lane, acc);
+                march2d<P, S == 5 ? 1 : 0, true, S == 4 ? 3 : 0, Coh, kRing>(d, k, cur, gsrc, strip, r0, r1,
+                                                                     lane, acc);
         }
         acc_finish<P>(acc, k);
         {
@@ -98,13 +102,13 @@ __global__ void __launch_bounds__(P::kRes2Threads) run_resident2d_kernel(
                 s_fl[wave] = fl;
             }
         }
-        stores_done();
+        if constexpr (Coh) stores_done();
         __syncthreads();
         if (wave == 0) {
             double m = wave_max(lane < nw ? s_sm[lane] : 0.0);
             uint32_t f = wave_flags(lane < nw ? s_fl[lane] : 0u);
             bool out = false;
-            if (G > 1u)
+            if constexpr (Coh)
                 out = exchange_slots<R>(slots + (size_t)(st & 1) * nwg * kResSlot, G, b, gen, lane,
                                         spin_limit, m, f);
             if (lane == 0) s_c.decide(d, c, out, m, f);
@@ -133,7 +137,7 @@ __global__ void __launch_bounds__(P::kRes2Threads) run_resident2d_kernel(
             if (st_c >= 1) {
                 // the sums of the accepted state, from its cells
                 const typename P::K k = P::make(d, 0.0);
-                const Planes<St, NC, true> pl(d.buf[cur0 ^ (nacc & 1)], d.ncell);
+                const Planes<St, NC, Coh> pl(d.buf[cur0 ^ (nacc & 1)], d.ncell);
                 const int x0 = strip * kInterior;
                 const int w = (int)d.nx - x0 < kInterior ? (int)d.nx - x0 : kInterior;
                 acc_init(acc);
@@ -154,28 +158,28 @@ __global__ void __launch_bounds__(P::kRes2Threads) run_resident2d_kernel(
 
 // ================================================================ launchers
 
-template <template <int> class Pol>
+template <template <int> class Pol, bool Coh>
 static const void* kernel2d_of(int s)
 {
     using P = Pol<5>;
     switch (s) {
-    case 0: return (const void*)run_resident2d_kernel<P, 0>;
-    case 1: return (const void*)run_resident2d_kernel<P, 1>;
-    case 2: return (const void*)run_resident2d_kernel<P, 2>;
-    case 3: return (const void*)run_resident2d_kernel<P, 3>;
-    case 5: return (const void*)run_resident2d_kernel<P, 5>;
+    case 0: return (const void*)run_resident2d_kernel<P, 0, Coh>;
+    case 1: return (const void*)run_resident2d_kernel<P, 1, Coh>;
+    case 2: return (const void*)run_resident2d_kernel<P, 2, Coh>;
+    case 3: return (const void*)run_resident2d_kernel<P, 3, Coh>;
+    case 5: return (const void*)run_resident2d_kernel<P, 5, Coh>;
     default: break;
     }
     if constexpr (std::is_same<typename P::K, K64>::value)
-        if (s == 4) return (const void*)run_resident2d_kernel<P, 4>;
+        if (s == 4) return (const void*)run_resident2d_kernel<P, 4, Coh>;
     return nullptr;
 }
 
-static const void* kernel2d_of(int prec, int s)
+static const void* kernel2d_of(int prec, int s, bool coh)
 {
-    if (prec == 0) return kernel2d_of<Plain64>(s);
-    if (prec == 1) return kernel2d_of<Dev32>(s);
-    if (prec == 2) return kernel2d_of<Mix32>(s);
+    if (prec == 0) return coh ? kernel2d_of<Plain64, true>(s) : kernel2d_of<Plain64, false>(s);
+    if (prec == 1) return coh ? kernel2d_of<Dev32, true>(s) : kernel2d_of<Dev32, false>(s);
+    if (prec == 2) return coh ? kernel2d_of<Mix32, true>(s) : kernel2d_of<Mix32, false>(s);
     return nullptr;
 }
 
@@ -185,9 +189,9 @@ int resident2d_max_waves(int prec)
                       : (prec == 1 ? Dev32<5>::kRes2Threads : Mix32<5>::kRes2Threads)) / kWave;
 }
 
-hipError_t resident2d_capacity(int prec, int s, int waves, int* blocks_per_cu)
+hipError_t resident2d_capacity(int prec, int s, bool coh, int waves, int* blocks_per_cu)
 {
-    const void* k = kernel2d_of(prec, s);
+    const void* k = kernel2d_of(prec, s, coh);
     if (!k || waves < 2 || waves > resident2d_max_waves(prec)) return hipErrorInvalidValue;
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k, waves * kWave, 0);
 }
@@ -196,7 +200,7 @@ hipError_t launch_resident2d(int prec, int s, const InstDesc* descs, InstCtrl* c
                              const ResSync& sync, int grid, int chunks, int waves, int64_t nsteps,
                              int32_t spin_limit, hipStream_t st)
 {
-    const void* k = kernel2d_of(prec, s);
+    const void* k = kernel2d_of(prec, s, grid > 1);
     // (grid * waves covers strips * chunks: waves beyond them idle)
     if (!k || grid < 1 || grid > sync.nwg || grid > kCoopFlat || chunks < 1 || waves < 2 ||
         waves > resident2d_max_waves(prec) || nsteps < 1 || nsteps > kCoopMaxSteps || spin_limit < 0)
