@@ -278,7 +278,8 @@ int ng_set_small_limit(ng_solver* s, int64_t max_cells);
  * limit, graph length and acceptance are the defaults and steps are not timed.
  * max_cells: -1 restores the default (4194304; less for 2D solves in FP64 with the
  * HLL flux or closures that are not compiled in for their ends, from some 10^5
- * cells, and in FP32 with HLL, 3670016), 0 turns the path off (the persistent one-workgroup path or one launch per step take over).
+ * cells, and in FP32 with HLL, 3670016), 0 turns the path off (the persistent
+ * one-workgroup path or one launch per step take over).
  * spin_limit: polls of memory (about a microsecond each) a workgroup spends
  * in one barrier wait before it gives up (-1: the default, 1048576).  A wait
  * that runs out (the workgroups were kept off the GPU by a long kernel of
