@@ -706,11 +706,11 @@ void resident_shape(const InstDesc& d, int prec, int64_t cap, ResLaunch& r)
                                      resident_max_waves(kind_of(prec)));
 }
 
-// Shape of a 2D solve's cooperative launch on at most `cap` workgroups: one row per wave, or two, when that
-// gives every wave a SIMD of its own (workgroups of four waves); else every
-// strip's rows in as many runs as the largest workgroups have waves for.  A wave
-// needs four rows more than it updates, but the step then lasts as long as its
-// longest run.  Us per step with runs of 1, 2, 3 and 4 rows, FP32 / FP64: 48x40
+// Shape of a 2D solve's cooperative launch on at most `cap` workgroups: one row
+// per wave, or two, when that gives every wave a SIMD of its own (workgroups of
+// four waves); else every strip's rows in as many runs as the largest workgroups
+// have waves for.  A wave needs four rows more than it updates, but the step then
+// lasts as long as its longest run.  Us per step with runs of 1, 2, 3 and 4 rows, FP32 / FP64: 48x40
 // 4.0 / 6.2, 4.7 / 8.1, 5.4 / 10.1, 6.1 / 11.9; 256^2 (five waves in some
 // workgroups at one row) 5.8 / 10.3, 5.4 / 9.1, 5.8 / 11.0, 6.2 / 12.6; 600^2
 // (as many waves as fit below 4) 8.7 / 18.0, the same, the same, 9.8 / 20.9.
@@ -1043,10 +1043,10 @@ int choose_coop(ng_batch* b)
 }
 
 // Enqueue the cooperative launches of the dims in `dims` (a bit each) for nsteps
-// steps (each of at most kCoopMaxSteps steps).  *ran: false when the runtime refused the first of them
-// and nothing was enqueued -- the device gives its cooperative queue to one
-// process at a time.  The object then keeps to the other paths, whose tables
-// hold the same solves, until the next ng_batch_set_coop.
+// steps (each of at most kCoopMaxSteps steps).  *ran: false when the runtime
+// refused the first of them and nothing was enqueued -- the device gives its
+// cooperative queue to one process at a time.  The object then keeps to the other
+// paths, whose tables hold the same solves, until the next ng_batch_set_coop.
 int enqueue_coop(ng_batch* b, int64_t nsteps, int dims, bool* ran)
 {
     *ran = false;
