@@ -1401,12 +1401,12 @@ bool capturing(const ng_batch* b)
     return st != hipStreamCaptureStatusNone;
 }
 
-// Enqueue nsteps steps of every live solve.
-int enqueue_steps(ng_batch* b, int64_t nsteps)
+// Enqueue nsteps steps of every live solve (recorded: into a caller's graph).
+int enqueue_steps(ng_batch* b, int64_t nsteps, bool recorded)
 {
     int rc = rebuild(b);
     if (rc) return rc;
-    if (capturing(b))
+    if (recorded)
         b->captured = true;
     else
         for (Slot& s : b->slots)
@@ -2151,7 +2151,7 @@ int ng_step(ng_solver* s, int64_t nsteps)
     int rc = s->limited ? set_limits(s->b, s->slot, INFINITY, -1) : NG_OK;
     if (!rc) {
         s->limited = false;
-        rc = enqueue_steps(s->b, nsteps);
+        rc = enqueue_steps(s->b, nsteps, false);
     }
     return solver_rc(s, rc);
 }
@@ -2189,7 +2189,7 @@ int ng_run_to_time(ng_solver* s, double t_end, int64_t max_steps, int64_t* steps
         double est = c.dt_cfl > 0.0 ? (t_end - c.t) / c.dt_cfl : (double)left;
         int64_t chunk = (int64_t)std::min<double>((double)left, ceil(est * 1.02) + 1.0);
         if (chunk < 1) chunk = 1;
-        rc = enqueue_steps(b, chunk);
+        rc = enqueue_steps(b, chunk, capturing(b));
         if (rc) return solver_rc(s, rc);
     }
 }
@@ -2461,7 +2461,7 @@ int ng_batch_add(ng_batch* b, const ng_gas* gas, const ng_grid* grid, const ng_n
 int ng_batch_run(ng_batch* b, int64_t nsteps)
 {
     if (!b || nsteps < 0) return NG_EINVAL;
-    return enqueue_steps(b, nsteps);
+    return enqueue_steps(b, nsteps, capturing(b));
 }
 
 int ng_batch_poll(ng_batch* b, int32_t* done_slots, int32_t cap, int32_t* ndone)
