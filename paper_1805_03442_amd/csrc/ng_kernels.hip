@@ -549,8 +549,8 @@ __global__ void __launch_bounds__(256) readout_kernel(const InstDesc* __restrict
                                                       int32_t* __restrict__ status)
 {
     const InstDesc& d = descs[inst];
-    if (status && blockIdx.x == 0 && threadIdx.x == 0) *status = ctrls[inst].status;
-    const St* __restrict__ src = (const St*)d.buf[ctrls[inst].cur];
+    const int32_t cur = ctrls[inst].cur, left = ctrls[inst].status;
+    const St* __restrict__ src = (const St*)d.buf[cur];
     constexpr int iE = NC == 5 ? 3 : 2, iV = NC - 1;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m;
          i += (int64_t)gridDim.x * blockDim.x) {
@@ -571,6 +571,7 @@ __global__ void __launch_bounds__(256) readout_kernel(const InstDesc* __restrict
         }
         for (int c = 0; c < NC; c++) __builtin_nontemporal_store(U[c], out + c * m + i);
     }
+    if (status && blockIdx.x == 0 && threadIdx.x == 0) *status = left;
 }
 
 // Set the stop condition of a set of solves (a kernel, so that it can sit in
